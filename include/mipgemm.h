@@ -451,13 +451,13 @@ int mipgemm_pack_b(int64_t k, int64_t n,
  * the paper's table of matrix-oriented instructions (vpdpwssd, smopa).  This device has no
  * integer matrix instruction for 16-bit operands, so the product is built from 8-bit ones:
  * with x' = x - 128 every int16 is two signed bytes, x' = 256 h + l, and the sum over k of
- * a b is 65536 (ah bh) + 256 (ah bl + al bh) + (al bl) + 128 (sum a' + sum b') + 16384 k,
- * three s8 x s8 GEMMs of this library on the byte planes (the middle one of depth 2 k) and
- * one pass that puts the pieces together: about four times the work of an 8-bit product of
+ * a b is 65536 (ah bh) + 256 (ah bl + al bh) + (al bl) + 128 (sum a + sum b) - 16384 k,
+ * formed by one kernel that splits the operands on their way to the matrix instructions
+ * (operands without 16-byte runs are rewritten first): four times the work of an 8-bit product of
  * the same size.  Sums wrap modulo 2^32, which products of up to 2^30 reach much sooner
  * than bytes do.  Arguments and their numbers as for mipgemm_s8s8s32 (lda, ldb count
  * elements); the workspace is REQUIRED here for k > 0: mipgemm_workspace_size_s16(m, n, k)
- * bytes of device memory (planes, plane sums, three m x n int32 products); a null
+ * bytes of device memory (rewritten operands, partial sums); a null
  * workspace is -14, one that is too small -15, and nothing is touched.
  */
 size_t mipgemm_workspace_size_s16(int64_t m, int64_t n, int64_t k);

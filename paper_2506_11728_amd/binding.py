@@ -385,7 +385,7 @@ def mipgemm_workspace_size_s16(m, n, k) -> int:
 
 def mipgemm_s16s16s32(m, n, k, A, lda, orderA, B, ldb, orderB, C, ldc, orderC, mode,
                       workspace=None, workspace_bytes=0, stream=None, check=True):
-    """C = [C +] A * B with int16 operands, through byte planes on the 8-bit kernels; needs a
+    """C = [C +] A * B with int16 operands, as byte planes on the 8-bit matrix instructions; needs a
     workspace of mipgemm_workspace_size_s16(m, n, k) bytes."""
     return _call("mipgemm_s16s16s32", m, n, k, A, lda, orderA, B, ldb, orderB, C, ldc, orderC,
                  mode, workspace, workspace_bytes, stream, check)

@@ -1,6 +1,5 @@
-// C-ABI entry point of the product with 16-bit operands: the operands are split into byte
-// planes, three 8-bit GEMMs of this library run on them, and one kernel puts the pieces
-// together (kernel_s16.hip).  Host only.
+// C-ABI entry point of the product with 16-bit operands (kernel_s16.hip): argument checks and
+// the workspace.  Host only.
 #include "api_internal.h"
 
 using mip::order_ok;
@@ -9,8 +8,11 @@ namespace {
 
 int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
 
-// The workspace of a call, every part a multiple of 256 bytes: the planes of A (m rows of
-// 2 kp bytes) and of B (n rows), four vectors of plane sums, three dense m x n int32 products.
+// The workspace a caller is asked for, every part a multiple of 256 bytes: A and B as m and n rows of
+// 2 kp bytes (operands that cannot be streamed as they are stored are rewritten there), and
+// room for four vectors of sums and three dense m x n int32 products, of which the partial
+// sums of a split k take what they need.  The size is part of the interface: callers have
+// allocated by it.
 struct S16Layout {
   int64_t kp;
   size_t planes_a, planes_b, sums, product, total;
@@ -95,35 +97,15 @@ int mipgemm_s16s16s32(int64_t m, int64_t n, int64_t k, const int16_t *A, int64_t
   const size_t skip = (256 - reinterpret_cast<uintptr_t>(ws) % 256) % 256;
   if (workspace_bytes < skip + L.total) return -15;
   ws += skip;
-  uint8_t *PA = ws, *PB = PA + L.planes_a;
-  int32_t *sums = reinterpret_cast<int32_t *>(PB + L.planes_b);
-  int32_t *sA = sums, *sB = sums + 2 * rm + (2 * rm % 4 ? 4 - 2 * rm % 4 : 0);  // (16-byte aligned)
-  int32_t *T1 = reinterpret_cast<int32_t *>(reinterpret_cast<uint8_t *>(sums) + L.sums);
-  int32_t *T2 = reinterpret_cast<int32_t *>(reinterpret_cast<uint8_t *>(T1) + L.product);
-  int32_t *T3 = reinterpret_cast<int32_t *>(reinterpret_cast<uint8_t *>(T2) + L.product);
-  const int64_t kp = L.kp;
-
-  hipError_t e = mip::launch_split_planes(X, x_sr, x_sk, rm, k, kp, PA, true, s);   // [ah | al]
-  if (e != hipSuccess) return static_cast<int>(e);
-  e = mip::launch_split_planes(Y, y_sr, y_sk, rn, k, kp, PB, false, s);              // [bl | bh]
-  if (e != hipSuccess) return static_cast<int>(e);
-  // a row of 2 kp bytes is two columns of kp: one launch per operand sums both planes of every row
-  e = mip::launch_column_sums(kp, 2 * rm, PA, kp, sA, s);
-  if (e == hipSuccess) e = mip::launch_column_sums(kp, 2 * rn, PB, kp, sB, s);
-  if (e != hipSuccess) return static_cast<int>(e);
-  // the three byte products, each an s8 x s8 GEMM of this library on the planes
-  const int R = MIPGEMM_ROW_MAJOR, Cm = MIPGEMM_COL_MAJOR, OVW = MIPGEMM_OVERWRITE;
-  int rc = mip::run_gemm(0, 0, 0, 1.0f, rm, rn, kp, PA, 2 * kp, R, PB + kp, 2 * kp, Cm, T1, rn, R, OVW,
-                         nullptr, 0, stream);                                   // ah bh
-  if (rc == 0)
-    rc = mip::run_gemm(0, 0, 0, 1.0f, rm, rn, 2 * kp, PA, 2 * kp, R, PB, 2 * kp, Cm, T2, rn, R, OVW,
-                       nullptr, 0, stream);                                     // ah bl + al bh
-  if (rc == 0)
-    rc = mip::run_gemm(0, 0, 0, 1.0f, rm, rn, kp, PA + kp, 2 * kp, R, PB, 2 * kp, Cm, T3, rn, R, OVW,
-                       nullptr, 0, stream);                                     // al bl
-  if (rc != 0) return rc > 0 ? rc : static_cast<int>(hipErrorInvalidValue);  // (sizes were checked above)
-  return static_cast<int>(mip::launch_combine_planes(T1, T2, T3, sA, sB, rm, rn, k, C, ldc,
-                                                     accumulate, s));
+  mip::S16Problem p;
+  p.m = rm; p.n = rn; p.k = k;
+  p.A = X; p.a_sm = x_sr; p.a_sk = x_sk;
+  p.B = Y; p.b_sk = y_sk; p.b_sn = y_sr;
+  p.C = C; p.ldc = ldc;
+  p.accumulate = accumulate;
+  p.ws = ws;
+  p.ws_bytes = workspace_bytes - skip;
+  return static_cast<int>(mip::launch_s16(p, s));
 }
 
 }  // extern "C"

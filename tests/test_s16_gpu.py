@@ -1,5 +1,5 @@
-"""GPU parity of the product with 16-bit operands (byte planes on the 8-bit kernels) against
-the int16 oracle, bit for bit, through the C ABI."""
+"""GPU parity of the product with 16-bit operands against the int16 oracle, bit for bit, through the
+C ABI."""
 import numpy as np
 import pytest
 
@@ -145,3 +145,31 @@ def test_s16_empty_problems_and_error_paths(gpu):
     assert call(-1, 4, 5, dA, 5, R, dA, 4, R, dC, 4, R, OVW, workspace=ws, workspace_bytes=need) == -1
     torch.cuda.synchronize()
     assert np.array_equal(dC.cpu().numpy(), C0)
+
+
+@pytest.mark.parametrize("variant", ["s16_64", "s16_128"])
+@pytest.mark.parametrize("orders", [(0, 1, 0), (0, 0, 0), (1, 0, 0), (1, 1, 1)])
+def test_s16_tile_edges_block_counts_and_ranges(gpu, oracle, variant, orders):
+    """Both tiles at their edges, one to five blocks of k and remainders in eights (streamed as stored)
+    and in twos (one operand rewritten, the other not), and k in ranges whose sums meet in slots."""
+    oa, ob, oc = orders
+    for (m, n, k) in ((8, 8, 8), (64, 128, 64), (136, 120, 72), (72, 264, 128), (128, 64, 200), (136, 136, 264),
+                      (136, 136, 70), (130, 136, 320)):
+        _check(gpu, oracle, m, n, k, oa, ob, oc, W.OVERWRITE, 0, "edges", seed=9, variant=variant)
+    for ranges in (2, 3, 5):
+        with gpu.tuning(MIPGEMM_SPLITK=str(ranges)):
+            _check(gpu, oracle, 136, 200, 1352, oa, ob, oc, W.ACCUMULATE, 8, "uniform", seed=10, variant=variant)
+
+
+def test_s16_rows_further_apart_than_32_bit_offsets(gpu, oracle):
+    import torch
+    m, n, k, lda = 64, 16, 72, (1 << 25) + (1 << 21)   # the last row of A starts 4.5 GB behind the first
+    A2, B2 = _operands(m, n, k, "uniform", 11)
+    A = torch.empty(m * lda, dtype=torch.int16, device="cuda")
+    A.view(m, lda)[:, :k] = torch.from_numpy(A2).cuda()
+    B, C = torch.from_numpy(B2).cuda(), torch.zeros((m, n), dtype=torch.int32, device="cuda")
+    ws = torch.empty(gpu.mipgemm_workspace_size_s16(m, n, k), dtype=torch.uint8, device="cuda")
+    gpu.mipgemm_s16s16s32(m, n, k, A, lda, W.ROW_MAJOR, B, n, W.ROW_MAJOR, C, n, W.ROW_MAJOR, W.OVERWRITE,
+                          workspace=ws, workspace_bytes=ws.numel())
+    want = (A2.astype(np.int64) @ B2.astype(np.int64)).astype(np.int32)
+    assert np.array_equal(C.cpu().numpy(), want)
