@@ -1,4 +1,4 @@
-"""Thin ctypes binding of the C ABI declared in ``include/mipgemm.h``.
+"""Thin binding of the C ABI declared in ``include/mipgemm.h``.
 
 Argument marshalling only: every step of the GEMM runs in the HIP kernels of
 ``libmipgemm.so``.  Operands are device pointers: pass torch CUDA tensors (their
@@ -153,8 +153,57 @@ def load_library() -> ctypes.CDLL:
             lib.mipgemm_s8s8s32_noalloc.argtypes = _GEMM_ARGTYPES[:13] + [vp]
             lib.mipgemm_static_scratch_bytes.restype = ctypes.c_size_t
             lib.mipgemm_static_scratch_bytes.argtypes = []
+            _register_native(lib)
             _lib = lib
     return _lib
+
+
+# ---- calls ----
+# The entry points that run on the device go through _call.so (native/call.c), which converts the
+# arguments in C.  What it does not take (returning None), and everything where it has not been built, goes
+# through ctypes below.
+
+try:
+    from . import _call as _native
+except ImportError:  # no Python headers where the library was built
+    _native = None
+
+_GEMM_FORMAT, _CONV_FORMAT = "qqqpqipqipqiipzs", "qqqqqqqqqpppipzs"
+_BATCHED_FORMAT, _PACKED_FORMAT = "qqqpqiqpqiqpqiqqipzs", "qqqpqippqiipzs"
+_FORMATS = {
+    **{"mipgemm_" + t: _GEMM_FORMAT for t in ("s8s8s32", "u8s8s32", "s8u8s32", "s16s16s32")},
+    **{"mipgemm_" + t: _GEMM_FORMAT + "f" for t in ("s8s8f32", "u8s8f32", "s8u8f32", "s8s8s8", "u8s8s8", "s8u8s8")},
+    **{"mipgemm_%s_batched" % t: _BATCHED_FORMAT for t in ("s8s8s32", "u8s8s32", "s8u8s32")},
+    **{"mipgemm_%s_packed" % t: _PACKED_FORMAT for t in ("s8s8s32", "u8s8s32")},
+    "mipgemm_conv_s8u8s32": _CONV_FORMAT, "mipgemm_conv_s8u8f32": _CONV_FORMAT + "f",
+    "mipgemm_conv_s8u8s32_with_sums": _CONV_FORMAT + "p",
+    "mipgemm_conv_s8u8f32_with_sums": _CONV_FORMAT + "fp", "mipgemm_conv_s8u8s8": _CONV_FORMAT + "fp",
+}
+
+
+def _register_native(lib):
+    if _native is not None:
+        for name, fmt in _FORMATS.items():
+            _native.register(name, fmt, ctypes.cast(getattr(lib, name), ctypes.c_void_p).value)
+
+
+def _run(check, name, *args):
+    """Calls the entry point; the arguments in the order of its prototype, as the caller gave them."""
+    rc = _native.call(name, *args) if _native is not None and _lib is not None else None
+    if rc is None:
+        fn = getattr(load_library(), name)
+        rc = fn(*[_stream(x) if f == "s" else _ptr(x) if f == "p" else x
+                  for f, x in zip(_FORMATS[name], args)])
+    if check and rc != 0:
+        raise MipGemmError(rc, mipgemm_strerror(rc))
+    return rc
+
+
+def _tell_stream_source(torch):
+    """From the first call on (which has initialised torch's runtime), None as a stream is looked up without torch.cuda.current_stream's Stream object."""
+    device, handle = (getattr(torch._C, n, None) for n in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
+    if _native is not None and device is not None and handle is not None:
+        _native.stream_source(device, handle)
 
 
 def _ptr(x):
@@ -168,7 +217,9 @@ def _ptr(x):
 def _stream(stream):
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        current = torch.cuda.current_stream().cuda_stream
+        _tell_stream_source(torch)
+        return current or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None    # torch.cuda.Stream
@@ -176,12 +227,8 @@ def _stream(stream):
 
 def _call(name, m, n, k, A, lda, orderA, B, ldb, orderB, C, ldc, orderC, mode,
           workspace, workspace_bytes, stream, check, *extra):
-    rc = getattr(load_library(), name)(
-        m, n, k, _ptr(A), lda, orderA, _ptr(B), ldb, orderB, _ptr(C), ldc, orderC, mode,
-        _ptr(workspace), workspace_bytes, _stream(stream), *extra)
-    if check and rc != 0:
-        raise MipGemmError(rc, mipgemm_strerror(rc))
-    return rc
+    return _run(check, name, m, n, k, A, lda, orderA, B, ldb, orderB, C, ldc, orderC, mode,
+                workspace, workspace_bytes, stream, *extra)
 
 
 def mipgemm_s8s8s32(m, n, k, A, lda, orderA, B, ldb, orderB, C, ldc, orderC, mode,
@@ -250,23 +297,15 @@ def mipgemm_s8u8s8(m, n, k, A, lda, orderA, B, ldb, orderB, C, ldc, orderC, mode
 def mipgemm_conv_s8u8s32(b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode,
                          workspace=None, workspace_bytes=0, stream=None, check=True):
     """O = [O +] CONV(F, I) by lowering to the integer GEMM (see include/mipgemm.h)."""
-    rc = load_library().mipgemm_conv_s8u8s32(
-        b, hi, wi, ci, co, hf, wf, stride, pad, _ptr(F), _ptr(I), _ptr(O), mode,
-        _ptr(workspace), workspace_bytes, _stream(stream))
-    if check and rc != 0:
-        raise MipGemmError(rc, mipgemm_strerror(rc))
-    return rc
+    return _run(check, "mipgemm_conv_s8u8s32", b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode,
+                workspace, workspace_bytes, stream)
 
 
 def mipgemm_conv_s8u8f32(b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode,
                          workspace=None, workspace_bytes=0, stream=None, scale=1.0, check=True):
     """O (float) = [O +] scale * CONV(F, I): the lowered convolution with the scale fused in."""
-    rc = load_library().mipgemm_conv_s8u8f32(
-        b, hi, wi, ci, co, hf, wf, stride, pad, _ptr(F), _ptr(I), _ptr(O), mode,
-        _ptr(workspace), workspace_bytes, _stream(stream), scale)
-    if check and rc != 0:
-        raise MipGemmError(rc, mipgemm_strerror(rc))
-    return rc
+    return _run(check, "mipgemm_conv_s8u8f32", b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode,
+                workspace, workspace_bytes, stream, scale)
 
 
 def mipgemm_conv_filter_sums(co, k, F, sums, stream=None, check=True):
@@ -280,34 +319,22 @@ def mipgemm_conv_filter_sums(co, k, F, sums, stream=None, check=True):
 def mipgemm_conv_s8u8s32_with_sums(b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode, filter_sums,
                                    workspace=None, workspace_bytes=0, stream=None, check=True):
     """mipgemm_conv_s8u8s32 with the filters' k-sums (mipgemm_conv_filter_sums) supplied."""
-    rc = load_library().mipgemm_conv_s8u8s32_with_sums(
-        b, hi, wi, ci, co, hf, wf, stride, pad, _ptr(F), _ptr(I), _ptr(O), mode,
-        _ptr(workspace), workspace_bytes, _stream(stream), _ptr(filter_sums))
-    if check and rc != 0:
-        raise MipGemmError(rc, mipgemm_strerror(rc))
-    return rc
+    return _run(check, "mipgemm_conv_s8u8s32_with_sums", b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode,
+                workspace, workspace_bytes, stream, filter_sums)
 
 
 def mipgemm_conv_s8u8f32_with_sums(b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode, filter_sums,
                                    workspace=None, workspace_bytes=0, stream=None, scale=1.0, check=True):
     """mipgemm_conv_s8u8f32 with the filters' k-sums supplied."""
-    rc = load_library().mipgemm_conv_s8u8f32_with_sums(
-        b, hi, wi, ci, co, hf, wf, stride, pad, _ptr(F), _ptr(I), _ptr(O), mode,
-        _ptr(workspace), workspace_bytes, _stream(stream), scale, _ptr(filter_sums))
-    if check and rc != 0:
-        raise MipGemmError(rc, mipgemm_strerror(rc))
-    return rc
+    return _run(check, "mipgemm_conv_s8u8f32_with_sums", b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode,
+                workspace, workspace_bytes, stream, scale, filter_sums)
 
 
 def mipgemm_conv_s8u8s8(b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode, filter_sums=None,
                         workspace=None, workspace_bytes=0, stream=None, scale=1.0, check=True):
     """O (int8) = clip(rint(scale * CONV(F, I))): the lowered convolution requantised for the next layer."""
-    rc = load_library().mipgemm_conv_s8u8s8(
-        b, hi, wi, ci, co, hf, wf, stride, pad, _ptr(F), _ptr(I), _ptr(O), mode,
-        _ptr(workspace), workspace_bytes, _stream(stream), scale, _ptr(filter_sums))
-    if check and rc != 0:
-        raise MipGemmError(rc, mipgemm_strerror(rc))
-    return rc
+    return _run(check, "mipgemm_conv_s8u8s8", b, hi, wi, ci, co, hf, wf, stride, pad, F, I, O, mode,
+                workspace, workspace_bytes, stream, scale, filter_sums)
 
 
 def mipgemm_conv_workspace_size(b, hi, wi, ci, co, hf, wf, stride, pad) -> int:
@@ -335,13 +362,8 @@ def mipgemm_im2col_u8(b, hi, wi, ci, hf, wf, stride, pad, I, M, ldm, stream=None
 
 def _batched(entry, m, n, k, A, lda, orderA, strideA, B, ldb, orderB, strideB,
              C, ldc, orderC, strideC, batch, mode, workspace, workspace_bytes, stream, check):
-    rc = getattr(load_library(), entry)(
-        m, n, k, _ptr(A), lda, orderA, strideA, _ptr(B), ldb, orderB, strideB,
-        _ptr(C), ldc, orderC, strideC, batch, mode, _ptr(workspace), workspace_bytes,
-        _stream(stream))
-    if check and rc != 0:
-        raise MipGemmError(rc, mipgemm_strerror(rc))
-    return rc
+    return _run(check, entry, m, n, k, A, lda, orderA, strideA, B, ldb, orderB, strideB,
+                C, ldc, orderC, strideC, batch, mode, workspace, workspace_bytes, stream)
 
 
 def mipgemm_s8s8s32_batched(m, n, k, A, lda, orderA, strideA, B, ldb, orderB, strideB,
@@ -409,11 +431,8 @@ def mipgemm_pack_weights(k, n, B, ldb, orderB, packed, packed_bytes=None, stream
 
 def _call_packed(name, m, n, k, A, lda, orderA, packed, C, ldc, orderC, mode, workspace,
                  workspace_bytes, stream, check):
-    rc = getattr(load_library(), name)(m, n, k, _ptr(A), lda, orderA, _ptr(packed), _ptr(C), ldc,
-                                       orderC, mode, _ptr(workspace), workspace_bytes, _stream(stream))
-    if check and rc != 0:
-        raise MipGemmError(rc, mipgemm_strerror(rc))
-    return rc
+    return _run(check, name, m, n, k, A, lda, orderA, packed, C, ldc, orderC, mode,
+                workspace, workspace_bytes, stream)
 
 
 def mipgemm_s8s8s32_packed(m, n, k, A, lda, orderA, packed, C, ldc, orderC, mode,

@@ -4,6 +4,7 @@ from __future__ import annotations
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -56,7 +57,28 @@ def build_library(verbose: bool = False, jobs: int = 0) -> str:
             os.remove(tmp)
         raise RuntimeError("link failed:\n" + proc.stdout)
     os.replace(tmp, LIB)
+    build_binding(verbose)
     return LIB
+
+
+def build_binding(verbose: bool = False) -> None:
+    """The binding's argument conversion (native/call.c); without Python's headers it stays with ctypes."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        print("no Python.h in %s: the binding converts its arguments through ctypes" % include, flush=True)
+        return
+    out = os.path.join(HERE, "_call.so")
+    tmp = out + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I" + include,
+           os.path.join(HERE, "native", "call.c"), "-o", tmp]
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+        raise RuntimeError("the binding's call.c failed:\n" + proc.stdout)
+    os.replace(tmp, out)
+    if verbose:
+        print("compiled native/call.c", flush=True)
 
 
 if __name__ == "__main__":

@@ -265,3 +265,55 @@ def test_batched_entry_point_validation(M, entry):
     assert call_b(batch=0) == 0                      # nothing to do, nothing launched
     for code in (-18, -19, -20):
         assert str(-code) in M.mipgemm_strerror(code)
+
+
+def _invalid_calls():
+    """One call per entry point and bad argument, as (function, args, keywords): every one is refused by
+    validation, so nothing is launched."""
+    import torch
+    X = torch.zeros(64, dtype=torch.int8)
+    p = X.data_ptr()
+    for name in ("s8s8s32", "u8s8s32", "s8u8s32", "s8s8f32", "u8s8f32", "s8u8f32", "s8s8s8", "u8s8s8", "s8u8s8", "s16s16s32"):
+        kw = {} if name.endswith("s32") else {"scale": 1}
+        good = [4, 4, 4, X, 4, 0, p, 4, 0, X, 4, 0, 0]
+        for at, value in ((0, -1), (1, 1 << 40), (4, True), (5, 9), (7, -(1 << 63)), (8, 2 + (1 << 32)), (10, 0), (12, 5)):
+            yield "mipgemm_" + name, good[:at] + [value] + good[at + 1:], kw
+        yield "mipgemm_" + name, good, dict(kw, workspace_bytes=8)
+    for name in ("s8s8s32", "u8s8s32", "s8u8s32"):
+        good = [4, 4, 4, X, 4, 0, 0, X, 4, 0, 0, X, 4, 0, 0, 2, 0]
+        for at, value in ((2, -1), (6, -1), (10, -1), (14, -1), (15, 70000), (16, 3)):
+            yield "mipgemm_%s_batched" % name, good[:at] + [value] + good[at + 1:], {}
+    for name in ("s8s8s32", "u8s8s32"):
+        for at, value in ((0, -1), (5, 3), (6, None), (8, 1), (10, 2)):
+            good = [4, 4, 4, X, 4, 0, p // 16 * 16, X, 4, 0, 0]
+            yield "mipgemm_%s_packed" % name, good[:at] + [value] + good[at + 1:], {}
+    for name, more in (("s8u8s32", ()), ("s8u8f32", ()), ("s8u8s32_with_sums", (X,)), ("s8u8f32_with_sums", (X,)), ("s8u8s8", (X,))):
+        for at, value in ((0, -1), (3, -1), (7, 0), (8, -2), (10, None), (12, 4)):
+            good = [1, 4, 4, 4, 4, 1, 1, 1, 0, X, X, X, 0]
+            yield "mipgemm_conv_" + name, good[:at] + [value] + good[at + 1:] + list(more), {}
+
+
+def test_both_ways_of_converting_arguments_agree(monkeypatch):
+    """The binding's C conversion and the ctypes one: the same refusals, error numbers and exceptions."""
+    import paper_2506_11728_amd as M
+    from paper_2506_11728_amd import binding
+    M.load_library()
+    if binding._native is None:
+        pytest.skip("built without Python headers")
+    calls = [(f, a, dict(k, stream=0, check=False)) for f, a, k in _invalid_calls()]
+    native = [getattr(M, f)(*a, **k) for f, a, k in calls]
+    odd = [("mipgemm_s8s8s32", [4, 4, 4.0, 0, 4, 0, 0, 4, 0, 0, 4, 0, 0], {}),
+           ("mipgemm_s8s8s32", [4, 4, 4, "x", 4, 0, 0, 4, 0, 0, 4, 0, 0], {}),
+           ("mipgemm_s8s8f32", [4, 4, 4, 0, 4, 0, 0, 4, 0, 0, 4, 0, 0], {"scale": "x"}),
+           ("mipgemm_s8s8s32", [-1, 4, 4, 0, 4, 0, 0, 4, 0, 0, 4, 0, 0], {"stream": "x"}),
+           ("mipgemm_s8s8s32", [-1, 4, 4, 0, 4, 0, 0, 4, 0, 0, 4, 0, 0], {"check": True})]
+
+    def raised(f, a, k):
+        with pytest.raises(Exception) as e:
+            getattr(M, f)(*a, **dict({"stream": 0}, **k))
+        return type(e.value)
+    kinds = [raised(*c) for c in odd]
+    monkeypatch.setattr(binding, "_native", None)
+    assert native == [getattr(M, f)(*a, **k) for f, a, k in calls]
+    assert all(rc < 0 for rc in native)
+    assert kinds == [raised(*c) for c in odd]
