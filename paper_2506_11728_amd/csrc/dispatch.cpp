@@ -207,12 +207,14 @@ Plan choose_plan(const Problem &p) {
     // cold, us: (32, 11008, 4096) 18.9 -> 16.5, (64, 11008, 4096) 20.7 -> 18.7, (32, 4096, 11008)
     // 18.9 -> 15.3, (64, 4096, 11008) 21.5 -> 18.9; warm within 0.5 us either way; at
     // (64, 4096, 4096) the 64 x 64 tiles stay ahead, 11.6 against 12.7.  A k-contiguous B has no
-    // lines to complete: (64, 11008, 4096) 13.3/19.2 us warm/cold on 64 x 64, 16.2/20.8 on 64 x 128.)
+    // lines to complete: (64, 11008, 4096) 13.3/19.2 us warm/cold on 64 x 64, 16.2/20.8 on 64 x 128.
+    // A float output needs enough of them, its ranges of k meeting in slots: (32, 4096, 11008), 32
+    // tiles, 19.0 us against 14.0 on 64 x 64.)
     if (p.m <= 64 && p.n > 128)
       sh = p.k >= 512 && enough(SHAPE_64X256, p.m)
                ? SHAPE_64X256
                : (p.m >= 32 && p.k >= 512 && p.b_sn == 1 && p.n * p.k >= ((int64_t)32 << 20) &&
-                          dma_eligible(p, SHAPE_64X128)
+                          (!p.out_float || tile_count(p, SHAPE_64X128) >= 64) && dma_eligible(p, SHAPE_64X128)
                       ? SHAPE_64X128
                       : SHAPE_64);
     else if (p.n <= 64 && p.m > 128) sh = p.k >= 512 && enough(SHAPE_256X64, p.n) ? SHAPE_256X64 : SHAPE_64;

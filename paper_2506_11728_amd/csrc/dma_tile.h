@@ -56,7 +56,7 @@ static __device__ __attribute__((aligned(16))) const uint8_t conv_zero_block[16]
 
 // UNS: 0 both operands signed, 1 A unsigned, 2 B unsigned; 3 and 4: as 1 and 2 with the k sums
 // of the signed operand read from P.ksum instead of being accumulated from the fragments
-// (whole problem only: with split k every range would add them).
+// (with split k by the first range alone).
 template <int BM, int BN, bool A_KC, bool B_KC, int UNS, bool CONV = false>
 __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(DmaTileParams P) {
   constexpr bool FLIP_A = UNS == 1 || UNS == 3, FLIP_B = UNS == 2 || UNS == 4;
@@ -302,14 +302,14 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(DmaTileParams P) {
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       const int64_t col = n0 + wn * (BN / 2) + j * 32 + (lane & 31);
-      sumB[j] = lane < 32 && col < P.n ? P.ksum[col] : 0;
+      sumB[j] = lane < 32 && col < P.n && blockIdx.y == 0 ? P.ksum[col] : 0;
     }
   }
   if (UNS == 4) {
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       const int64_t row = m0 + wm * (BM / 2) + i * 32 + (lane & 31);
-      sumA[i] = lane < 32 && row < P.m ? P.ksum[row] : 0;
+      sumA[i] = lane < 32 && row < P.m && blockIdx.y == 0 ? P.ksum[row] : 0;
     }
   }
   unsigned_correction<FM, FN>(acc, sumA, sumB, FLIP_A, FLIP_B, lane);
@@ -434,9 +434,9 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   size_t lds = (size_t)stages * (BM + BN) * BK;
   if (lds < 4 * (size_t)STORE_PATCH_BYTES) lds = 4 * (size_t)STORE_PATCH_BYTES;
   const int uns = p.a_unsigned ? 1 : (p.b_unsigned ? 2 : 0);
-  // supplied k sums (pre-packed weights): for an unsplit k and a k-contiguous signed operand,
-  // which packed weights always are; otherwise the sums are accumulated in the loop as usual
-  const bool supplied = p.ksum != nullptr && splits == 1 && p.batch <= 1 && !p.conv &&
+  // supplied k sums (pre-packed weights): for a k-contiguous signed operand, which packed weights
+  // always are; otherwise the sums are accumulated in the loop as usual
+  const bool supplied = p.ksum != nullptr && p.batch <= 1 && !p.conv &&
                         ((uns == 1 && b_kc) || (uns == 2 && a_kc));
   P.ksum = supplied ? p.ksum : nullptr;
   void (*kern)(DmaTileParams) = nullptr;
@@ -456,7 +456,7 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   if (p.conv) {
     P.conv = *p.conv;
     // (the gathered matrix is the unsigned A, the filters the signed, k-contiguous B)
-    const bool filter_sums = p.ksum != nullptr && splits == 1;
+    const bool filter_sums = p.ksum != nullptr;
     P.ksum = filter_sums ? p.ksum : nullptr;
     kern = filter_sums ? dma_tile_kernel<BM, BN, true, true, 3, true> : dma_tile_kernel<BM, BN, true, true, 1, true>;
   } else {

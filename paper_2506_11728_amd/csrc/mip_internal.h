@@ -54,6 +54,7 @@ struct Problem {
   // not null: A is never materialised, the kernel gathers it from the image tensor
   // (only the direct-to-LDS tile kernels can; a_sm is then the nominal row length k)
   const ConvGeom *conv = nullptr;
+  bool packed_weights = false;  // one operand is the library's packed weights
 };
 
 // Workgroup tile of the MFMA kernels (rows x columns of C).

@@ -108,6 +108,7 @@ int run_gemm(int a_unsigned, int b_unsigned, int out_float, float scale, int64_t
   if (rc != 0) return rc;
   // (the sums belong to the signed operand whichever role the normalisation has given it)
   p.ksum = (a_unsigned != 0) != (b_unsigned != 0) ? ksum : nullptr;
+  p.packed_weights = ksum != nullptr;
   p.out_float = out_float;
   p.scale = scale;
   p.batch = batch.count;

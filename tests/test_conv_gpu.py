@@ -7,6 +7,8 @@ import os
 import numpy as np
 import pytest
 
+import workloads as W
+
 pytestmark = pytest.mark.gpu
 
 
@@ -560,3 +562,19 @@ def test_conv_with_int8_output(gpu, oracle, shape, env):
                                    check=False) == -13
     torch.cuda.synchronize()
     assert (dO.cpu().numpy() == 0x11).all()
+
+
+@pytest.mark.parametrize("splits", [2, 3])
+def test_supplied_filter_sums_with_ranges_of_k(gpu, oracle, splits):
+    import torch
+    b, geo = 2, (14, 64, 96, 3, 1, 1)
+    hi, ci, co, hf, stride, pad = geo
+    image, filt = W.conv_tensors(b, geo)
+    want = oracle.conv_direct(image, filt, stride, pad)
+    dF, dI = torch.from_numpy(filt.view(np.uint8)).cuda(), torch.from_numpy(image).cuda()
+    sums = torch.empty(co, dtype=torch.int32, device="cuda")
+    gpu.mipgemm_conv_filter_sums(co, hf * hf * ci, dF, sums)
+    dO = torch.zeros(want.size, dtype=torch.int32, device="cuda")
+    with gpu.tuning(MIPGEMM_SPLITK=str(splits)):
+        gpu.mipgemm_conv_s8u8s32_with_sums(b, hi, hi, ci, co, hf, hf, stride, pad, dF, dI, dO, W.OVERWRITE, sums)
+    assert np.array_equal(dO.cpu().numpy(), want.reshape(-1))

@@ -220,3 +220,17 @@ def test_packed_weights_replay_from_a_hip_graph(gpu, oracle):
         graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(dC.cpu().numpy(), want), "replay %d" % replay
+
+
+@pytest.mark.parametrize("variant", ["dma64", "dma64x128", "dma128x64"])
+@pytest.mark.parametrize("splits", [2, 3, 7])
+def test_supplied_sums_are_added_once_over_the_ranges_of_k(gpu, oracle, variant, splits):
+    for mode in (W.OVERWRITE, W.ACCUMULATE):
+        for orderC in (W.ROW_MAJOR, W.COL_MAJOR):
+            _check_gemm(gpu, oracle, 70, 200, 1024, True, W.ROW_MAJOR, W.ROW_MAJOR, orderC, mode, 0, variant,
+                        splits=splits, seed=31)
+
+
+@pytest.mark.parametrize("m,n,k", [(33, 2048, 2048), (64, 4096, 2112), (40, 5120, 2048)])
+def test_packed_weights_above_32_rows_as_dispatched(gpu, oracle, m, n, k):
+    _check_gemm(gpu, oracle, m, n, k, True, W.ROW_MAJOR, W.ROW_MAJOR, W.ROW_MAJOR, W.OVERWRITE, 0, "auto", seed=32)

@@ -585,6 +585,24 @@ def test_skinny_m_slab_kernel(gpu, oracle, case, variant):
     check_case(gpu, oracle, case, variant)
 
 
+@pytest.mark.parametrize("variant", ["slab16", "slab32", "slab64"])
+@pytest.mark.parametrize("m,k", [(1, 64), (16, 192), (17, 1088), (33, 3200), (64, 1600), (5, 6464)])
+def test_slab_step_counts(gpu, oracle, variant, m, k):
+    """128-deep steps: a 64-deep last one, fewer steps than waves, as many as a ring holds and more, with
+    either operand unsigned and both orders of B."""
+    for i, (uns, order) in enumerate(((0, W.COL_MAJOR), (1, W.COL_MAJOR), (2, W.COL_MAJOR), (0, W.ROW_MAJOR), (1, W.ROW_MAJOR))):
+        check_case(gpu, oracle, W.Case("slab_steps_%d_%d_%d_%s" % (m, k, i, variant), 8, 900 + i, m, 192, k,
+                                       a_unsigned=uns == 1, b_unsigned=uns == 2, orderB=order, seed=90), variant)
+
+
+@pytest.mark.parametrize("k", [64, 448, 2112])
+def test_more_narrow_slabs_than_compute_units(gpu, oracle, k):
+    """Rings of half the depth, two workgroups to a compute unit."""
+    for i, order in enumerate((W.COL_MAJOR, W.ROW_MAJOR)):
+        check_case(gpu, oracle, W.Case("slab_many_%d_%d" % (k, i), 8, 950 + i, 9, 16 * 517, k, orderB=order,
+                                       a_unsigned=i == 0, seed=91), "slab16")
+
+
 def test_skinny_m_slab_kernel_wraps(gpu, oracle):
     """All(-128) x all(-128) over k = 2^17: every sum is 2^31, which wraps to -2^31."""
     m, n, k = 4, 32, 1 << 17
