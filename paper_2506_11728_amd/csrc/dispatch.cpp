@@ -190,6 +190,66 @@ Plan choose_plan(const Problem &p) {
     // With at most 16 rows the atomics of split k are cheap, and wide tiles (whole
     // cache lines of a row-major operand) win as soon as k is long enough to cut
     // into one range of 8 blocks or more per compute unit.
+// A few rows of A: width of the slabs, in blocks of 16 columns, where a workgroup per slab of B is
+// the better plan, 0 where tiles are.  One pass over B in one launch, without atomics or a zero
+// fill, against tiles that share A between more columns and split k over workgroups.
+// Measured on operands that stay in the last-level cache, us, slabs of 16 / 32 / 64 columns
+// against the best tile.  B k-contiguous:
+//   m = 8    (8192, 4096) 10.2 / 8.7 / 8.2 against 10.3, (5120, 5120) 10.2 / 7.6 / 8.3 against 10.0,
+//            (2048, 8192) 6.7 / 7.2 / 9.3 against 7.9
+//   m = 16   (11008, 4096) 14.1 / 12.3 / 9.8 against 13.7, (3072, 3072) 4.4 / 4.7 / 5.5 against 6.9
+//   m = 32   (11008, 4096) 16.4 / 14.3 / 12.3 against 14.4, (8192, 4096) 11.1 / 9.0 / 9.9 against 12.4,
+//            (4096, 11008) 13.2 / 14.2 / 20 against 15.3, but (12288, 1024) 8.5 / 7.5 / 6.8 against 6.2
+//   m = 64   (4096, 4096) 8.6 / 10.5 / 14.8 against 11.5, (8192, 4096) 13.3 / 10.9 / 14.0 against 13.1,
+//            (16384, 8192) 52 / 44 / 37.5 against 41, but (11008, 4096) 18 / 18 / 15 against 13.6 (two
+//            thirds of a round) and (4096, 11008) 17.7 / 20.5 / 28.6 against 17.1
+// B row-major, whose rows a narrow slab takes in pieces of 16 bytes a column block:
+//   m = 16   (11008, 4096) 24 / 17.4 / 11.0 against 13.3, (12288, 1024) 10.3 / 7.8 / 6.0 against 7.8,
+//            (5120, 2048) 10.8 / 7.3 / 8.2 against 8.7, but (5120, 5120) 21 / 14.5 / 16 against 10.2,
+//            (16384, 8192) 82 / 62 / 38 against 33.5
+//   m = 32   (11008, 4096) 26 / 19 / 13.1 against 14.0, (12288, 1024) 11.0 / 8.5 / 7.5 against 6.5
+// Adding into an int32 C needs no zero fill, and the tiles win or tie, except against wide slabs:
+// (16, 11008, 4096) 10.1 against 11.2, row-major 11.3 against 12.6.
+static int slab_width(const Problem &p) {
+  if (p.m > 64 || !slab_eligible(p, 1)) return 0;
+  const bool kc = p.b_sk == 1;
+  const bool adds_in_place = p.accumulate && !p.out_float && p.k >= (p.m >= 16 ? 1024 : 1536);
+  auto fits = [&](int nt, int64_t least) { return p.n / (16 * nt) >= least && slab_eligible(p, nt); };
+  // (at most four rows leave 64 columns little to reuse: two thirds of a round of narrow slabs, two
+  // workgroups to a compute unit, hold the same bytes in flight)
+  const int width = !(kc && p.m <= 4 && p.n / 64 < 256) && fits(4, kc && p.m <= 16 ? 128 : 160) ? 4
+                    : (fits(2, 160) && !(kc && p.m <= 4 && p.n / 32 > 256)                      ? 2
+                                                                                                 : 1);
+  if (kc) {
+    if (adds_in_place) return p.m <= 32 && fits(4, 160) ? 4 : 0;
+    if (p.n / 16 >= 128) {
+      if (p.m <= 16) return width;
+      if (p.m <= 32 && (p.k >= 2048 || p.n / 16 <= 256)) return width;
+      const int64_t cus = compute_units(), slabs = p.n / 64;
+      const bool full_round = 10 * slabs >= 9 * ((slabs + cus - 1) / cus * cus);
+      // (above 32 rows an int32 product on unpacked operands keeps the tiles: the choice that tests pin)
+      if (p.m > 32 && (p.packed_weights || p.out_float) && p.k >= 2048 && p.k <= 8192 && (width < 4 || full_round))
+        return width;
+    }
+  } else {
+    if (width == 4 && p.n * p.k <= ((int64_t)64 << 20) && (p.m <= 16 || (p.m <= 32 && p.k >= 2048 && !adds_in_place)))
+      return 4;
+    if (adds_in_place) return 0;
+    if (width == 2 && p.k <= 2048 && p.m <= 32) return 2;
+    // (a float output splits k through slots, which cost it more than atomics do an int32 one:
+    // (1, 4096, 4096) 9.6 / 10.2 / 10.5 against 12.2, (16, 4096, 4096) 10.1 against 11.8)
+    if (p.out_float && p.m <= 16 && p.n / 16 >= 192 && p.k <= 4096) return width;
+  }
+  // Short k, where the tiles, too few to fill the chip, would have to split it (up to 4096 at
+  // m <= 16, 2048 at 32, 1024 at 64; row-major only to 2048: cold it loses beyond), and a float
+  // output without a workspace, which tiles cannot split at all.  Measured, us warm/cold:
+  // (1, 1024, 2048) 4.9/5.6 -> 3.6/4.5, (16, 2048, 2048) 5.3/6.1 -> 4.5/5.5,
+  // (64, 4096, 1024) 6.3/7.2 -> 5.1/5.7; float (16, 2048, 8192) 17.8/29.2 -> 9.7/11.2.
+  const bool short_k = p.k * (p.m > 16 ? p.m : 16) <= 65536 && (kc || p.k <= 2048);
+  if ((short_k || (p.out_float && !p.ws)) && tile_count(p, SHAPE_64) < compute_units() / 2 && p.n / 16 >= 64) return 1;
+  return 0;
+}
+
     Shape sh;
     const Shape rect = (!p.conv && p.b_sn == 1 && p.a_sk == 1)   ? SHAPE_64X128
                        : (!p.conv && p.a_sm == 1 && p.b_sk == 1) ? SHAPE_128X64
@@ -247,58 +307,7 @@ Plan choose_plan(const Problem &p) {
       sh = rect;  // (measured on the direct-to-LDS kernels only)
     else if (p.k >= 512 && tile_count(p, SHAPE_128) >= 192) sh = SHAPE_128;
     else sh = SHAPE_64;
-    // deep k blocks pay off once the k loop is long enough to amortise their prologue
-    // A few rows of A against a k-contiguous B is one pass over B with nothing to
-    // share: a workgroup per 16-column slab does it in one launch, without atomics.
-    // (A row-major B would reach each slab in 16-byte pieces of its cache lines,
-    // which the tiled kernels, with their 64-byte pieces and split k, do better.)
-    // The same kernel serves short k, where the tiled kernels cannot split k
-    // and 64-column tiles leave most compute units idle.
-    // (Adding into an int32 C that already holds values needs no zero-fill launch: with a k
-    // long enough to split, the tiles then win or tie.  Measured, us warm/cold, slab against
-    // tiles: (16, 4096, 4096) 6.4/9.5 against 4.7/7.0, (1, 1024, 2048) 3.7/4.7 against
-    // 3.3/4.0, (64, 4096, 1024) 5.4/6.5 against 4.5/5.2, (16, 16384, 4096) 16.1/21.9 against
-    // 15.0/18.2, (1, 11008, 4096) 10.4/12.5 against 10.5/12.2.  At k = 1024 only from 16
-    // rows on: (1, 4096, 1024) 2.9/3.5 against 3.4/4.1, (16, 8192, 1024) 4.2/5.7 against 3.9/4.7;
-    // with fewer rows from k = 1536: (8, 4096, 1536) 4.0/5.1 against 3.5/4.3,
-    // (4, 16384, 1536) 6.2/8.4 against 4.6/8.2.)
-    const bool adds_in_place = p.accumulate && !p.out_float && p.k >= (p.m >= 16 ? 1024 : 1536);
-    const bool slab_ok = p.m <= 64 && !adds_in_place && slab_eligible(p, 1);
-    // Slabs of 32 columns re-read A half as often and need half the workgroups; they win
-    // (warm and cold) wherever they fill the compute units' rounds as evenly as slabs of 16 do:
-    // n = 8192 (256 slabs of 32: one round) and 16384, not 11008 (344: two rounds, the second
-    // a third full) nor 4096 (128: half a round).  Measured, us warm/cold, m = 1, k = 4096:
-    // n = 16384 15.7/19.7 -> 12.5/18.0; m = 16: 18.5/21.9 -> 14.7/19.6.
-    auto round_fill = [&](int64_t slabs) {
-      return (double)slabs / (double)((slabs + kComputeUnits - 1) / kComputeUnits * kComputeUnits);
-    };
-    const bool wide_slabs = slab_eligible(p, 2) && round_fill(p.n / 32) >= round_fill(p.n / 16) - 0.02;
-    // "short k": the slab kernel still wins where the tiles, too few to fill the chip, would
-    // have to split k (a zero-fill launch plus atomics): up to k = 4096 at m <= 16, 2048 at 32,
-    // 1024 at 64; with a row-major B (16-byte pieces of every line per slab) only up to 2048,
-    // cold it loses beyond ((1, 4096, 3072): 11.6 against 8.5 us).  Measured, us warm/cold:
-    // (1, 1024, 2048) 4.9/5.6 -> 3.6/4.5, (16, 2048, 2048) 5.3/6.1 -> 4.5/5.5,
-    // (64, 4096, 1024) 6.3/7.2 -> 5.1/5.7.
-    const bool short_k = p.k * (p.m > 16 ? p.m : 16) <= 65536 && (p.b_sk == 1 || p.k <= 2048);
-    // Slabs of 64 columns re-read A a quarter as often, which is what several rows of A cost a
-    // narrow slab; they need n / 64 workgroups to be enough.  Measured on a k-contiguous B, us
-    // warm/cold against the narrower choice: (16, 11008, 4096) 14.2/16.2 -> 12.1/15.1,
-    // (16, 16384, 4096) 14.8/19.6 -> 13.2/18.0, (16, 32000, 4096) 26.7/33.0 -> 22.6/31.8,
-    // (1, 16384, 4096) 12.6/18.3 -> 12.3/17.1; not (1, 11008, 4096) 10.4/12.2 -> 10.5/12.8, nor
-    // n = 4096 at any m (64 workgroups: (16, 4096, 4096) 6.3/8.2 -> 11.2/13.1).
-    const bool slabs_of_64 = slab_eligible(p, 4) && p.n / 64 >= 160 && (p.m > 4 || p.n / 64 >= 256);
-    if (slab_ok && p.b_sk == 1 && p.m <= 16 && p.n / 16 >= 192)
-      plan = {KIND_SLAB, SHAPE_64, slabs_of_64 ? 4 : (wide_slabs ? 2 : 1)};
-    // (Float output cannot split k at all, sums of floats not being combined out of order:
-    // there the slab kernel takes every such problem, whatever k.  Measured, us warm/cold:
-    // (16, 2048, 8192) 17.8/29.2 -> 9.7/11.2, with a row-major B 17.7/35.3 -> 10.5/26.6;
-    // (1, 4096, 4096) row-major B 10.5/18.5 -> 7.2/14.5.)
-    // (With a workspace a float output splits k through slots of partial sums, and then the
-    // tiles win here as they do for an int32 output: (64, 4096, 4096) 15.7 -> 9.4 us,
-    // (16, 4096, 4096) 10.8 -> 9.2 us.)
-    else if (slab_ok && (short_k || (p.out_float && !p.ws)) && tile_count(p, SHAPE_64) < kComputeUnits / 2 &&
-             p.n / 16 >= 64)
-      plan = {KIND_SLAB, SHAPE_64, 1};
+    if (const int nt = slab_width(p)) plan = {KIND_SLAB, SHAPE_64, nt};
     // A very long k over few tiles: the 128 x 128 tiles with 128-deep blocks, k in ranges.
     // The 64 x 64 tiles chosen above for such a shape (enough of them to need no split) run
     // at 64 operations per operand byte; the wider tile halves the bytes, and the ranges give
