@@ -175,21 +175,6 @@ size_t splitk_slot_bytes(const Problem &p, const Plan &plan) {
   return bytes < 1.0e15 ? (size_t)bytes : 0;
 }
 
-Plan choose_plan(const Problem &p) {
-  const int64_t kComputeUnits = compute_units();
-  if (p.m == 0 || p.n == 0) return {KIND_NONE, SHAPE_64, 1};
-  // (the zero fill writes words; an int8 output of an empty sum goes through the simple kernel)
-  if (p.k == 0) return {p.accumulate ? KIND_NONE : (p.out_float == 2 ? KIND_SIMPLE : KIND_FILL), SHAPE_64, 1};
-  Plan plan;
-  if (!forced_plan(p, &plan)) {
-    // The largest tile that still gives most compute units a workgroup; a
-    // matrix that is short in one dimension takes a tile that is short there too.
-    // A short side (a few tokens, a few output channels) makes the problem a
-    // stream over the long operand: wide tiles only when the long side alone
-    // fills the chip, else 64 x 64 tiles, which give four times as many workgroups.
-    // With at most 16 rows the atomics of split k are cheap, and wide tiles (whole
-    // cache lines of a row-major operand) win as soon as k is long enough to cut
-    // into one range of 8 blocks or more per compute unit.
 // A few rows of A: width of the slabs, in blocks of 16 columns, where a workgroup per slab of B is
 // the better plan, 0 where tiles are.  One pass over B in one launch, without atomics or a zero
 // fill, against tiles that share A between more columns and split k over workgroups.
@@ -250,6 +235,21 @@ static int slab_width(const Problem &p) {
   return 0;
 }
 
+Plan choose_plan(const Problem &p) {
+  const int64_t kComputeUnits = compute_units();
+  if (p.m == 0 || p.n == 0) return {KIND_NONE, SHAPE_64, 1};
+  // (the zero fill writes words; an int8 output of an empty sum goes through the simple kernel)
+  if (p.k == 0) return {p.accumulate ? KIND_NONE : (p.out_float == 2 ? KIND_SIMPLE : KIND_FILL), SHAPE_64, 1};
+  Plan plan;
+  if (!forced_plan(p, &plan)) {
+    // The largest tile that still gives most compute units a workgroup; a
+    // matrix that is short in one dimension takes a tile that is short there too.
+    // A short side (a few tokens, a few output channels) makes the problem a
+    // stream over the long operand: wide tiles only when the long side alone
+    // fills the chip, else 64 x 64 tiles, which give four times as many workgroups.
+    // With at most 16 rows the atomics of split k are cheap, and wide tiles (whole
+    // cache lines of a row-major operand) win as soon as k is long enough to cut
+    // into one range of 8 blocks or more per compute unit.
     Shape sh;
     const Shape rect = (!p.conv && p.b_sn == 1 && p.a_sk == 1)   ? SHAPE_64X128
                        : (!p.conv && p.a_sm == 1 && p.b_sk == 1) ? SHAPE_128X64
