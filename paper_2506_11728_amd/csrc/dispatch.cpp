@@ -54,7 +54,14 @@ const char *plan_name(const Plan &plan) {
     case KIND_STAGED: return staged[plan.shape];
     case KIND_DMA: return dma[plan.shape];
     case KIND_DMA_K128: return plan.shape == SHAPE_128 ? "mfma_dma128_k128" : "mfma_dma256_k128";
-    case KIND_DMA_K128_SPLIT: return plan.shape == SHAPE_256 ? "mfma_dma256_k128_ragged" : "mfma_dma128_k128_split";
+    case KIND_DMA_K128_SPLIT:
+      switch (plan.shape) {
+        case SHAPE_256: return "mfma_dma256_k128_ragged";
+        case SHAPE_256X192: return "mfma_dma256x192_k128";
+        case SHAPE_192X256: return "mfma_dma192x256_k128";
+        case SHAPE_192: return "mfma_dma192_k128";
+        default: return "mfma_dma128_k128_split";
+      }
     case KIND_SLAB: return plan.splits == 4 ? "mfma_slab64" : (plan.splits == 2 ? "mfma_slab32" : "mfma_slab16");
     default: return "?";
   }
@@ -107,6 +114,14 @@ static bool forced_plan(const Problem &p, Plan *plan) {
     *plan = {KIND_DMA_K128_SPLIT, SHAPE_256, 1};
     return true;
   }
+  static const struct { const char *name; Shape shape; } with_192[3] = {
+      {"dma256x192k128", SHAPE_256X192}, {"dma192x256k128", SHAPE_192X256}, {"dma192k128", SHAPE_192}};
+  for (const auto &v : with_192)
+    if (!std::strcmp(e, v.name)) {
+      if (!dma_k128_split_eligible(p, true)) return false;
+      *plan = {KIND_DMA_K128_SPLIT, v.shape, 1};
+      return true;
+    }
   if (!std::strcmp(e, "slab16") || !std::strcmp(e, "slab32") || !std::strcmp(e, "slab64")) {
     const int nt = e[4] == '6' ? 4 : (e[4] == '3' ? 2 : 1);
     if (!slab_eligible(p, nt)) return false;
@@ -235,6 +250,42 @@ static int slab_width(const Problem &p) {
   return 0;
 }
 
+// Tiles with a side of 192 for the kernel with 128-deep blocks, where 256 x 256 ones leave a last round
+// mostly idle or are too few and 128 x 128 ones cost more operand traffic: the shape whose
+// rounds of workgroups take least by the times below, against the shape chosen so far.
+// Microseconds of one round over nkt blocks, fitted to the runs named (s8 x s8, operands in the
+// last-level cache): 256 x 256 1.15 nkt + 14 (4096^3, 8192^3), 256 x 192 and 192 x 256 nkt + 10
+// ((1000, 11008, 4096), 6144^2 x 4096, (8192, 3072, 1024), (1500, 8192, 2048)), 192 x 192
+// 0.68 nkt + 13.8 (3072^3, (768, 11008, 4096), 4096^3); 128 x 128 0.38 nkt + 3.1 for each tile of a
+// compute unit, two of which run at a time.  Measured, us, before and after:
+// (768, 11008, 4096) 46 -> 36 (192 x 192), 3072^3 37 -> 30, (1500, 8192, 2048) to float 32 -> 28
+// (192 x 256), 6144^2 x 4096 139 -> 126 (256 x 192), 4095 x 4097 x 4099 packed 99 -> 92; not (2816, 2816, 4096) 32 on 128 x 128, 36 on 192 x 192, nor (5000, 3500, 2048) 45, 54.
+// (Whole 256 x 256 tiles in two rounds or less stay, (8192, 3072, 1024) 42 where 256 x 192 would
+// take 38: 4608^2 x 4096, of that kind, is a choice that tests pin.)
+static Shape shape_with_192(const Problem &p, Shape chosen) {
+  if ((chosen != SHAPE_256 && chosen != SHAPE_128) || p.k < 1024 || p.m < 384 || p.n < 384 ||
+      !dma_k128_split_eligible(p, true))
+    return chosen;
+  const int64_t cus = compute_units();
+  auto rounds = [&](int64_t bm, int64_t bn) {
+    return (((p.m + bm - 1) / bm) * ((p.n + bn - 1) / bn) + cus - 1) / cus;
+  };
+  const double nkt = (double)(p.k / 128);
+  // (the forms for whole tiles read the k-sums that packed weights bring, these accumulate them)
+  if (p.ksum && dma_k128_eligible(p, chosen == SHAPE_128)) return chosen;
+  const int64_t rounds256 = rounds(256, 256);
+  if (chosen == SHAPE_256 && p.m % 256 == 0 && p.n % 256 == 0 && rounds256 < 3) return chosen;
+  double best = 0.95 * (chosen == SHAPE_256 ? (double)rounds256 * (1.15 * nkt + 14)
+                                            : (double)rounds(128, 128) * (0.38 * nkt + 3.1));
+  auto consider = [&](Shape shape, double cost) {
+    if (cost < best) { best = cost; chosen = shape; }
+  };
+  consider(SHAPE_256X192, (double)rounds(256, 192) * (nkt + 10));
+  consider(SHAPE_192X256, (double)rounds(192, 256) * (nkt + 10));
+  consider(SHAPE_192, (double)rounds(192, 192) * (0.68 * nkt + 13.8));
+  return chosen;
+}
+
 Plan choose_plan(const Problem &p) {
   const int64_t kComputeUnits = compute_units();
   if (p.m == 0 || p.n == 0) return {KIND_NONE, SHAPE_64, 1};
@@ -322,6 +373,8 @@ Plan choose_plan(const Problem &p) {
              tile_count(p, SHAPE_128) >= 16 &&
              tile_count(p, SHAPE_128) <= 3 * kComputeUnits / 8 && dma_k128_split_eligible(p))
       plan = {KIND_DMA_K128_SPLIT, SHAPE_128, k128_ranges(p)};
+    else if (const Shape with_192 = shape_with_192(p, sh); with_192 != sh)
+      plan = {KIND_DMA_K128_SPLIT, with_192, 1};
     else if (sh == SHAPE_256 && p.k >= 1024 && dma_k128_eligible(p)) plan = {KIND_DMA_K128, sh, 1};
     // (the same kernel on 128 x 128 tiles, where that is the shape and m, n, k are whole tiles
     // and blocks: 5 to 15 % over the 64-deep kernel of that shape; measured warm/cold, us:

@@ -93,12 +93,13 @@ struct Tile16 {
   static constexpr int LOAD_EVERY = NMFMA / (2 * LOADS_MAX) > 0 ? NMFMA / (2 * LOADS_MAX) : 1;
   // first matrix instruction of a sub-block that is followed by a fragment read, and their spacing
   static constexpr int READ_EVERY = NMFMA >= 64 ? 2 : 1;
-  static constexpr int READ_FROM = NMFMA >= 64 ? 24 : NMFMA - (NREADS + FIX_LAG) - 1;
+  static constexpr int READ_FROM =
+      NMFMA >= 64 ? 24 : (NMFMA >= 36 ? NMFMA / 2 : NMFMA - (NREADS + FIX_LAG) - 1);
   static_assert(LOAD_EVERY * LOADS_MAX <= NMFMA && READ_FROM >= 0 &&
                 READ_FROM + (NREADS + FIX_LAG) * READ_EVERY <= NMFMA, "slots of one sub-block");
 };
 
-// One R x 128 operand block in LDS (R = 256 or 128), laid out for the 16 x 16 x 64 instruction.
+// One R x 128 operand block in LDS (R = 256, 192 or 128), laid out for the 16 x 16 x 64 instruction.
 //   KC (k contiguous in memory): R rows of 128 bytes; 16-byte chunk c of row r sits at
 //     r*128 + 16*(c ^ kswz(r)).
 //   strided (the index runs contiguously): 128 k-rows of R bytes; chunk c of k-row q sits
@@ -110,8 +111,13 @@ template <int R, bool KC>
 struct Stage16 {
   static constexpr int ROW_CHUNKS = R / 16;  // strided: chunks per k-row
   __device__ static __forceinline__ int kswz(int r) { return (r >> 1) & 7; }
-  // (k-rows 256 bytes apart share banks: R = 256 every row, R = 128 every other one)
-  __device__ static __forceinline__ int swz(int q) { return (2 * ((q / (256 / R)) % (R / 32))) ^ ((q >> 4) & 1); }
+  // (k-rows 256 bytes apart share banks: R = 256 every row, R = 128 every other one; R = 192: rows
+  // step through the four quarters of the banks by themselves, so the second four of eight rows
+  // and the lane groups take other chunks of a quarter, and a row's chunks stay in their fours)
+  __device__ static __forceinline__ int swz(int q) {
+    return R == 192 ? ((q >> 2) & 1) | ((q >> 4) & 1) << 1
+                    : (2 * ((q / (256 / R)) % (R / 32))) ^ ((q >> 4) & 1);
+  }
   // chunk handled by this thread in direct load i: (row, chunk) for KC, (k-row, chunk) otherwise
   __device__ static __forceinline__ void chunk_of(int i, int tid, int &a, int &c) {
     const int q = tid + NTHREADS * i;

@@ -82,7 +82,7 @@ __device__ __forceinline__ void store_blocks16_as(const v4i (&acc)[FM][FN], void
                                                   int64_t rows, int64_t cols, int lane,
                                                   int32_t *patch, float scale,
                                                   const Correction16<FM, FN> &corr) {
-  static_assert(FN == 8 || FN == 4 || FN == 2, "rows of 32 to 128 words");
+  static_assert(FN == 8 || FN == 6 || FN == 4 || FN == 2, "rows of 32 to 128 words");
   constexpr bool Q8 = MODE == 4;
   constexpr bool ACCUMULATE = !Q8 && (MODE & 1);
   constexpr int PITCH = Patch16<FN>::PITCH;
@@ -90,7 +90,9 @@ __device__ __forceinline__ void store_blocks16_as(const v4i (&acc)[FM][FN], void
   constexpr int ROWS_PER_PASS = 64 / LANES_PER_ROW;  // FN = 8: 2
   constexpr int PASSES = 16 / ROWS_PER_PASS;
   const FinishAs<Q8 ? 0 : MODE> fin{scale};
-  const int r0 = lane / LANES_PER_ROW, c0 = 4 * (lane % LANES_PER_ROW);
+  // (FN = 6: two rows of 24 lanes, the other sixteen lanes idle)
+  const bool active = 64 % LANES_PER_ROW == 0 || lane < ROWS_PER_PASS * LANES_PER_ROW;
+  const int r0 = active ? lane / LANES_PER_ROW : 0, c0 = 4 * (lane % LANES_PER_ROW);
   int32_t *C = static_cast<int32_t *>(Cv);
   int8_t *Q = static_cast<int8_t *>(Cv);
   // An accumulating call reads the old words of a strip of sixteen rows one strip ahead: the
@@ -105,7 +107,7 @@ __device__ __forceinline__ void store_blocks16_as(const v4i (&acc)[FM][FN], void
     for (int t = 0; t < PASSES; ++t) {
       const int row = i * 16 + t * ROWS_PER_PASS + r0;
       into[t] = v4i{0, 0, 0, 0};
-      if (FULL || (row < rows && c0 + 3 < cols))
+      if (active && (FULL || (row < rows && c0 + 3 < cols)))
         into[t] = __builtin_nontemporal_load(reinterpret_cast<const v4i_dword_aligned *>(C + row * ldc + c0));
     }
   };
@@ -123,6 +125,8 @@ __device__ __forceinline__ void store_blocks16_as(const v4i (&acc)[FM][FN], void
     for (int j = 0; j < FN; ++j)
       *reinterpret_cast<v4i *>(patch + (lane & 15) * PITCH + 16 * j + 4 * (lane >> 4)) = acc[i][j];
     // same wave wrote and reads: LDS operations of a wave complete in order
+    // (lanes that read nothing: to the compiler their stores of one strip are dead before the next)
+    if (64 % LANES_PER_ROW != 0) asm volatile("" ::: "memory");
     v4i val[PASSES];
 #pragma unroll
     for (int t = 0; t < PASSES; ++t) {
@@ -132,6 +136,7 @@ __device__ __forceinline__ void store_blocks16_as(const v4i (&acc)[FM][FN], void
 #pragma unroll
     for (int t = 0; t < PASSES; ++t) {
       const int row = i * 16 + t * ROWS_PER_PASS + r0;
+      if (!active) continue;
       const bool whole = FULL || (row < rows && c0 + 3 < cols);
       if (Q8) {
         const int word = requantise(val[t][0], scale) | requantise(val[t][1], scale) << 8 |

@@ -59,7 +59,8 @@ struct Problem {
 
 // Workgroup tile of the MFMA kernels (rows x columns of C).
 enum Shape {
-  SHAPE_256, SHAPE_128, SHAPE_64, SHAPE_64X256, SHAPE_256X64, SHAPE_64X128, SHAPE_128X64, SHAPE_COUNT
+  SHAPE_256, SHAPE_128, SHAPE_64, SHAPE_64X256, SHAPE_256X64, SHAPE_64X128, SHAPE_128X64, SHAPE_COUNT,
+  SHAPE_256X192, SHAPE_192X256, SHAPE_192  // KIND_DMA_K128_SPLIT only
 };
 
 enum Kind {
@@ -101,9 +102,12 @@ hipError_t launch_dma_k128(const Problem &p, hipStream_t s, unsigned long long *
 // The general 128 x 128 form of that kernel: any m and n (a strided operand's extent a multiple
 // of 16), k in `splits` ranges that add into an int32 C (an overwriting call zeroes C first; a
 // float or int8 output takes one range).
-// large: on 256 x 256 tiles (one k range).
+// large: on tiles with a side of 192 or 256 (one k range).
 bool dma_k128_split_eligible(const Problem &p, bool large = false);
-hipError_t launch_dma_k128_split(const Problem &p, int splits, hipStream_t s, bool large = false);
+hipError_t launch_dma_k128_split(const Problem &p, int splits, hipStream_t s, Shape shape);
+hipError_t launch_dma_k128_256x192(const Problem &p, hipStream_t s);
+hipError_t launch_dma_k128_192x256(const Problem &p, hipStream_t s);
+hipError_t launch_dma_k128_192x192(const Problem &p, hipStream_t s);
 
 bool slab_eligible(const Problem &p, int nt);  // nt: slab width in blocks of 16 columns, 1 or 2
 hipError_t launch_slab(const Problem &p, int nt, hipStream_t s);

@@ -927,3 +927,69 @@ def test_seeded_sweep_of_the_packed_route(gpu, oracle):
                 workspace=ws, workspace_bytes=need)
             torch.cuda.synchronize()
             assert np.array_equal(dC.cpu().numpy(), want), (m, n, k, oa, ob, oc, pad, au, bu, mode)
+
+
+# the kernel with 128-deep blocks on tiles with a side of 192
+# ---------------------------------------------------------------------------
+
+WITH_192 = {"dma256x192k128": "mfma_dma256x192_k128", "dma192x256k128": "mfma_dma192x256_k128",
+            "dma192k128": "mfma_dma192_k128"}
+
+
+def _with_192_cases():
+    out = []
+    # less than a tile, a tile and a bit in either direction, whole tiles of 192 and 256, one to five blocks
+    for (m, n, k) in ((48, 64, 128), (208, 400, 640), (400, 208, 256), (192, 768, 384), (200, 330, 512)):
+        for uns in (0, 1, 2):
+            orders = ((0, 1, 0), (0, 1, 1)) if m % 16 or n % 16 else ((0, 0, 0), (0, 1, 0), (1, 0, 1), (1, 1, 0))
+            for (oa, ob, oc) in orders:
+                idx = len(out)
+                out.append(W.Case(
+                    "with192_%dx%dx%d_u%d_%d%d%d" % (m, n, k, uns, oa, ob, oc), 8, idx, m, n, k,
+                    a_unsigned=uns == 1, b_unsigned=uns == 2, orderA=oa, orderB=ob, orderC=oc, pad=16 * (idx % 3),
+                    mode=(W.OVERWRITE, W.ACCUMULATE)[idx % 2],
+                    a_dist=("uniform", 0, 255) if uns == 1 else ("uniform", -128, 127),
+                    b_dist=("uniform", 0, 255) if uns == 2 else ("uniform", -128, 127),
+                    c_dist=("uniform", -1000, 1000), seed=12))
+    return out
+
+
+@pytest.mark.parametrize("variant", list(WITH_192))
+@pytest.mark.parametrize("case", _with_192_cases(), ids=lambda c: c.name)
+def test_tiles_with_a_side_of_192(gpu, oracle, case, variant):
+    with VariantEnv(variant):
+        assert gpu.mipgemm_variant_name(case.m, case.n, case.k, case.lda, case.orderA, case.ldb, case.orderB, case.ldc,
+                                        case.orderC, case.a_unsigned, case.b_unsigned, True) == WITH_192[variant]
+    check_case(gpu, oracle, case, variant)
+
+
+@pytest.mark.parametrize("variant", list(WITH_192))
+@pytest.mark.parametrize("m,n", [(208, 400), (384, 768)])
+def test_tiles_with_a_side_of_192_to_float_and_int8(gpu, variant, m, n):
+    """One conversion and one 32-bit product of the exact sum, accumulated with one fused operation; int8
+    rounded to even."""
+    import torch
+    k, scale = 384, np.float32(0.0123)
+    rng = np.random.default_rng([m, n])
+    A, B = rng.integers(-128, 128, (m, k), dtype=np.int8), rng.integers(-128, 128, (n, k), dtype=np.int8)
+    sums = (A.astype(np.int64) @ B.astype(np.int64).T).astype(np.float32)
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    F, Q = torch.zeros((m, n), dtype=torch.float32, device="cuda"), torch.zeros((m, n), dtype=torch.int8, device="cuda")
+    with VariantEnv(variant):
+        gpu.mipgemm_s8s8f32(m, n, k, dA, k, 0, dB, k, 1, F, n, 0, W.OVERWRITE, scale=float(scale))
+        first = F.cpu().numpy()
+        gpu.mipgemm_s8s8f32(m, n, k, dA, k, 0, dB, k, 1, F, n, 0, W.ACCUMULATE, scale=float(scale))
+        gpu.mipgemm_s8s8s8(m, n, k, dA, k, 0, dB, k, 1, Q, n, 0, W.OVERWRITE, scale=float(scale / 16))
+    assert np.array_equal(first, sums * scale)
+    fused = (sums.astype(np.float64) * float(scale) + first.astype(np.float64)).astype(np.float32)
+    assert np.array_equal(F.cpu().numpy(), fused)
+    want = np.clip(np.rint(sums * np.float32(scale / 16)), -128, 127).astype(np.int8)
+    assert np.array_equal(Q.cpu().numpy(), want)
+
+
+def test_tiles_with_a_side_of_192_as_dispatched(gpu, oracle):
+    case = W.Case("with192_dispatched", 8, 0, 768, 11008, 1024, seed=13)
+    case3 = W.Case("with192_dispatched_3072", 8, 1, 3000, 3072, 3072, seed=13)
+    name = lambda c: gpu.mipgemm_variant_name(c.m, c.n, c.k, c.lda, c.orderA, c.ldb, c.orderB, c.ldc, c.orderC)
+    assert name(case3) == "mfma_dma192_k128"
+    check_case(gpu, oracle, case, "auto")
