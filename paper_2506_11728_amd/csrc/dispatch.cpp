@@ -260,7 +260,7 @@ static int slab_width(const Problem &p) {
 // compute unit, two of which run at a time.  Measured, us, before and after:
 // (768, 11008, 4096) 46 -> 36 (192 x 192), 3072^3 37 -> 30, (1500, 8192, 2048) to float 32 -> 28
 // (192 x 256), 6144^2 x 4096 139 -> 126 (256 x 192), 4095 x 4097 x 4099 packed 99 -> 92; not (2816, 2816, 4096) 32 on 128 x 128, 36 on 192 x 192, nor (5000, 3500, 2048) 45, 54.
-// (Whole 256 x 256 tiles in two rounds or less stay, (8192, 3072, 1024) 42 where 256 x 192 would
+// (Whole 256 x 256 tiles, or packed operands padded to them, in two rounds or less stay, (8192, 3072, 1024) 42 where 256 x 192 would
 // take 38: 4608^2 x 4096, of that kind, is a choice that tests pin.)
 static Shape shape_with_192(const Problem &p, Shape chosen) {
   if ((chosen != SHAPE_256 && chosen != SHAPE_128) || p.k < 1024 || p.m < 384 || p.n < 384 ||
@@ -274,7 +274,8 @@ static Shape shape_with_192(const Problem &p, Shape chosen) {
   // (the forms for whole tiles read the k-sums that packed weights bring, these accumulate them)
   if (p.ksum && dma_k128_eligible(p, chosen == SHAPE_128)) return chosen;
   const int64_t rounds256 = rounds(256, 256);
-  if (chosen == SHAPE_256 && p.m % 256 == 0 && p.n % 256 == 0 && rounds256 < 3) return chosen;
+  const bool whole = (p.m % 256 == 0 && p.n % 256 == 0) || p.rows_padded_to_256;
+  if (chosen == SHAPE_256 && whole && rounds256 < 3) return chosen;
   double best = 0.95 * (chosen == SHAPE_256 ? (double)rounds256 * (1.15 * nkt + 14)
                                             : (double)rounds(128, 128) * (0.38 * nkt + 3.1));
   auto consider = [&](Shape shape, double cost) {

@@ -611,6 +611,14 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
   const int64_t slot_bytes = count * side * side * 4;
   if (splits > (end - ws) / slot_bytes) splits = (end - ws) / slot_bytes;
   if (splits > 1024) splits = 1024;
+  // (a captured call would keep its counters for every replay, while later calls draw the same ones
+  // again once the ring has gone round: it takes k whole)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (splits > 1 && s != nullptr && hipStreamIsCapturing(s, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    splits = 1;
+  }
+  if (capture != hipStreamCaptureStatusNone) splits = 1;
   if (splits > 1 && splitk_tickets(count, &P.tickets) == hipSuccess) {
     P.splits = (int)splits;
     P.slots = reinterpret_cast<int32_t *>(ws);

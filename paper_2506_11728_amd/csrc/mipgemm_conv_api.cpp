@@ -158,7 +158,8 @@ const char *mipgemm_conv_variant_name(int64_t b, int64_t hi, int64_t wi, int64_t
       MIP_NAME("mfma_tile128"), MIP_NAME("mfma_tile64"), MIP_NAME("mfma_tile64x256"),
       MIP_NAME("mfma_tile256x64"), MIP_NAME("mfma_dma64x128"), MIP_NAME("mfma_dma128x64"),
       MIP_NAME("mfma_tile64x128"), MIP_NAME("mfma_tile128x64"), MIP_NAME("mfma_dma256_k128"), MIP_NAME("mfma_slab16"),
-      MIP_NAME("mfma_slab32"), MIP_NAME("simple")};
+      MIP_NAME("mfma_slab32"), MIP_NAME("mfma_dma256x192_k128"), MIP_NAME("mfma_dma192x256_k128"),
+      MIP_NAME("mfma_dma192_k128"), MIP_NAME("simple")};
 #undef MIP_NAME
   const char *base = mip::plan_name(plan);
   for (const auto &n : names)

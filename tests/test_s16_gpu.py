@@ -173,3 +173,29 @@ def test_s16_rows_further_apart_than_32_bit_offsets(gpu, oracle):
                           workspace=ws, workspace_bytes=ws.numel())
     want = (A2.astype(np.int64) @ B2.astype(np.int64)).astype(np.int32)
     assert np.array_equal(C.cpu().numpy(), want)
+
+
+def test_s16_replayed_from_a_graph(gpu):
+    import torch
+    m, n, k = 64, 192, 1024                            # a shape that splits k outside a capture
+    A2, B2 = _operands(m, n, k, "uniform", 12)
+    A, B = torch.from_numpy(A2).cuda(), torch.from_numpy(B2).cuda()
+    C, E = (torch.zeros((m, n), dtype=torch.int32, device="cuda") for _ in range(2))
+    ws, ws2 = (torch.empty(gpu.mipgemm_workspace_size_s16(m, n, k), dtype=torch.uint8, device="cuda") for _ in range(2))
+    call = lambda out, w: gpu.mipgemm_s16s16s32(m, n, k, A, k, 0, B, n, 0, out, n, 0, W.OVERWRITE, workspace=w,
+                                                workspace_bytes=w.numel())
+    want = (A2.astype(np.int64) @ B2.astype(np.int64)).astype(np.int32)
+    call(E, ws2)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        call(C, ws)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        call(C, ws)
+    for _ in range(3):
+        C.zero_()
+        graph.replay()
+        call(E, ws2)
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy(), want) and np.array_equal(E.cpu().numpy(), want)
