@@ -52,7 +52,8 @@ struct S16Params {
   int splits;     // ranges of k, one per blockIdx.y
   int accumulate;
   int wide_offsets;  // rows of a tile reach further than 32-bit offsets do
-  // splits > 1: `splits` slots of partial sums per tile and one zeroed counter per tile
+  // splits > 1: `splits` slots of partial sums per tile and one zeroed counter per tile; null: the
+  // ranges add into C, which holds zeros (or what the call accumulates into) before the launch
   int32_t *slots;
   unsigned *tickets;
 };
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
       acc[i][j] = (__builtin_bit_cast(v4u, hh[i][j]) << 16) + (__builtin_bit_cast(v4u, mid[i][j]) << 8) +
                   __builtin_bit_cast(v4u, ll[i][j]);
 
-  if (P.splits > 1) {
+  if (__builtin_expect(P.splits > 1 && P.slots, 0)) {
     // Partial sums of a range of k: into the range's slot, with this range's corrections in
     // them; the workgroup that draws the tile's last ticket adds the other slots to its own
     // registers.  Slot accesses are device-scope, the ticket is drawn after the stores
@@ -428,6 +429,33 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
     // the corrections are in the sums
     for (int x = tid; x < BM + BN; x += NT) rows[x] = 0;
     __syncthreads();
+  }
+
+  if (__builtin_expect(P.splits > 1 && !P.slots, 0)) {
+    // The range's sums into C, in any order the same bits.  Turned through the wave's patch as
+    // below, so that an instruction adds to whole rows of the sub-tile: whole cache lines.
+    static_assert(WN == 32, "two rows of the sub-tile to an instruction");
+    const int64_t mw = m0 + wm * WM, col = n0 + wn * WN + (lane & 31);
+    const uint32_t colc = cols[wn * WN + (lane & 31)];
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int row0 = 16 * (i ^ flipA);
+      if (mw + row0 >= P.m) continue;  // wave-uniform
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        *reinterpret_cast<v4u *>(patch + (lane & 15) * PITCH + 16 * (j ^ flipB) + 4 * (lane >> 4)) = acc[i][j];
+      // same wave wrote and reads: LDS operations of a wave complete in order
+      asm volatile("" ::: "memory");
+#pragma unroll 1
+      for (int p = 0; p < 8; ++p) {
+        const int r = 2 * p + (lane >> 5);
+        const int64_t row = mw + row0 + r;
+        if (row < P.m && col < P.n)
+          __hip_atomic_fetch_add(P.C + row * P.ldc + col, patch[r * PITCH + (lane & 31)] + colc + rows[wm * WM + row0 + r],
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    return;
   }
 
   // Sixteen rows at a time turned through the wave's patch, so that a store covers whole rows of
@@ -597,31 +625,49 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
   const int64_t side = large ? 128 : 64, count = tiles(side);
   P.tiles_m = (int)((p.m + side - 1) / side);
   P.tiles_n = (int)((p.n + side - 1) / side);
-  // Ranges of k, where the tiles leave compute units with less than three workgroups (a wave
-  // alone on its SIMD issues at half rate) and the workspace has room for slots: at most four (eight
-  // of few tiles), each of enough blocks to pay for the exchange.  Measured, us, with 1 / 2 / 4 / 8
-  // ranges of k = 4096: 16 tiles 31 / 19 / 13.0 / 11.5, 64 tiles 31 / 19 / 14.0 / 14.6, 128 tiles
-  // 32 / 21 / 18 / 20, 192 tiles 32 / 26 / 22 / 27; of k = 1024: 64 tiles 10.7 / 9.1 / 8.6,
-  // 128 tiles 10.6 / 9.5 / 9.8, 192 tiles 10.7 / 11.1 / 11.1; of k = 512: 64 tiles 7.1 / 7.4.
+  // Ranges of k, where that gives a compute unit at most three workgroups (a wave alone on its SIMD
+  // issues at half rate): at most four, eight of few tiles, sixteen of very few with a very long k,
+  // each of enough blocks to pay for the exchange.  Measured through slots, us, with 1 / 2 / 4 / 8 / 16
+  // ranges of k = 4096: 16 tiles 31 / 19 / 13.3 / 11.9 / 14.2, 64 tiles 31 / 20 / 15.1 / 15.4 / 19,
+  // 128 tiles 32 / 20 / 18 / 21 / 31, 192 tiles 32 / 26 / 23 / 27 / 43; of k = 1024: 64 tiles 10.8 / 9.4 /
+  // 9.4, 128 tiles 10.9 / 10.0 / 10.1, 192 tiles 11.0 / 11.3 / 11.2; of k = 16384: 16 tiles
+  // 112 / 60 / 34 / 21.9 / 19.5.
+  const int64_t most = count > 32 ? 4 : (count > 16 || P.nkt < 256 ? 8 : 16);
   int64_t splits = large ? 1 : 3 * cus / count, blocks = count / 16 > 4 ? count / 16 : 4;
-  if (splits > (count <= 32 ? 8 : 4)) splits = count <= 32 ? 8 : 4;
+  if (splits > most) splits = most;
   if (count > 16 && P.nkt < 12) splits = 1;
   if (tuning().splitk > 0) { splits = tuning().splitk; blocks = 4; }
   if (splits > P.nkt / blocks) splits = P.nkt / blocks;
-  const int64_t slot_bytes = count * side * side * 4;
-  if (splits > (end - ws) / slot_bytes) splits = (end - ws) / slot_bytes;
   if (splits > 1024) splits = 1024;
-  // (a captured call would keep its counters for every replay, while later calls draw the same ones
-  // again once the ring has gone round: it takes k whole)
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (splits > 1 && s != nullptr && hipStreamIsCapturing(s, &capture) != hipSuccess) {
-    (void)hipGetLastError();
-    splits = 1;
-  }
-  if (capture != hipStreamCaptureStatusNone) splits = 1;
-  if (splits > 1 && splitk_tickets(count, &P.tickets) == hipSuccess) {
+  if (splits > 1) {
+    // The ranges meet in slots, where the workspace has room for at least half of them.  A captured
+    // call would keep its counters for every replay, while later calls draw the same ones again
+    // once the ring has gone round: it gets none.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (s != nullptr && hipStreamIsCapturing(s, &capture) != hipSuccess) {
+      (void)hipGetLastError();
+      capture = hipStreamCaptureStatusActive;
+    }
+    const int64_t room = (end - ws) / (count * side * side * 4), fit = room < splits ? room : splits;
+    if (fit > 1 && 2 * fit >= splits && capture == hipStreamCaptureStatusNone &&
+        splitk_tickets(count, &P.tickets) == hipSuccess) {
+      P.slots = reinterpret_cast<int32_t *>(ws);
+      splits = fit;
+    } else if (!p.accumulate) {
+      // Otherwise they add into C, which an overwriting call has zeroed first: 2 us more, which a
+      // short k does not save.  Measured, us, k whole and in the ranges chosen above: k = 512 16 tiles
+      // 7.5 and 7.7; k = 1024 16 tiles 10.6 and 7.7, 64 tiles 10.7 and 9.5, 128 tiles 10.8 and 11.5;
+      // k = 2048 128 tiles 17.7 and 14.1, 192 tiles 17.8 and 17.9; k = 4096 192 tiles 32 and 26.
+      if (P.nkt < 12 + count / 8 && tuning().splitk == 0) {
+        splits = 1;
+      } else {
+        Problem z;
+        z.m = p.m; z.n = p.n; z.k = 0; z.C = p.C; z.ldc = p.ldc;
+        const hipError_t e = launch_fill_zero(z, s);
+        if (e != hipSuccess) return e;
+      }
+    }
     P.splits = (int)splits;
-    P.slots = reinterpret_cast<int32_t *>(ws);
   }
   return large ? launch_tiles<2, 4, 4, 2>(P, a_kc, b_kc, s) : launch_tiles<2, 2, 2, 2>(P, a_kc, b_kc, s);
 }

@@ -199,3 +199,81 @@ def test_s16_replayed_from_a_graph(gpu):
         call(E, ws2)
         torch.cuda.synchronize()
         assert np.array_equal(C.cpu().numpy(), want) and np.array_equal(E.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("variant", ["s16_64", "s16_128"])
+@pytest.mark.parametrize("orders", [(0, 1, 0), (1, 0, 1)])
+@pytest.mark.parametrize("mode", [W.OVERWRITE, W.ACCUMULATE])
+def test_s16_ranges_that_add_into_c(gpu, variant, orders, mode):
+    """A captured call, and one whose workspace has no room for slots: ranges of k meet in C itself, inside
+    its leading dimension, on every replay."""
+    import torch
+    oa, ob, oc = orders
+    m, n, k, pad = 130, 201, 1352, 3
+    A2, B2 = _operands(m, n, k, "uniform", 13)
+    A, lda = _flat(A2, oa, 8, 0x5A5A)
+    B, ldb = _flat(B2, ob, 8, 0x5A5A)
+    ldc = (n if oc == W.ROW_MAJOR else m) + pad
+    C0 = np.random.default_rng(14).integers(-1000, 1000, size=(m if oc == W.ROW_MAJOR else n) * ldc, dtype=np.int32)
+    want = C0.copy()
+    view = want.reshape(-1, ldc)[:, :ldc - pad]
+    product = (A2.astype(np.int64) @ B2.astype(np.int64)).astype(np.int32)
+    view[:] = (product if oc == W.ROW_MAJOR else product.T) + (view if mode == W.ACCUMULATE else 0)
+    dA, dB, first = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), torch.from_numpy(C0).cuda()
+    dC = first.clone()
+    ws = torch.empty(gpu.mipgemm_workspace_size_s16(m, n, k), dtype=torch.uint8, device="cuda")
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    stream.wait_stream(torch.cuda.current_stream())
+    with gpu.tuning(MIPGEMM_VARIANT=variant, MIPGEMM_SPLITK="3"):
+        with torch.cuda.graph(graph, stream=stream):
+            gpu.mipgemm_s16s16s32(m, n, k, dA, lda, oa, dB, ldb, ob, dC, ldc, oc, mode, workspace=ws,
+                                  workspace_bytes=ws.numel())
+    for replay in range(3):
+        dC.copy_(first)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(dC.cpu().numpy(), want), "replay %d" % replay
+
+
+def _time_of_a_call(gpu, m, n, k, captured, shift=0):
+    """us a call, the best of several; shift: elements between a 16-byte boundary and the operands."""
+    import torch
+    A = torch.zeros(m * k + 8, dtype=torch.int16, device="cuda")[shift:]
+    B = torch.zeros(k * n + 8, dtype=torch.int16, device="cuda")[shift:]
+    C = torch.zeros(m * n, dtype=torch.int32, device="cuda")
+    ws = torch.empty(gpu.mipgemm_workspace_size_s16(m, n, k), dtype=torch.uint8, device="cuda")
+    calls = 10
+
+    def body():
+        for _ in range(calls):
+            gpu.mipgemm_s16s16s32(m, n, k, A, k, 0, B, k, 1, C, n, 0, W.OVERWRITE, workspace=ws,
+                                  workspace_bytes=ws.numel())
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        body()
+    stream.synchronize()
+    if captured:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            body()
+        body = graph.replay
+    times = []
+    with torch.cuda.stream(stream):
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            body()
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end) * 1e3 / calls)
+    return min(times)
+
+
+@pytest.mark.parametrize("m,n,k", [(64, 192, 16384), (1, 1024, 16384), (5, 7, 30000)])
+def test_s16_few_tiles_keep_their_ranges_of_k(gpu, m, n, k):
+    """A few tiles with k whole run on as many compute units, five times as long as in ranges: neither a
+    capture nor operands rewritten into the workspace, which leave no room for slots there, may cost them."""
+    plain = _time_of_a_call(gpu, m, n, k, False)
+    assert _time_of_a_call(gpu, m, n, k, True) < 2.5 * plain
+    assert _time_of_a_call(gpu, m, n, k, False, shift=1) < 2.5 * plain
