@@ -537,13 +537,14 @@ size_t mipgemm_workspace_size(int64_t m, int64_t n, int64_t k,
  * call can use room for slots of partial sums: a problem with too few tiles of C
  * to occupy the device splits k over several workgroups per tile, and since float
  * sums must not be combined in arbitrary order, the workgroups of a tile meet in
- * such slots with their int32 partial sums (splits x tile size x 4 bytes per tile;
+ * such slots with their int32 partial sums (splits x tile size x 4 + 4 bytes per tile;
  * the last to arrive adds them up, still in integers, and converts once: same
  * result as an unsplit call).  Without the room such a call keeps all of k in one
  * workgroup per tile and runs up to twice as long on long-k, few-tile shapes.
  * (The per-tile counters of that scheme live in a 4 MiB static device array of
  * the library, handed out in rotation, so that concurrent calls use different
- * ones; the int32 entry points add their k ranges into C with atomics and need
+ * ones; a call under stream capture has them in its workspace, behind the slots, and
+ * keeps k whole where they do not fit; the int32 entry points add their k ranges into C with atomics and need
  * no slots.)
  */
 size_t mipgemm_workspace_size_f32(int64_t m, int64_t n, int64_t k,

@@ -406,8 +406,11 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   // ranges 8.3 against 9.1 us, (512, 512, 4096) 10.5 against 17 us.)
   if (splits > 1 && p.out_float && p.ws &&
       p.ws_bytes / ((size_t)BM * BN * 4) / (size_t)splits >= (size_t)all_tiles) {
+    const size_t bytes = (size_t)all_tiles * (size_t)splits * ((size_t)BM * BN * 4);
+    const bool counters_fit = (p.ws_bytes - bytes) / sizeof(unsigned) >= (size_t)all_tiles;
+    unsigned *own = counters_fit ? reinterpret_cast<unsigned *>(static_cast<uint8_t *>(p.ws) + bytes) : nullptr;
     unsigned *tickets = nullptr;
-    if (splitk_tickets(all_tiles, &tickets) == hipSuccess) {
+    if (splitk_tickets(all_tiles, s, own, &tickets) == hipSuccess) {
       P.slots = static_cast<int32_t *>(p.ws);
       P.tickets = tickets;
     }

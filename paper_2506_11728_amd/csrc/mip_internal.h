@@ -171,11 +171,13 @@ struct S16Problem {
 };
 hipError_t launch_s16(const S16Problem &p, hipStream_t s);
 
-// `count` zeroed 32-bit counters in device memory that no other call in flight uses: the
-// tickets of split k through partial-sum slots.  The kernels leave them zeroed.
-hipError_t splitk_tickets(int64_t count, unsigned **out);
+// `count` zeroed 32-bit counters in device memory that no other call in flight uses, for a call
+// on stream s: the tickets of split k through partial-sum slots.  The kernels leave them zeroed.
+// own: `count` words of the call's workspace, which become the counters of a call that is being
+// captured; without them (null) such a call gets an error.  A call that gets an error does without slots.
+hipError_t splitk_tickets(int64_t count, hipStream_t s, unsigned *own, unsigned **out);
 
-// Bytes of partial-sum slots the plan's split k wants (0: no split, or a kernel that adds
+// Bytes of partial-sum slots, and of counters behind them, that the plan's split k wants (0: no split, or a kernel that adds
 // into C with atomics whatever it is given).
 size_t splitk_slot_bytes(const Problem &p, const Plan &plan);
 

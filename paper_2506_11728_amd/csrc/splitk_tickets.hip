@@ -3,8 +3,10 @@
 // device array, zero from the moment the code object is loaded, because a caller's workspace
 // arrives with unknown contents and zeroing it would cost the very launch this scheme saves.
 // Every call takes the next `count` counters of the ring, so calls in flight at the same
-// time (other streams, other threads, other nodes of a captured graph) work on different
-// counters; a range is handed out again only after the whole ring has gone round.
+// time (other streams, other threads) work on different counters; a range is handed out again
+// only after the whole ring has gone round.  A call that is being captured would keep its
+// counters for every replay of the graph, at any later time, beside calls that have drawn the same ones
+// since: it takes none of the ring, but room of its own, which a kernel of the call zeroes.
 #include <atomic>
 #include <mutex>
 
@@ -28,8 +30,21 @@ PerDevice g_device[MAX_DEVICES];
 
 }  // namespace
 
-hipError_t splitk_tickets(int64_t count, unsigned **out) {
-  if (count < 1 || count > TICKETS / 4) return hipErrorInvalidValue;  // the caller falls back to atomics
+hipError_t splitk_tickets(int64_t count, hipStream_t s, unsigned *own, unsigned **out) {
+  if (count < 1 || count > TICKETS / 4) return hipErrorInvalidValue;
+  // (the null stream cannot be captured, and asking about it is an error while another one is)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (s != nullptr && hipStreamIsCapturing(s, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return hipErrorStreamCaptureUnsupported;
+  }
+  if (capture != hipStreamCaptureStatusNone) {
+    if (!own) return hipErrorStreamCaptureUnsupported;
+    Problem z;
+    z.m = 1; z.n = count; z.k = 0; z.C = reinterpret_cast<int32_t *>(own); z.ldc = count;
+    *out = own;
+    return launch_fill_zero(z, s);
+  }
   int device = 0;
   hipError_t e = hipGetDevice(&device);
   if (e != hipSuccess) return e;

@@ -242,3 +242,68 @@ def test_float_split_k_on_two_streams_at_once(gpu, oracle):
     S = np.rint(want / float(np.float32(0.01)))
     for o in outs:
         assert np.array_equal(o.cpu().numpy().reshape(case.m, case.n), S.astype(np.float32) * np.float32(0.01))
+
+
+def _captured_float_call(gpu, m, n, k, A, B, C, mode, ws, bytes_given, variant="dma64", splits=2):
+    import torch
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    stream.wait_stream(torch.cuda.current_stream())
+    with gpu.tuning(MIPGEMM_VARIANT=variant, MIPGEMM_SPLITK=splits):
+        with torch.cuda.graph(graph, stream=stream):
+            gpu.mipgemm_s8s8f32(m, n, k, A, k, 0, B, k, 1, C, n, 0, mode, workspace=ws, workspace_bytes=bytes_given)
+    return stream, graph
+
+
+@pytest.mark.parametrize("room", ["counters", "slots alone", "less"])
+def test_captured_float_split_k_brings_its_own_counters(gpu, room):
+    """Whatever the workspace holds before a replay; one range where the counters do not fit."""
+    import torch
+    m, n, k, splits = 70, 200, 1024, 3
+    tiles, slots = 2 * 4, 2 * 4 * 3 * 64 * 64 * 4
+    given = slots + {"counters": 4 * tiles, "slots alone": 4 * tiles - 4, "less": -16}[room]
+    rng = np.random.default_rng(23)
+    A, B = rng.integers(-128, 128, (m, k), dtype=np.int8), rng.integers(-128, 128, (n, k), dtype=np.int8)
+    want = (A.astype(np.int64) @ B.astype(np.int64).T).astype(np.float32)
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    C = torch.zeros((m, n), dtype=torch.float32, device="cuda")
+    ws = torch.full((slots + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    _, graph = _captured_float_call(gpu, m, n, k, dA, dB, C, W.OVERWRITE, ws, given, splits=splits)
+    for replay in range(3):
+        C.zero_()
+        ws.fill_(0xFF if replay == 1 else 0x5A)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy(), want), "replay %d" % replay
+        assert (ws[given:] == (0xFF if replay == 1 else 0x5A)).all()      # nothing behind the workspace
+
+
+def test_captured_float_split_k_beside_a_whole_round_of_counters(gpu):
+    """A graph replayed on one stream while calls on another go once round the ring of counters: the one
+    that draws what the captured call would have drawn from it runs beside a replay."""
+    import torch
+    m, n, k = 128, 4096, 512
+    rng = np.random.default_rng(24)
+    A, B = rng.integers(-1, 2, (m, k), dtype=np.int8), rng.integers(-1, 2, (n, k), dtype=np.int8)
+    one = A.astype(np.int64) @ B.astype(np.int64).T
+    calls = (1 << 20) // 128 + 64
+    assert np.abs(one).max() * calls < 1 << 24                            # every float sum below is exact
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    C, E = (torch.zeros((m, n), dtype=torch.float32, device="cuda") for _ in range(2))
+    ws, ws2 = (torch.empty(128 * 2 * 64 * 64 * 4 + 512, dtype=torch.uint8, device="cuda") for _ in range(2))
+    stream, graph = _captured_float_call(gpu, m, n, k, dA, dB, C, W.ACCUMULATE, ws, ws.numel())
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    replays = 0
+    with gpu.tuning(MIPGEMM_VARIANT="dma64", MIPGEMM_SPLITK=2):
+        for call in range(calls):
+            gpu.mipgemm_s8s8f32(m, n, k, dA, k, 0, dB, k, 1, E, n, 0, W.ACCUMULATE, workspace=ws2,
+                                workspace_bytes=ws2.numel(), stream=other)
+            if call % 4 == 0:
+                with torch.cuda.stream(stream):
+                    graph.replay()
+                replays += 1
+            if call % 512 == 511:
+                torch.cuda.synchronize()
+    torch.cuda.synchronize()
+    assert np.array_equal(E.cpu().numpy(), (one * calls).astype(np.float32))
+    assert np.array_equal(C.cpu().numpy(), (one * replays).astype(np.float32))
