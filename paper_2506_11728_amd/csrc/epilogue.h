@@ -378,15 +378,18 @@ __device__ __forceinline__ void store_blocks_q8_via_lds(const v16i (&acc)[FM][FN
 __device__ __forceinline__ void store16_device_scope(v4i *p, v4i v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
 }
-__device__ __forceinline__ v4i load16_device_scope(const v4i *p) {
-  v4i v;
-  asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-  return v;  // in flight: the caller waits with loads_landed before touching it
-}
-// "the loads issued above have landed": ties the registers to the wait, so that nothing that
-// uses them is scheduled before it
-__device__ __forceinline__ void loads_landed(v4i &a, v4i &b, v4i &c, v4i &d) {
-  asm volatile("s_waitcnt vmcnt(0)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d)::"memory");
+// Four pieces of a slot, 1024 bytes apart.  The wait sits in the statement that loads, so no
+// register is in use while a load into it is in flight.
+__device__ __forceinline__ void load_slot_quad(const v4i *p, v4i (&v)[4]) {
+  asm volatile(
+      "global_load_dwordx4 %0, %4, off sc1\n\t"
+      "global_load_dwordx4 %1, %4, off offset:1024 sc1\n\t"
+      "global_load_dwordx4 %2, %4, off offset:2048 sc1\n\t"
+      "global_load_dwordx4 %3, %4, off offset:3072 sc1\n\t"
+      "s_waitcnt vmcnt(0)"
+      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+      : "v"(p)
+      : "memory");
 }
 
 template <int FM, int FN>
@@ -415,9 +418,7 @@ __device__ __forceinline__ bool combine_k_ranges(v16i (&acc)[FM][FN], int32_t *s
 #pragma unroll
     for (int b = 0; b < FM * FN; ++b) {
       v4i v[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] = load16_device_scope(other + (b * 4 + q) * 64);
-      loads_landed(v[0], v[1], v[2], v[3]);
+      load_slot_quad(other + b * 256, v);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll

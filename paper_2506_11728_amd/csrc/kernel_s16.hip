@@ -128,20 +128,6 @@ struct StageS16 {
   }
 };
 
-// Device-scope accesses to the slots of partial sums: the wait sits in the statement that
-// loads, so no register is in use while a load into it is in flight.
-__device__ __forceinline__ void load_slot_quad(const v4i *p, v4i (&v)[4]) {
-  asm volatile(
-      "global_load_dwordx4 %0, %4, off sc1\n\t"
-      "global_load_dwordx4 %1, %4, off offset:1024 sc1\n\t"
-      "global_load_dwordx4 %2, %4, off offset:2048 sc1\n\t"
-      "global_load_dwordx4 %3, %4, off offset:3072 sc1\n\t"
-      "s_waitcnt vmcnt(0)"
-      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-      : "v"(p)
-      : "memory");
-}
-
 // WR x WC waves over a tile of C, each on FM x FN blocks of 16 x 16.  Fragments of block t + 1 are
 // read and split while block t is multiplied; loads run two blocks further ahead.  Two waves to
 // a SIMD: one alone issues an ordinary vector instruction only every eight clocks.
