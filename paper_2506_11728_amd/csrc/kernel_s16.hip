@@ -626,10 +626,10 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
   if (splits > P.nkt / blocks) splits = P.nkt / blocks;
   if (splits > 1024) splits = 1024;
   if (splits > 1) {
-    // The ranges meet in slots, where the workspace has room for at least half of them and the call is
-    // not being captured (splitk_tickets).
+    // The ranges meet in slots, where the workspace has room for at least half of them.  (A captured
+    // call, whose counters are never handed out again, does as well without.)
     const int64_t room = (end - ws) / (count * side * side * 4), fit = room < splits ? room : splits;
-    if (fit > 1 && 2 * fit >= splits && splitk_tickets(count, s, nullptr, &P.tickets) == hipSuccess) {
+    if (fit > 1 && 2 * fit >= splits && !being_captured(s) && splitk_tickets(count, s, nullptr, &P.tickets) == hipSuccess) {
       P.slots = reinterpret_cast<int32_t *>(ws);
       splits = fit;
     } else if (!p.accumulate) {

@@ -173,8 +173,9 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s);
 
 // `count` zeroed 32-bit counters in device memory that no other call in flight uses, for a call
 // on stream s: the tickets of split k through partial-sum slots.  The kernels leave them zeroed.
-// own: `count` words of the call's workspace, which become the counters of a call that is being
-// captured; without them (null) such a call gets an error.  A call that gets an error does without slots.
+// own: `count` words of the call's workspace, or null: what a call that is being captured falls back
+// to.  A call that gets an error does without slots.
+bool being_captured(hipStream_t s);
 hipError_t splitk_tickets(int64_t count, hipStream_t s, unsigned *own, unsigned **out);
 
 // Bytes of partial-sum slots, and of counters behind them, that the plan's split k wants (0: no split, or a kernel that adds

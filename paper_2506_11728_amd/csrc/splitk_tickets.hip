@@ -4,9 +4,10 @@
 // arrives with unknown contents and zeroing it would cost the very launch this scheme saves.
 // Every call takes the next `count` counters of the ring, so calls in flight at the same
 // time (other streams, other threads) work on different counters; a range is handed out again
-// only after the whole ring has gone round.  A call that is being captured would keep its
-// counters for every replay of the graph, at any later time, beside calls that have drawn the same ones
-// since: it takes none of the ring, but room of its own, which a kernel of the call zeroes.
+// only after the whole ring has gone round.  A call that is being captured keeps its counters for
+// every replay of the graph, at any later time, beside calls that would have drawn the same ones
+// since: its counters come from an array of their own and are never handed out again.  Once
+// that is used up they lie in the call's workspace, where a kernel of the call zeroes them (1.5 us).
 #include <atomic>
 #include <mutex>
 
@@ -16,52 +17,66 @@ namespace mip {
 
 namespace {
 
-constexpr int64_t TICKETS = 1 << 20;  // 4 MiB per device
-static __device__ unsigned g_tickets[TICKETS];
+constexpr int64_t TICKETS = 1 << 20;   // 4 MiB per device
+constexpr int64_t CAPTURED = 1 << 19;  // some thousands of captured calls
+static __device__ unsigned g_tickets[TICKETS], g_captured[CAPTURED];
 
 constexpr int MAX_DEVICES = 64;
 struct PerDevice {
   std::once_flag once;
-  unsigned *base = nullptr;
+  unsigned *ring = nullptr, *captured = nullptr;
   hipError_t status = hipErrorNotInitialized;
-  std::atomic<uint64_t> cursor{0};
+  std::atomic<uint64_t> cursor{0}, captured_cursor{0};
 };
 PerDevice g_device[MAX_DEVICES];
 
 }  // namespace
 
-hipError_t splitk_tickets(int64_t count, hipStream_t s, unsigned *own, unsigned **out) {
-  if (count < 1 || count > TICKETS / 4) return hipErrorInvalidValue;
-  // (the null stream cannot be captured, and asking about it is an error while another one is)
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (s != nullptr && hipStreamIsCapturing(s, &capture) != hipSuccess) {
+bool being_captured(hipStream_t s) {
+  // (the null stream cannot be, and asking about it is an error while another stream is)
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (s == nullptr) return false;
+  if (hipStreamIsCapturing(s, &status) != hipSuccess) {
     (void)hipGetLastError();
-    return hipErrorStreamCaptureUnsupported;
+    return true;
   }
-  if (capture != hipStreamCaptureStatusNone) {
-    if (!own) return hipErrorStreamCaptureUnsupported;
-    Problem z;
-    z.m = 1; z.n = count; z.k = 0; z.C = reinterpret_cast<int32_t *>(own); z.ldc = count;
-    *out = own;
-    return launch_fill_zero(z, s);
-  }
+  return status != hipStreamCaptureStatusNone;
+}
+
+hipError_t splitk_tickets(int64_t count, hipStream_t s, unsigned *own, unsigned **out) {
+  if (count < 1 || count > CAPTURED / 4) return hipErrorInvalidValue;
   int device = 0;
   hipError_t e = hipGetDevice(&device);
   if (e != hipSuccess) return e;
   if (device < 0 || device >= MAX_DEVICES) return hipErrorInvalidDevice;
   PerDevice &d = g_device[device];
   std::call_once(d.once, [&d] {
-    void *p = nullptr;
-    d.status = hipGetSymbolAddress(&p, HIP_SYMBOL(g_tickets));
-    d.base = d.status == hipSuccess ? static_cast<unsigned *>(p) : nullptr;
+    void *ring = nullptr, *captured = nullptr;
+    d.status = hipGetSymbolAddress(&ring, HIP_SYMBOL(g_tickets));
+    if (d.status == hipSuccess) d.status = hipGetSymbolAddress(&captured, HIP_SYMBOL(g_captured));
+    d.ring = static_cast<unsigned *>(ring);
+    d.captured = static_cast<unsigned *>(captured);
   });
   if (d.status != hipSuccess) return d.status;
+  if (being_captured(s)) {
+    uint64_t at = d.captured_cursor.load(std::memory_order_relaxed);
+    while (at + (uint64_t)count <= (uint64_t)CAPTURED)
+      if (d.captured_cursor.compare_exchange_weak(at, at + (uint64_t)count, std::memory_order_relaxed)) {
+        *out = d.captured + at;
+        return hipSuccess;
+      }
+    if (!own) return hipErrorOutOfMemory;
+    Problem z;
+    z.m = 1; z.n = count; z.k = 0; z.C = reinterpret_cast<int32_t *>(own); z.ldc = count;
+    *out = own;
+    return launch_fill_zero(z, s);
+  }
   // the next `count` counters that do not straddle the end of the ring
   uint64_t at = d.cursor.load(std::memory_order_relaxed), first;
   do {
     first = at + (uint64_t)count > (uint64_t)TICKETS ? 0 : at;
   } while (!d.cursor.compare_exchange_weak(at, first + (uint64_t)count, std::memory_order_relaxed));
-  *out = d.base + first;
+  *out = d.ring + first;
   return hipSuccess;
 }
 

@@ -255,8 +255,10 @@ def _captured_float_call(gpu, m, n, k, A, B, C, mode, ws, bytes_given, variant="
 
 
 @pytest.mark.parametrize("room", ["counters", "slots alone", "less"])
-def test_captured_float_split_k_brings_its_own_counters(gpu, room):
-    """Whatever the workspace holds before a replay; one range where the counters do not fit."""
+@pytest.mark.parametrize("pool", ["counters of its own", "used up"])
+def test_captured_float_split_k_whatever_the_workspace_holds(gpu, room, pool):
+    """Counters that no other call is handed, then, once the library has none left, in the workspace, which holds
+    anything before a replay; one range where they do not fit."""
     import torch
     m, n, k, splits = 70, 200, 1024, 3
     tiles, slots = 2 * 4, 2 * 4 * 3 * 64 * 64 * 4
@@ -267,6 +269,8 @@ def test_captured_float_split_k_brings_its_own_counters(gpu, room):
     dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
     C = torch.zeros((m, n), dtype=torch.float32, device="cuda")
     ws = torch.full((slots + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    if pool == "used up":
+        _use_up_the_counters(gpu)
     _, graph = _captured_float_call(gpu, m, n, k, dA, dB, C, W.OVERWRITE, ws, given, splits=splits)
     for replay in range(3):
         C.zero_()
@@ -275,6 +279,22 @@ def test_captured_float_split_k_brings_its_own_counters(gpu, room):
         torch.cuda.synchronize()
         assert np.array_equal(C.cpu().numpy(), want), "replay %d" % replay
         assert (ws[given:] == (0xFF if replay == 1 else 0x5A)).all()      # nothing behind the workspace
+
+
+def _use_up_the_counters(gpu):
+    """Captures (and never runs) calls of 1024 tiles until the counters kept for captured calls are gone, down to the last eight."""
+    import torch
+    A = torch.zeros(64 * 32 * 128, dtype=torch.int8, device="cuda")
+    C = torch.zeros(64 * 32 * 64 * 32, dtype=torch.float32, device="cuda")
+    ws = torch.empty(2 * 1024 * 64 * 64 * 4 + 4096, dtype=torch.uint8, device="cuda")
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    stream.wait_stream(torch.cuda.current_stream())
+    with gpu.tuning(MIPGEMM_VARIANT="dma64", MIPGEMM_SPLITK=2):
+        with torch.cuda.graph(graph, stream=stream):
+            for side, calls in ((64 * 32, 512), (64, 1024)):
+                for _ in range(calls):
+                    gpu.mipgemm_s8s8f32(side, side, 128, A, 128, 0, A, 128, 1, C, side, 0, W.OVERWRITE, workspace=ws,
+                                        workspace_bytes=ws.numel())
 
 
 def test_captured_float_split_k_beside_a_whole_round_of_counters(gpu):
