@@ -193,60 +193,90 @@ size_t splitk_slot_bytes(const Problem &p, const Plan &plan) {
 // A few rows of A: width of the slabs, in blocks of 16 columns, where a workgroup per slab of B is
 // the better plan, 0 where tiles are.  One pass over B in one launch, without atomics or a zero
 // fill, against tiles that share A between more columns and split k over workgroups.
-// Measured on operands that stay in the last-level cache, us, slabs of 16 / 32 / 64 columns
-// against the best tile.  B k-contiguous:
-//   m = 8    (8192, 4096) 10.2 / 8.7 / 8.2 against 10.3, (5120, 5120) 10.2 / 7.6 / 8.3 against 10.0,
-//            (2048, 8192) 6.7 / 7.2 / 9.3 against 7.9
-//   m = 16   (11008, 4096) 14.1 / 12.3 / 9.8 against 13.7, (3072, 3072) 4.4 / 4.7 / 5.5 against 6.9
-//   m = 32   (11008, 4096) 16.4 / 14.3 / 12.3 against 14.4, (8192, 4096) 11.1 / 9.0 / 9.9 against 12.4,
-//            (4096, 11008) 13.2 / 14.2 / 20 against 15.3, but (12288, 1024) 8.5 / 7.5 / 6.8 against 6.2
-//   m = 64   (4096, 4096) 8.6 / 10.5 / 14.8 against 11.5, (8192, 4096) 13.3 / 10.9 / 14.0 against 13.1,
-//            (16384, 8192) 52 / 44 / 37.5 against 41, but (11008, 4096) 18 / 18 / 15 against 13.6 (two
-//            thirds of a round) and (4096, 11008) 17.7 / 20.5 / 28.6 against 17.1
-// B row-major, whose rows a narrow slab takes in pieces of 16 bytes a column block:
-//   m = 16   (11008, 4096) 24 / 17.4 / 11.0 against 13.3, (12288, 1024) 10.3 / 7.8 / 6.0 against 7.8,
-//            (5120, 2048) 10.8 / 7.3 / 8.2 against 8.7, but (5120, 5120) 21 / 14.5 / 16 against 10.2,
-//            (16384, 8192) 82 / 62 / 38 against 33.5
-//   m = 32   (11008, 4096) 26 / 19 / 13.1 against 14.0, (12288, 1024) 11.0 / 8.5 / 7.5 against 6.5
-// Adding into an int32 C needs no zero fill, and the tiles win or tie, except against wide slabs:
-// (16, 11008, 4096) 10.1 against 11.2, row-major 11.3 against 12.6.
+//
+// The width is the narrowest of which one round of compute units holds all slabs: a narrower one leaves a
+// second round mostly idle, a wider one has fewer bytes of B in flight.  Up to 16 rows, where the
+// shallow rings put two workgroups on a compute unit, more slabs than that do no harm.
+//
+// Where slabs are taken was measured on 14 to 36 widths n, 7 to 10 depths k and 5 to 8 row counts
+// each, with operands that stay in the last-level cache ("warm") and with operands that come from
+// memory ("cold", what decoding sees: the weights of a layer are gone when its turn comes again).
+// us, cold / warm, slabs against tiles, (m, n, k), B k-contiguous:
+//   (32, 8192, 4096) 10.7 / 6.8 against 17.7 / 12.1, (24, 12288, 4096) 15.0 / 11.8 against 19.2 / 12.8;
+//   but (24, 12288, 1024) 6.8 / 5.2 against 7.3 / 4.8 and, a third of a second round with more than
+//   16 rows, (24, 22016, 3072) 22 / 17.6 against 23 / 15.0.
+// B row-major, whose rows a slab takes in pieces of 16 bytes a column block, where the tiles of 256
+// columns take whole lines:
+//   (16, 8192, 2048) 10.0 / 5.4 against 10.5 / 6.7,
+//   (8, 12288, 2048) 11.7 / 7.1 against 12.8 / 8.5, but (16, 6144, 3072) 13.7 / 8.0 against 11.0 / 7.8
+//   and (8, 12288, 4096) 19.6 / 13.1 against 15.3 / 13.3.
+// How deep they may go depends on the leading dimension: pieces whole multiples of 512 bytes apart
+// meet in few memory channels: (16, 11264, 3072) 1.18 times the tiles' cold time, (16, 12288, 3072) at
+// ld = 12352 0.90.
+// Adding into an int32 C needs no zero fill, and the tiles win or tie except against slabs of 64 columns of
+// a k-contiguous B: (16, 11008, 4096) 12.5 / 9.9 against 14.1 / 11.7; row-major
+// (1, 10240, 4096) 21 / 13.4 against 11.6 / 9.7.
 static int slab_width(const Problem &p) {
   if (p.m > 64 || !slab_eligible(p, 1)) return 0;
+  const int64_t cus = compute_units(), m = p.m, n = p.n, k = p.k;
   const bool kc = p.b_sk == 1;
-  const bool adds_in_place = p.accumulate && !p.out_float && p.k >= (p.m >= 16 ? 1024 : 1536);
-  auto fits = [&](int nt, int64_t least) { return p.n / (16 * nt) >= least && slab_eligible(p, nt); };
-  // (at most four rows leave 64 columns little to reuse: two thirds of a round of narrow slabs, two
-  // workgroups to a compute unit, hold the same bytes in flight)
-  const int width = !(kc && p.m <= 4 && p.n / 64 < 256) && fits(4, kc && p.m <= 16 ? 128 : 160) ? 4
-                    : (fits(2, 160) && !(kc && p.m <= 4 && p.n / 32 > 256)                      ? 2
-                                                                                                 : 1);
-  if (kc) {
-    if (adds_in_place) return p.m <= 32 && fits(4, 160) ? 4 : 0;
-    if (p.n / 16 >= 128) {
-      if (p.m <= 16) return width;
-      if (p.m <= 32 && (p.k >= 2048 || p.n / 16 <= 256)) return width;
-      const int64_t cus = compute_units(), slabs = p.n / 64;
-      const bool full_round = 10 * slabs >= 9 * ((slabs + cus - 1) / cus * cus);
-      // (above 32 rows an int32 product on unpacked operands keeps the tiles: the choice that tests pin)
-      if (p.m > 32 && (p.packed_weights || p.out_float) && p.k >= 2048 && p.k <= 8192 && (width < 4 || full_round))
-        return width;
+  const bool into_int32 = p.accumulate && !p.out_float;
+  const bool adds_in_place = into_int32 && k >= (m >= 16 ? 1024 : 1536);
+  auto slabs = [&](int nt) { return n / (16 * nt); };
+  int width = slabs(1) <= cus ? 1 : (slabs(2) <= cus ? 2 : 4);
+  if (!slab_eligible(p, width)) width = 1;
+  const bool one_round = slabs(width) <= cus;
+  // Up to 16 rows the tiles of 256 columns, in as many ranges of k as fill the chip, may leave an XCD
+  // (an eighth of it) a second round: (16, 12352, 4096) row-major 14.9 / 11.0 on slabs, 20.7 / 17.5 on tiles.
+  const int64_t tiles = (n + 255) / 256;
+  const bool crowded = m <= 16 && k / 512 * tiles >= cus && (tiles + 7) / 8 * (cus / tiles) > cus / 8;
+  if (kc && slabs(1) >= 128) {
+    if (m <= 16) {
+      // (at most four rows from k = 4096 on: narrow slabs, two workgroups to a compute unit, come
+      // near wide ones and pass them at k = 8192: (1, 11008, 4096) 11.7 / 9.4 and 11.1 / 9.1,
+      // (1, 11008, 8192) 17.8 / 14.9 and 19.4 / 15.1)
+      if (!adds_in_place) return m <= 4 && width == 4 && one_round && k >= 4096 ? 1 : width;
+      if (width == 4 && (one_round || k <= 3072 || 3 * slabs(4) >= 4 * cus || crowded)) return 4;
+    } else if (m <= 32) {
+      if (width < 4) {
+        if (one_round && !adds_in_place && (p.out_float || slabs(1) >= 192 || k <= 8192)) return width;
+      } else if (one_round) {
+        if (k >= 2048 && (slabs(4) <= 240 || k < 2560 || k >= 5120)) return 4;
+      } else if (k >= 8192 && 10 * slabs(4) >= 9 * ((slabs(4) + cus - 1) / cus * cus)) {
+        return 4;  // (the rounds nearly full: (24, 32000, 8192) 0.94 of the tiles' time, (24, 22016, 8192) 1.07)
+      }
+    } else if (width < 4 && one_round && !adds_in_place && (p.packed_weights || p.out_float) && k >= 2048 &&
+               k <= 8192) {
+      // (above 32 rows for a float output, which the tiles combine through slots, and for packed weights)
+      if (width == 1 && (p.out_float || slabs(1) >= 192 || k <= 5120)) return 1;
+      if (width == 2 && (p.packed_weights || slabs(2) >= 164 || k <= 3072)) return 2;
     }
-  } else {
-    if (width == 4 && p.n * p.k <= ((int64_t)64 << 20) && (p.m <= 16 || (p.m <= 32 && p.k >= 2048 && !adds_in_place)))
-      return 4;
-    if (adds_in_place) return 0;
-    if (width == 2 && p.k <= 2048 && p.m <= 32) return 2;
-    // (a float output splits k through slots, which cost it more than atomics do an int32 one:
-    // (1, 4096, 4096) 9.6 / 10.2 / 10.5 against 12.2, (16, 4096, 4096) 10.1 against 11.8)
-    if (p.out_float && p.m <= 16 && p.n / 16 >= 192 && p.k <= 4096) return width;
   }
+  if (!kc && one_round) {
+    if (width == 4) {
+      const bool spread = p.b_sk % 512 != 0;  // the leading dimension
+      bool pays;
+      if (m > 16) pays = m <= 32 && !into_int32 && spread && slabs(4) >= 160 && slabs(4) <= 224 && k >= 3072;
+      else if (into_int32) pays = k < 1024 || crowded;
+      else if (p.out_float) pays = p.b_sk % 2048 != 0 || slabs(4) >= 192 || k <= 3072;
+      else pays = crowded ||
+                  k <= (spread ? 4096 : (slabs(4) >= 180 || p.b_sk % 2048 ? 2560 : 1024));
+      if (pays && n * k <= ((int64_t)64 << 20)) return 4;
+    } else if (!adds_in_place) {
+      if (width == 2 && m <= 32 && k <= 2048) return 2;
+      // (a float output splits k through slots, which cost it more than atomics do an int32 one:
+      // (16, 4096, 4096) 13.4 / 8.1 against 14.4 / 10.8)
+      if (p.out_float && m <= 16 && slabs(1) >= 192 && k <= 4096) return width;
+    }
+  }
+  if (adds_in_place) return 0;
   // Short k, where the tiles, too few to fill the chip, would have to split it (up to 4096 at
   // m <= 16, 2048 at 32, 1024 at 64; row-major only to 2048: cold it loses beyond), and a float
   // output without a workspace, which tiles cannot split at all.  Measured, us warm/cold:
   // (1, 1024, 2048) 4.9/5.6 -> 3.6/4.5, (16, 2048, 2048) 5.3/6.1 -> 4.5/5.5,
   // (64, 4096, 1024) 6.3/7.2 -> 5.1/5.7; float (16, 2048, 8192) 17.8/29.2 -> 9.7/11.2.
-  const bool short_k = p.k * (p.m > 16 ? p.m : 16) <= 65536 && (kc || p.k <= 2048);
-  if ((short_k || (p.out_float && !p.ws)) && tile_count(p, SHAPE_64) < compute_units() / 2 && p.n / 16 >= 64) return 1;
+  const bool short_k = k * (m > 16 ? m : 16) <= 65536 && (kc || k <= 2048);
+  if ((short_k || (p.out_float && !p.ws)) && tile_count(p, SHAPE_64) < cus / 2 && slabs(1) >= 64) return width;
   return 0;
 }
 
@@ -320,13 +350,14 @@ Plan choose_plan(const Problem &p) {
     // 18.9 -> 15.3, (64, 4096, 11008) 21.5 -> 18.9; warm within 0.5 us either way; at
     // (64, 4096, 4096) the 64 x 64 tiles stay ahead, 11.6 against 12.7.  A k-contiguous B has no
     // lines to complete: (64, 11008, 4096) 13.3/19.2 us warm/cold on 64 x 64, 16.2/20.8 on 64 x 128.
-    // A float output needs enough of them, its ranges of k meeting in slots: (32, 4096, 11008), 32
-    // tiles, 19.0 us against 14.0 on 64 x 64.)
+    // A float output needs enough of them, its ranges of k meeting in slots, cold / warm: (32, 4096, 8192),
+    // 32 tiles, 20 / 16.9 us against 17.1 / 11.9 on 64 x 64, (48, 5120, 8192) 21.8 / 17.0 and 21.9 / 14.8; but
+    // (32, 6144, 8192), 48 tiles, 21.1 / 16.3 against 24.2 / 16.2.)
     if (p.m <= 64 && p.n > 128)
       sh = p.k >= 512 && enough(SHAPE_64X256, p.m)
                ? SHAPE_64X256
                : (p.m >= 32 && p.k >= 512 && p.b_sn == 1 && p.n * p.k >= ((int64_t)32 << 20) &&
-                          (!p.out_float || tile_count(p, SHAPE_64X128) >= 64) && dma_eligible(p, SHAPE_64X128)
+                          (!p.out_float || tile_count(p, SHAPE_64X128) >= 44) && dma_eligible(p, SHAPE_64X128)
                       ? SHAPE_64X128
                       : SHAPE_64);
     else if (p.n <= 64 && p.m > 128) sh = p.k >= 512 && enough(SHAPE_256X64, p.n) ? SHAPE_256X64 : SHAPE_64;

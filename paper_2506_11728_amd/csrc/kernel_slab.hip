@@ -33,11 +33,24 @@ namespace mip {
 
 namespace {
 
-// Waves of a workgroup, and steps of B and of A in flight per wave: what 160 KB of LDS hold.
-constexpr int slab_waves(int mt, int nt) { return (mt >= 4 && nt >= 2) || (mt == 2 && nt == 4) ? 4 : 8; }
-constexpr int steps_of_a(int mt, int nt) { return mt >= 4 ? (nt == 2 ? 3 : 2) : (nt == 1 ? (mt == 1 ? 4 : 3) : 2); }
-constexpr int steps_of_b(int mt, int nt) {
-  return mt >= 4 ? (nt == 1 ? 2 : 3) : (nt >= 4 ? (mt == 2 ? 3 : 2) : (nt == 2 ? (mt == 2 ? 3 : 4) : (mt == 1 ? 6 : 4)));
+// Rings of a workgroup.  DEEP: eight waves (four where A or the slab is wide), together all of a
+// compute unit's 160 KB of LDS.  HALF: eight waves and half of it, for more narrow slabs than there are
+// compute units.  FEW: four waves, two or three workgroups to a compute unit, for more slabs than that
+// with little k, where most of eight waves would have no step, or 64 columns wide.  (1, 32000, 768) on
+// 64 columns 8.7 / 5.2 us cold / warm deep, 7.1 / 4.1 few; (4, 15472, 11008) on 16 columns 35.7 / 26.8
+// half, 40.9 / 28.2 few.
+enum Rings { DEEP, HALF, FEW };
+constexpr int slab_waves(int mt, int nt, Rings rings) {
+  return rings == FEW || (mt >= 4 && nt >= 2) || (mt == 2 && nt == 4) ? 4 : 8;
+}
+// steps of A and of B in flight per wave
+constexpr int steps_of_a(int mt, int nt, Rings rings) {
+  return rings != DEEP ? 2 : mt >= 4 ? (nt == 2 ? 3 : 2) : (nt == 1 ? (mt == 1 ? 4 : 3) : 2);
+}
+constexpr int steps_of_b(int mt, int nt, Rings rings) {
+  return rings != DEEP ? (nt >= 4 ? 2 : (rings == FEW && mt == 1 ? 4 : 3))
+         : mt >= 4     ? (nt == 1 ? 2 : 3)
+                       : (nt >= 4 ? (mt == 2 ? 3 : 2) : (nt == 2 ? (mt == 2 ? 3 : 4) : (mt == 1 ? 6 : 4)));
 }
 
 struct SlabParams {
@@ -73,12 +86,11 @@ __device__ __forceinline__ int kc_chunk(int q, int lane) { return (lane & 7) ^ (
 
 // MT: row blocks of 16 (m <= 16 * MT).  NT: column blocks of 16 per workgroup.
 // B_KC: B stored with k contiguous (column-major).  UNS: 0 both signed, 1 A
-// unsigned, 2 B unsigned.  SHALLOW: rings of half the depth, so that two workgroups fit a compute
-// unit: for more narrow slabs than there are compute units.
-template <int MT, int NT, bool B_KC, int UNS, bool SHALLOW>
-__global__ __launch_bounds__(64 * slab_waves(MT, NT)) void slab_kernel(SlabParams P) {
+// unsigned, 2 B unsigned.
+template <int MT, int NT, bool B_KC, int UNS, Rings RINGS>
+__global__ __launch_bounds__(64 * slab_waves(MT, NT, RINGS)) void slab_kernel(SlabParams P) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  constexpr int W = slab_waves(MT, NT), DA = SHALLOW ? 2 : steps_of_a(MT, NT), DB = SHALLOW ? 3 : steps_of_b(MT, NT);
+  constexpr int W = slab_waves(MT, NT, RINGS), DA = steps_of_a(MT, NT, RINGS), DB = steps_of_b(MT, NT, RINGS);
   static_assert(DB >= DA, "the waits below");
   constexpr int NB = 2 * NT, NA = 2 * MT;           // direct loads of a step
   constexpr int B_STEP = NB * 1024, A_STEP = NA * 1024;  // its bytes
@@ -299,12 +311,12 @@ __global__ __launch_bounds__(64 * slab_waves(MT, NT)) void slab_kernel(SlabParam
   }
 }
 
-template <int MT, int NT, bool SHALLOW = false>
+template <int MT, int NT, Rings RINGS = DEEP>
 void (*pick(bool b_kc, int uns))(SlabParams) {
-  if (b_kc) return uns == 0 ? slab_kernel<MT, NT, true, 0, SHALLOW>
-                            : (uns == 1 ? slab_kernel<MT, NT, true, 1, SHALLOW> : slab_kernel<MT, NT, true, 2, SHALLOW>);
-  return uns == 0 ? slab_kernel<MT, NT, false, 0, SHALLOW>
-                  : (uns == 1 ? slab_kernel<MT, NT, false, 1, SHALLOW> : slab_kernel<MT, NT, false, 2, SHALLOW>);
+  if (b_kc) return uns == 0 ? slab_kernel<MT, NT, true, 0, RINGS>
+                            : (uns == 1 ? slab_kernel<MT, NT, true, 1, RINGS> : slab_kernel<MT, NT, true, 2, RINGS>);
+  return uns == 0 ? slab_kernel<MT, NT, false, 0, RINGS>
+                  : (uns == 1 ? slab_kernel<MT, NT, false, 1, RINGS> : slab_kernel<MT, NT, false, 2, RINGS>);
 }
 
 }  // namespace
@@ -342,19 +354,23 @@ hipError_t launch_slab(const Problem &p, int nt, hipStream_t s) {
   const int uns = p.a_unsigned ? 1 : (p.b_unsigned ? 2 : 0);
   const int mt = p.m <= 16 ? 1 : (p.m <= 32 ? 2 : 4);
   void (*kern)(SlabParams) = nullptr;
-  const bool shallow = nt == 1 && mt == 1 && P.tiles > compute_units();
-  if (shallow) kern = pick<1, 1, true>(b_kc, uns);
+  const bool many = P.tiles > compute_units(), few_steps = P.nsteps <= 4;
+  Rings rings = DEEP;
+  if (nt == 1 && mt == 1) rings = few_steps || (many && P.nsteps < 16) ? FEW : (many ? HALF : DEEP);
+  else if ((nt == 4 && mt == 1) || (nt == 1 && mt == 2)) rings = many || few_steps ? FEW : DEEP;
+  if (rings == HALF) kern = pick<1, 1, HALF>(b_kc, uns);
+  else if (rings == FEW) kern = nt == 4 ? pick<1, 4, FEW>(b_kc, uns) : (mt == 1 ? pick<1, 1, FEW>(b_kc, uns) : pick<2, 1, FEW>(b_kc, uns));
   else if (nt == 1) kern = mt == 1 ? pick<1, 1>(b_kc, uns) : (mt == 2 ? pick<2, 1>(b_kc, uns) : pick<4, 1>(b_kc, uns));
   else if (nt == 2) kern = mt == 1 ? pick<1, 2>(b_kc, uns) : (mt == 2 ? pick<2, 2>(b_kc, uns) : pick<4, 2>(b_kc, uns));
   else kern = mt == 1 ? pick<1, 4>(b_kc, uns) : (mt == 2 ? pick<2, 4>(b_kc, uns) : pick<4, 4>(b_kc, uns));
-  const size_t lds = (size_t)slab_waves(mt, nt) * 2048 *
-                     (shallow ? 5 : steps_of_b(mt, nt) * nt + steps_of_a(mt, nt) * mt);
+  const int waves = slab_waves(mt, nt, rings);
+  const size_t lds = (size_t)waves * 2048 * (steps_of_b(mt, nt, rings) * nt + steps_of_a(mt, nt, rings) * mt);
   {
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds);
     if (e != hipSuccess) return e;
   }
   dim3 grid((unsigned)(((P.tiles + 7) / 8) * 8));
-  hipLaunchKernelGGL(kern, grid, dim3(64 * slab_waves(mt, nt)), lds, s, P);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * waves), lds, s, P);
   return hipGetLastError();
 }
 

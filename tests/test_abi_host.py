@@ -317,3 +317,19 @@ def test_both_ways_of_converting_arguments_agree(monkeypatch):
     assert native == [getattr(M, f)(*a, **k) for f, a, k in calls]
     assert all(rc < 0 for rc in native)
     assert kinds == [raised(*c) for c in odd]
+
+
+# (m, n, k, order of B, mode, kernel): either side of the rules of the skinny kernel, where slabs were
+# measured slower than tiles, or slabs of another width slower than these
+@pytest.mark.parametrize("m,n,k,order,mode,name", [
+    (1, 10240, 5120, 0, 1, "tiles"), (16, 12288, 4096, 0, 1, "tiles"),
+    (8, 10240, 4096, 0, 0, "tiles"), (8, 10240, 1024, 0, 0, "mfma_slab64"),
+    (16, 12352, 4096, 0, 0, "mfma_slab64"), (24, 22016, 2048, 0, 0, "tiles"),
+    (16, 6144, 2048, 0, 0, "mfma_slab32"), (16, 6144, 3072, 0, 0, "tiles"),
+    (24, 22016, 3072, 1, 0, "tiles"), (32, 16384, 3072, 1, 0, "tiles"), (32, 16384, 8192, 1, 0, "mfma_slab64"),
+    (17, 31984, 576, 1, 0, "tiles"), (24, 6144, 768, 1, 0, "mfma_slab32"), (32, 2048, 11008, 1, 0, "tiles"),
+    (1, 12288, 768, 1, 0, "mfma_slab64"), (16, 8192, 4096, 1, 0, "mfma_slab32"), (16, 4608, 4096, 1, 0, "mfma_slab32"),
+    (16, 4096, 4096, 1, 0, "mfma_slab16"), (8, 18272, 320, 1, 0, "mfma_slab16"), (16, 16448, 8192, 1, 1, "tiles")])
+def test_which_skinny_products_take_slabs(M, m, n, k, order, mode, name):
+    chosen = M.mipgemm_variant_name_for_mode(m, n, k, k, 0, n if order == 0 else k, order, n, 0, mode=mode)
+    assert chosen == name if name != "tiles" else chosen.startswith("mfma_dma"), chosen

@@ -603,6 +603,17 @@ def test_more_narrow_slabs_than_compute_units(gpu, oracle, k):
                                        a_unsigned=i == 0, seed=91), "slab16")
 
 
+@pytest.mark.parametrize("variant,m,n,k", [("slab16", 20, 16 * 260, 64), ("slab16", 32, 16 * 257, 1088), ("slab16", 17, 96, 512),
+                                           ("slab64", 9, 64 * 257, 128), ("slab64", 16, 64 * 259, 1600), ("slab64", 1, 192, 448),
+                                           ("slab16", 16, 16 * 257, 2048)])
+def test_slabs_with_four_waves_and_with_half_the_rings(gpu, oracle, variant, m, n, k):
+    """More slabs than compute units, and fewer steps than eight waves: one step and more than the rings hold."""
+    for i, (uns, order) in enumerate(((0, W.COL_MAJOR), (1, W.ROW_MAJOR), (2, W.COL_MAJOR))):
+        check_case(gpu, oracle, W.Case("slab_few_%s_%d_%d_%d_%d" % (variant, m, n, k, i), 8, 970 + i, m, n, k,
+                                       a_unsigned=uns == 1, b_unsigned=uns == 2, orderB=order,
+                                       mode=(W.OVERWRITE, W.ACCUMULATE)[i % 2], seed=92), variant)
+
+
 def test_skinny_m_slab_kernel_wraps(gpu, oracle):
     """All(-128) x all(-128) over k = 2^17: every sum is 2^31, which wraps to -2^31."""
     m, n, k = 4, 32, 1 << 17
