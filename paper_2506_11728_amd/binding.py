@@ -11,6 +11,7 @@ There is no fallback: if the shared library has not been built
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 import threading
 
@@ -159,14 +160,11 @@ def load_library() -> ctypes.CDLL:
 
 
 # ---- calls ----
-# The entry points that run on the device go through _call.so (native/call.c), which converts the
+# The entry points that run on the device go through the module _call (native/call.c), which converts the
 # arguments in C.  What it does not take (returning None), and everything where it has not been built, goes
 # through ctypes below.
 
-try:
-    from . import _call as _native
-except ImportError:  # no Python headers where the library was built
-    _native = None
+_native = None  # the module, once the library is loaded
 
 _GEMM_FORMAT, _CONV_FORMAT = "qqqpqipqipqiipzs", "qqqqqqqqqpppipzs"
 _BATCHED_FORMAT, _PACKED_FORMAT = "qqqpqiqpqiqpqiqqipzs", "qqqpqippqiipzs"
@@ -182,9 +180,15 @@ _FORMATS = {
 
 
 def _register_native(lib):
-    if _native is not None:
-        for name, fmt in _FORMATS.items():
-            _native.register(name, fmt, ctypes.cast(getattr(lib, name), ctypes.c_void_p).value)
+    global _native
+    importlib.invalidate_caches()  # it may have been built since this package was imported
+    try:
+        from . import _call
+    except ImportError:  # no Python headers or no C compiler where the library was built
+        return
+    for name, fmt in _FORMATS.items():
+        _call.register(name, fmt, ctypes.cast(getattr(lib, name), ctypes.c_void_p).value)
+    _native = _call
 
 
 def _run(check, name, *args):

@@ -61,24 +61,33 @@ def build_library(verbose: bool = False, jobs: int = 0) -> str:
     return LIB
 
 
-def build_binding(verbose: bool = False) -> None:
-    """The binding's argument conversion (native/call.c); without Python's headers it stays with ctypes."""
+def build_binding(verbose: bool = False) -> bool:
+    """The binding's argument conversion (native/call.c), for this interpreter; without Python's headers or a
+    C compiler the binding converts its arguments through ctypes."""
+    for old in glob.glob(os.path.join(HERE, "_call*.so")):
+        os.remove(old)
     include = sysconfig.get_paths()["include"]
     if not os.path.exists(os.path.join(include, "Python.h")):
         print("no Python.h in %s: the binding converts its arguments through ctypes" % include, flush=True)
-        return
-    out = os.path.join(HERE, "_call.so")
+        return False
+    out = os.path.join(HERE, "_call" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
     tmp = out + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I" + include,
            os.path.join(HERE, "native", "call.c"), "-o", tmp]
-    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if proc.returncode != 0:
+    try:
+        proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        failed = proc.stdout if proc.returncode != 0 else None
+    except OSError as e:
+        failed = str(e)
+    if failed is not None:
         if os.path.exists(tmp):
             os.remove(tmp)
-        raise RuntimeError("the binding's call.c failed:\n" + proc.stdout)
+        print("native/call.c did not compile, the binding converts its arguments through ctypes:\n" + failed, flush=True)
+        return False
     os.replace(tmp, out)
     if verbose:
         print("compiled native/call.c", flush=True)
+    return True
 
 
 if __name__ == "__main__":

@@ -319,6 +319,36 @@ def test_both_ways_of_converting_arguments_agree(monkeypatch):
     assert kinds == [raised(*c) for c in odd]
 
 
+@pytest.mark.parametrize("compiler", ["no-such-compiler", "false"])
+def test_a_build_without_a_c_compiler_leaves_the_binding_to_ctypes(monkeypatch, tmp_path, compiler):
+    from paper_2506_11728_amd import build
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setenv("CC", compiler)
+    (tmp_path / "_call.so").write_bytes(b"of an older build")
+    assert build.build_binding() is False
+    assert not list(tmp_path.iterdir())
+
+
+def test_binding_built_after_the_package_was_imported(tmp_path):
+    """The module carries this interpreter's tag, and a process that imports first and builds then uses it."""
+    import shutil
+    import subprocess
+    import sys
+    import sysconfig
+    from paper_2506_11728_amd import build
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")) or not shutil.which("gcc"):
+        pytest.skip("nothing to build it with")
+    package = tmp_path / "paper_2506_11728_amd"
+    shutil.copytree(build.HERE, package, ignore=shutil.ignore_patterns("_call*", "_build", "csrc", "__pycache__"))
+    code = ("import paper_2506_11728_amd.binding as b, paper_2506_11728_amd.build as build\n"
+            "assert b._native is None and build.build_binding()\n"
+            "b.load_library()\n"
+            "print(b._native.__file__)\n")
+    out = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+    assert out.stdout.strip().endswith("_call" + sysconfig.get_config_var("EXT_SUFFIX"))
+
+
 # (m, n, k, order of B, mode, kernel): either side of the rules of the skinny kernel, where slabs were
 # measured slower than tiles, or slabs of another width slower than these
 @pytest.mark.parametrize("m,n,k,order,mode,name", [
