@@ -183,7 +183,8 @@ static int64_t tile_count(const Problem &p, Shape s) {
 }
 
 size_t splitk_slot_bytes(const Problem &p, const Plan &plan) {
-  if (plan.kind != KIND_DMA || plan.splits < 2 || !p.out_float) return 0;  // (int32 outputs add into C)
+  // (int32 outputs add into C, and 256 x 256 tiles have no slots)
+  if (plan.kind != KIND_DMA || plan.shape == SHAPE_256 || plan.splits < 2 || !p.out_float) return 0;
   const int64_t bm = kShapeRows[plan.shape], bn = kShapeCols[plan.shape];
   const int64_t tiles = ((p.m + bm - 1) / bm) * ((p.n + bn - 1) / bn) * (p.batch > 1 ? p.batch : 1);
   const double bytes = (double)tiles * ((double)plan.splits * (double)(bm * bn * 4) + sizeof(unsigned));

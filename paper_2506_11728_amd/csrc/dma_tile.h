@@ -313,13 +313,17 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(DmaTileParams P) {
     }
   }
   unsigned_correction<FM, FN>(acc, sumA, sumB, FLIP_A, FLIP_B, lane);
-  if (P.slots) {  // only the workgroup that draws the tile's last ticket writes C
-    const int64_t tile = ((int64_t)blockIdx.z * P.tiles_m + tm) * P.tiles_n + tn;
-    if (!combine_k_ranges<FM, FN>(acc, P.slots + tile * P.splits * (int64_t)(BM * BN), blockIdx.y,
-                                  P.splits, P.tickets + tile, wave, lane, tid,
-                                  reinterpret_cast<int *>(smem)))
-      return;
-    __syncthreads();  // the word of LDS the ticket went through is patch memory below
+  // (not on 256 x 256 tiles, of which there are never too few: the exchange of their 256 accumulators
+  // spills registers that the rest of the kernel pays for)
+  if constexpr (BM * BN < 256 * 256) {
+    if (P.slots) {  // only the workgroup that draws the tile's last ticket writes C
+      const int64_t tile = ((int64_t)blockIdx.z * P.tiles_m + tm) * P.tiles_n + tn;
+      if (!combine_k_ranges<FM, FN>(acc, P.slots + tile * P.splits * (int64_t)(BM * BN), blockIdx.y,
+                                    P.splits, P.tickets + tile, wave, lane, tid,
+                                    reinterpret_cast<int *>(smem)))
+        return;
+      __syncthreads();  // the word of LDS the ticket went through is patch memory below
+    }
   }
   const int64_t mw = m0 + wm * (BM / 2), nw = n0 + wn * (BN / 2);  // the wave's sub-tile
   if (mw < P.m && nw < P.n) {
@@ -404,7 +408,7 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   // large, 2048^3 in two ranges 22 against 40 us, but there no split wins at all, 15 us;
   // where splitting pays C is small and the atomics are cheaper, (16, 4096, 4096) in four
   // ranges 8.3 against 9.1 us, (512, 512, 4096) 10.5 against 17 us.)
-  if (splits > 1 && p.out_float && p.ws &&
+  if (splits > 1 && p.out_float && p.ws && BM * BN < 256 * 256 &&
       p.ws_bytes / ((size_t)BM * BN * 4) / (size_t)splits >= (size_t)all_tiles) {
     const size_t bytes = (size_t)all_tiles * (size_t)splits * ((size_t)BM * BN * 4);
     const bool counters_fit = (p.ws_bytes - bytes) / sizeof(unsigned) >= (size_t)all_tiles;
