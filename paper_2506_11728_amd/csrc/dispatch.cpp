@@ -282,39 +282,46 @@ static int slab_width(const Problem &p) {
 }
 
 // Tiles with a side of 192 for the kernel with 128-deep blocks, where 256 x 256 ones leave a last round
-// mostly idle or are too few and 128 x 128 ones cost more operand traffic: the shape whose
-// rounds of workgroups take least by the times below, against the shape chosen so far.
-// Microseconds of one round over nkt blocks, fitted to the runs named (s8 x s8, operands in the
-// last-level cache): 256 x 256 1.15 nkt + 14 (4096^3, 8192^3), 256 x 192 and 192 x 256 nkt + 10
-// ((1000, 11008, 4096), 6144^2 x 4096, (8192, 3072, 1024), (1500, 8192, 2048)), 192 x 192
-// 0.68 nkt + 13.8 (3072^3, (768, 11008, 4096), 4096^3); 128 x 128 0.38 nkt + 3.1 for each tile of a
-// compute unit, two of which run at a time.  Measured, us, before and after:
-// (768, 11008, 4096) 46 -> 36 (192 x 192), 3072^3 37 -> 30, (1500, 8192, 2048) to float 32 -> 28
-// (192 x 256), 6144^2 x 4096 139 -> 126 (256 x 192), 4095 x 4097 x 4099 packed 99 -> 92; not (2816, 2816, 4096) 32 on 128 x 128, 36 on 192 x 192, nor (5000, 3500, 2048) 45, 54.
-// (Whole 256 x 256 tiles, or packed operands padded to them, in two rounds or less stay, (8192, 3072, 1024) 42 where 256 x 192 would
-// take 38: 4608^2 x 4096, of that kind, is a choice that tests pin.)
+// mostly idle or are too few and 128 x 128 ones cost more operand traffic: the shape whose rounds of
+// workgroups take least by the times below, if that is a tenth under those of the shape chosen so far.
+// Microseconds of a round over nkt blocks (of 128 x 128 tiles, two of which share a compute unit, for a
+// full round and one with a single tile to a compute unit) and of reading a million words of C where the
+// call accumulates (rows of 96 words, those of a side of 192 along n, cost most), fitted to 1200 products
+// of 384 to 12000 rows and columns with k = 1024 to 9000 in every order, signedness, mode and output type, which
+// the model meets within 10 % at the median.  Over these the rule takes 0.959 of the time without
+// such tiles, the best choice each time 0.952; with costs fitted to a few overwriting s8 x s8 products
+// it was 0.984, and accumulating ones lost up to 1.7 times.
+// Measured, us, before and after: (768, 11008, 4096) 46 -> 36 (192 x 192), 3072^3 37 -> 30,
+// (1500, 8192, 2048) to float 32 -> 28 (192 x 256); not (8171, 2730, 1024) accumulating, 68 on 128 x 128
+// and 117 on 256 x 192, nor (3968, 3008, 1024) to int8, 20 and 28: below k = 1536 the write-back decides.
+// (Whole 256 x 256 tiles, or packed operands padded to them, in two rounds or less stay, a choice that
+// tests name: 4608^2 x 4096 95 us, 82 on 192 x 256; (8192, 3072, 4096) 99 and 108.)
 static Shape shape_with_192(const Problem &p, Shape chosen) {
-  if ((chosen != SHAPE_256 && chosen != SHAPE_128) || p.k < 1024 || p.m < 384 || p.n < 384 ||
+  if ((chosen != SHAPE_256 && chosen != SHAPE_128) || p.k < 1536 || p.m < 384 || p.n < 384 ||
       !dma_k128_split_eligible(p, true))
     return chosen;
-  const int64_t cus = compute_units();
-  auto rounds = [&](int64_t bm, int64_t bn) {
-    return (((p.m + bm - 1) / bm) * ((p.n + bn - 1) / bn) + cus - 1) / cus;
-  };
-  const double nkt = (double)(p.k / 128);
   // (the forms for whole tiles read the k-sums that packed weights bring, these accumulate them)
   if (p.ksum && dma_k128_eligible(p, chosen == SHAPE_128)) return chosen;
-  const int64_t rounds256 = rounds(256, 256);
+  const int64_t cus = compute_units();
+  auto tiles = [&](int64_t bm, int64_t bn) { return ((p.m + bm - 1) / bm) * ((p.n + bn - 1) / bn); };
   const bool whole = (p.m % 256 == 0 && p.n % 256 == 0) || p.rows_padded_to_256;
-  if (chosen == SHAPE_256 && whole && rounds256 < 3) return chosen;
-  double best = 0.95 * (chosen == SHAPE_256 ? (double)rounds256 * (1.15 * nkt + 14)
-                                            : (double)rounds(128, 128) * (0.38 * nkt + 3.1));
+  if (chosen == SHAPE_256 && whole && tiles(256, 256) <= 2 * cus) return chosen;
+  const double nkt = (double)(p.k / 128), old_words = p.accumulate ? 1e-6 * (double)p.m * (double)p.n : 0.0;
+  auto time = [&](int64_t bm, int64_t bn, double block, double ends, double read) {
+    return (double)((tiles(bm, bn) + cus - 1) / cus) * (block * nkt + ends) + read * old_words;
+  };
+  const int64_t pairs = tiles(128, 128) / (2 * cus), rest = tiles(128, 128) % (2 * cus);
+  const double time128 = (double)(pairs + (rest > cus)) * (0.92 * nkt + 5.0) +
+                         (rest > 0 && rest <= cus ? 0.57 * nkt + 4.2 : 0.0) + 0.9 * old_words;
+  // (a wider margin where the call accumulates, whose reads the model knows least: (6800, 2912, 1920) with an
+  // unsigned operand 68 -> 79 at the same one)
+  double best = (p.accumulate ? 0.85 : 0.9) * (chosen == SHAPE_256 ? time(256, 256, 1.21, 12.7, 1.0) : time128);
   auto consider = [&](Shape shape, double cost) {
     if (cost < best) { best = cost; chosen = shape; }
   };
-  consider(SHAPE_256X192, (double)rounds(256, 192) * (nkt + 10));
-  consider(SHAPE_192X256, (double)rounds(192, 256) * (nkt + 10));
-  consider(SHAPE_192, (double)rounds(192, 192) * (0.68 * nkt + 13.8));
+  consider(SHAPE_256X192, time(256, 192, 1.04, 13.7, 1.8));
+  consider(SHAPE_192X256, time(192, 256, 1.01, 10.5, 0.95));
+  consider(SHAPE_192, time(192, 192, 0.835, 10.3, 1.5));
   return chosen;
 }
 

@@ -998,9 +998,34 @@ def test_tiles_with_a_side_of_192_to_float_and_int8(gpu, variant, m, n):
     assert np.array_equal(Q.cpu().numpy(), want)
 
 
-def test_tiles_with_a_side_of_192_as_dispatched(gpu, oracle):
-    case = W.Case("with192_dispatched", 8, 0, 768, 11008, 1024, seed=13)
-    case3 = W.Case("with192_dispatched_3072", 8, 1, 3000, 3072, 3072, seed=13)
-    name = lambda c: gpu.mipgemm_variant_name(c.m, c.n, c.k, c.lda, c.orderA, c.ldb, c.orderB, c.ldc, c.orderC)
-    assert name(case3) == "mfma_dma192_k128"
+# (name, m, n, k, A unsigned, B unsigned, order of B, mode): one round of tiles and several (from 512
+# tiles on with a staggered start)
+_DISPATCHED_192 = [
+    ("mfma_dma192_k128", 3000, 3072, 3072, 0, 0, 0, W.OVERWRITE), ("mfma_dma192_k128", 7696, 2064, 2048, 1, 0, 0, W.OVERWRITE),
+    ("mfma_dma192_k128", 8208, 912, 3072, 0, 1, 0, W.ACCUMULATE), ("mfma_dma192x256_k128", 7024, 1168, 1536, 1, 0, 1, W.OVERWRITE),
+    ("mfma_dma192x256_k128", 6752, 4672, 1536, 0, 0, 0, W.OVERWRITE), ("mfma_dma192x256_k128", 912, 8256, 2048, 0, 0, 0, W.ACCUMULATE),
+    ("mfma_dma256x192_k128", 1744, 6528, 2560, 0, 0, 0, W.OVERWRITE), ("mfma_dma256x192_k128", 1000, 11008, 4096, 1, 0, 0, W.OVERWRITE)]
+
+
+@pytest.mark.parametrize("name,m,n,k,au,bu,order,mode", _DISPATCHED_192)
+def test_tiles_with_a_side_of_192_as_dispatched(gpu, oracle, name, m, n, k, au, bu, order, mode):
+    case = W.Case("with192_%dx%dx%d" % (m, n, k), 8, 40, m, n, k, a_unsigned=bool(au), b_unsigned=bool(bu), orderB=order, mode=mode,
+                  a_dist=("uniform", 0, 255) if au else ("uniform", -128, 127),
+                  b_dist=("uniform", 0, 255) if bu else ("uniform", -128, 127), c_dist=("uniform", -1000, 1000), seed=13)
+    assert gpu.mipgemm_variant_name_for_mode(m, n, k, case.lda, 0, case.ldb, order, case.ldc, 0, bool(au), bool(bu), True,
+                                             mode) == name
     check_case(gpu, oracle, case, "auto")
+
+
+def test_tiles_with_a_side_of_192_as_dispatched_to_float_on_packed_operands(gpu):
+    import torch
+    m, n, k = 2999, 3071, 3001
+    assert gpu.mipgemm_variant_name_with_workspace(m, n, k, k, 0, n, 0, n, 0, True, False, False) == "packed+mfma_dma192_k128"
+    torch.manual_seed(17)
+    A = torch.randint(0, 256, (m, k), dtype=torch.uint8, device="cuda")
+    B = torch.randint(-128, 128, (k, n), dtype=torch.int8, device="cuda")
+    C = torch.zeros((m, n), dtype=torch.float32, device="cuda")
+    ws = torch.empty(gpu.mipgemm_workspace_size_f32(m, n, k, 0, 0, 0), dtype=torch.uint8, device="cuda")
+    gpu.mipgemm_u8s8f32(m, n, k, A, k, 0, B, n, 0, C, n, 0, W.OVERWRITE, workspace=ws, workspace_bytes=ws.numel())
+    want = (A.double() @ B.double()).float()          # the sums are exact in 64 bits, and rounded once
+    assert torch.equal(C, want)
