@@ -483,49 +483,53 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
 
 // Operands that cannot be fetched 16 bytes at a time, rewritten k-contiguous: row r of P (pitch
 // kp elements, a multiple of 64) holds the k elements of row r of X, then zeros.  Both operands
-// in one launch; 64 rows x 64 k per workgroup, turned through LDS where X is strided.
+// in one launch; 64 rows x 64 k at a time per workgroup, turned through LDS where X is strided.
 struct Pack16Job {
   const int16_t *X;
   int64_t s_r, s_k, rows;
   int16_t *P;
-  int64_t blocks;  // workgroups of this job
+  int64_t blocks;  // of 64 x 64 in this job
 };
+constexpr int64_t PACK_GRID = 1 << 22;  // workgroups at most: x 256 threads stays below 2^32
 
 __global__ __launch_bounds__(256) void pack16_kernel(Pack16Job a, Pack16Job b, int64_t k, int64_t kp) {
   __shared__ short tile[64][66];
-  const bool first = (int64_t)blockIdx.x < a.blocks;
-  const Pack16Job J = first ? a : b;
-  const int64_t id = first ? blockIdx.x : blockIdx.x - a.blocks;
-  const int64_t kts = kp / KB;
-  const int64_t r0 = id / kts * 64, p0 = id % kts * KB;
   const int tid = threadIdx.x;
-  if (J.s_k != 1) {
-    const int64_t r = r0 + (tid & 63);
-#pragma unroll
-    for (int e = 0; e < KB / 4; ++e) {
-      const int q = 4 * e + (tid >> 6);
-      tile[q][tid & 63] = r < J.rows && p0 + q < k ? J.X[r * J.s_r + (p0 + q) * J.s_k] : (short)0;
-    }
-    __syncthreads();
-  }
-  // eight k of one row per thread, twice: eight threads write the 128 bytes of a row
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int64_t row = r0 + h * 32 + (tid >> 3), p = p0 + 8 * (tid & 7);
-    if (row >= J.rows) continue;
-    union { short e[8]; v4i v; } out;
+  for (int64_t block = blockIdx.x; block < a.blocks + b.blocks; block += gridDim.x) {
+    const bool first = block < a.blocks;
+    const Pack16Job J = first ? a : b;
+    const int64_t id = first ? block : block - a.blocks;
+    const int64_t kts = kp / KB;
+    const int64_t r0 = id / kts * 64, p0 = id % kts * KB;
     if (J.s_k != 1) {
+      const int64_t r = r0 + (tid & 63);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) out.e[e] = tile[8 * (tid & 7) + e][h * 32 + (tid >> 3)];
-    } else if (p + 8 <= k) {
-      const s16x8 x = *reinterpret_cast<const s16x8 *>(J.X + row * J.s_r + p);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) out.e[e] = x.v[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) out.e[e] = p + e < k ? J.X[row * J.s_r + p + e] : (short)0;
+      for (int e = 0; e < KB / 4; ++e) {
+        const int q = 4 * e + (tid >> 6);
+        tile[q][tid & 63] = r < J.rows && p0 + q < k ? J.X[r * J.s_r + (p0 + q) * J.s_k] : (short)0;
+      }
+      __syncthreads();
     }
-    *reinterpret_cast<v4i *>(J.P + row * kp + p) = out.v;
+    // eight k of one row per thread, twice: eight threads write the 128 bytes of a row
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t row = r0 + h * 32 + (tid >> 3), p = p0 + 8 * (tid & 7);
+      if (row >= J.rows) continue;
+      union { short e[8]; v4i v; } out;
+      if (J.s_k != 1) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out.e[e] = tile[8 * (tid & 7) + e][h * 32 + (tid >> 3)];
+      } else if (p + 8 <= k) {
+        const s16x8 x = *reinterpret_cast<const s16x8 *>(J.X + row * J.s_r + p);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out.e[e] = x.v[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out.e[e] = p + e < k ? J.X[row * J.s_r + p + e] : (short)0;
+      }
+      *reinterpret_cast<v4i *>(J.P + row * kp + p) = out.v;
+    }
+    if (J.s_k != 1) __syncthreads();  // the next block's loads overwrite the tile
   }
 }
 
@@ -581,8 +585,8 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
     ws += bytes;
   }
   if (const int64_t blocks = job[0].blocks + job[1].blocks) {
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(pack16_kernel, dim3((unsigned)blocks), dim3(256), 0, s, job[0], job[1], p.k, kp);
+    const unsigned grid = (unsigned)(blocks < PACK_GRID ? blocks : PACK_GRID);
+    hipLaunchKernelGGL(pack16_kernel, dim3(grid), dim3(256), 0, s, job[0], job[1], p.k, kp);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // (a packed row is zero from k on; with both packed no block ends early)

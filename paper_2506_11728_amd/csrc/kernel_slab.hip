@@ -331,7 +331,7 @@ bool slab_eligible(const Problem &p, int nt) {
   if ((p.m > 1 && lda % 16) || ldb % 16) return false;  // a single row of A has no stride
   if (reinterpret_cast<uintptr_t>(p.A) % 16 || reinterpret_cast<uintptr_t>(p.B) % 16) return false;
   if ((p.m > 1 && 64 * lda >= ((int64_t)1 << 31)) || 128 * ldb >= ((int64_t)1 << 31)) return false;
-  if (p.n / (16 * nt) > ((int64_t)1 << 30)) return false;
+  if (p.n / (16 * nt) >= ((int64_t)1 << 23)) return false;  // x 512 threads stays below 2^32
   return true;
 }
 

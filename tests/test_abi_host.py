@@ -365,6 +365,14 @@ def test_which_skinny_products_take_slabs(M, m, n, k, order, mode, name):
     assert chosen == name if name != "tiles" else chosen.startswith("mfma_dma"), chosen
 
 
+def test_skinny_products_with_more_slabs_than_a_grid_holds_take_tiles(M):
+    """A launch has fewer than 2^32 threads: 2^23 slabs of eight waves are too many."""
+    name = lambda n, order: M.mipgemm_variant_name(1, n, 64, 64, 0, n if order == 0 else 64, order, n, 0)
+    for order in (0, 1):
+        assert name(1 << 16, 1) == "mfma_slab64"
+        assert "slab" not in name((1 << 27) + 16, order) and "slab" not in name(1 << 29, order)
+
+
 # (m, n, k, order of A, of B, signedness, mode): products that lost 20 to 70 % on tiles with a side of 192
 @pytest.mark.parametrize("m,n,k,oa,ob,au,bu,mode", [
     (8171, 2730, 1024, 0, 1, 0, 0, 1), (5152, 4096, 1024, 0, 1, 0, 1, 1),

@@ -277,3 +277,18 @@ def test_s16_few_tiles_keep_their_ranges_of_k(gpu, m, n, k):
     plain = _time_of_a_call(gpu, m, n, k, False)
     assert _time_of_a_call(gpu, m, n, k, True) < 2.5 * plain
     assert _time_of_a_call(gpu, m, n, k, False, shift=1) < 2.5 * plain
+
+
+def test_s16_rewritten_operands_of_very_many_blocks(gpu):
+    """Two rows of 2^29 + 2 elements: 2^24 blocks of 64 x 64 to rewrite, more threads than one grid holds."""
+    import torch
+    k = (1 << 29) + 2
+    torch.manual_seed(15)
+    A = torch.randint(-32768, 32768, (k,), dtype=torch.int16, device="cuda")
+    B = torch.randint(-32768, 32768, (k,), dtype=torch.int16, device="cuda")
+    want = (A.int() * B.int()).sum(dtype=torch.int64).item()              # every product fits 32 bits
+    C = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(gpu.mipgemm_workspace_size_s16(1, 1, k), dtype=torch.uint8, device="cuda")
+    gpu.mipgemm_s16s16s32(1, 1, k, A, k, W.ROW_MAJOR, B, k, W.COL_MAJOR, C, 1, W.ROW_MAJOR, W.OVERWRITE,
+                          workspace=ws, workspace_bytes=ws.numel())
+    assert (C.item() - want) % (1 << 32) == 0
