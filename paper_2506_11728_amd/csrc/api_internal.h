@@ -36,3 +36,12 @@ int run_gemm(int a_unsigned, int b_unsigned, int out_float, float scale, int64_t
              const int32_t *ksum = nullptr);  // ksum: see Problem::ksum (pre-packed weights)
 
 }  // namespace mip
+
+// Every name that plan_name can give a plan with a kernel, for the tables that put a prefix before it.
+#define MIP_FOR_EACH_VARIANT(X)                                                                    \
+  X("simple") X("mfma_tile256") X("mfma_tile128") X("mfma_tile64") X("mfma_tile64x256")            \
+  X("mfma_tile256x64") X("mfma_tile64x128") X("mfma_tile128x64") X("mfma_dma256") X("mfma_dma128") \
+  X("mfma_dma64") X("mfma_dma64x256") X("mfma_dma256x64") X("mfma_dma64x128") X("mfma_dma128x64")  \
+  X("mfma_dma256_k128") X("mfma_dma128_k128") X("mfma_dma256_k128_ragged")                         \
+  X("mfma_dma128_k128_split") X("mfma_dma256x192_k128") X("mfma_dma192x256_k128")                  \
+  X("mfma_dma192_k128") X("mfma_slab16") X("mfma_slab32") X("mfma_slab64")

@@ -543,14 +543,8 @@ const char *mipgemm_variant_name_with_workspace(int64_t m, int64_t n, int64_t k,
   p.a_sk = p.b_sk = 1;
   p.k = kp;
   p.rows_padded_to_256 = true;
-#define MIP_NAME(x) {x, "packed+" x}
-  static const char *const names[][2] = {
-      MIP_NAME("mfma_dma256"), MIP_NAME("mfma_dma128"), MIP_NAME("mfma_dma64"),
-      MIP_NAME("mfma_dma64x256"), MIP_NAME("mfma_dma256x64"), MIP_NAME("mfma_dma64x128"),
-      MIP_NAME("mfma_dma128x64"), MIP_NAME("mfma_dma256_k128"), MIP_NAME("mfma_dma128_k128"),
-      MIP_NAME("mfma_dma256x192_k128"), MIP_NAME("mfma_dma192x256_k128"), MIP_NAME("mfma_dma192_k128"),
-      MIP_NAME("mfma_dma128_k128_split"), MIP_NAME("mfma_dma256_k128_ragged"), MIP_NAME("mfma_slab16"),
-      MIP_NAME("mfma_slab32"), MIP_NAME("mfma_slab64")};
+#define MIP_NAME(x) {x, "packed+" x},
+  static const char *const names[][2] = {MIP_FOR_EACH_VARIANT(MIP_NAME)};
 #undef MIP_NAME
   const char *base = mip::plan_name(mip::choose_plan(p));
   for (const auto &nm : names)

@@ -151,15 +151,8 @@ const char *mipgemm_conv_variant_name(int64_t b, int64_t hi, int64_t wi, int64_t
     plan = mip::choose_plan(conv_problem(c, co, fake, fake, const_cast<void *>(fake),
                                          MIPGEMM_OVERWRITE, false, fake));
   // static strings: every kernel variant name with either prefix
-#define MIP_NAME(x) {x, "implicit:" x, "im2col+" x}
-  static const char *const names[][3] = {
-      MIP_NAME("mfma_dma256"), MIP_NAME("mfma_dma128"), MIP_NAME("mfma_dma64"),
-      MIP_NAME("mfma_dma64x256"), MIP_NAME("mfma_dma256x64"), MIP_NAME("mfma_tile256"),
-      MIP_NAME("mfma_tile128"), MIP_NAME("mfma_tile64"), MIP_NAME("mfma_tile64x256"),
-      MIP_NAME("mfma_tile256x64"), MIP_NAME("mfma_dma64x128"), MIP_NAME("mfma_dma128x64"),
-      MIP_NAME("mfma_tile64x128"), MIP_NAME("mfma_tile128x64"), MIP_NAME("mfma_dma256_k128"), MIP_NAME("mfma_slab16"),
-      MIP_NAME("mfma_slab32"), MIP_NAME("mfma_dma256x192_k128"), MIP_NAME("mfma_dma192x256_k128"),
-      MIP_NAME("mfma_dma192_k128"), MIP_NAME("simple")};
+#define MIP_NAME(x) {x, "implicit:" x, "im2col+" x},
+  static const char *const names[][3] = {MIP_FOR_EACH_VARIANT(MIP_NAME)};
 #undef MIP_NAME
   const char *base = mip::plan_name(plan);
   for (const auto &n : names)

@@ -380,3 +380,10 @@ def test_skinny_products_with_more_slabs_than_a_grid_holds_take_tiles(M):
 def test_products_that_keep_tiles_with_sides_of_128_and_256(M, m, n, k, oa, ob, au, bu, mode):
     name = M.mipgemm_variant_name_for_mode(m, n, k, m if oa else k, oa, k if ob else n, ob, n, 0, bool(au), bool(bu), True, mode)
     assert name.startswith("mfma_dma") and "192" not in name
+
+
+@pytest.mark.parametrize("shape,name", [((32, 56, 96, 256, 3), "im2col+mfma_dma128_k128"), ((1, 4, 160, 4096, 1), "im2col+mfma_slab16"),
+                                        ((40, 49, 96, 200, 3), "im2col+mfma_dma128_k128_split"), ((1, 8, 48, 16384, 3), "im2col+mfma_dma64")])
+def test_names_of_convolutions_through_the_written_out_matrix(M, shape, name):
+    b, hw, ci, co, f = shape
+    assert M.mipgemm_conv_variant_name(b, hw, hw, ci, co, f, f, 1, f // 2) == name
