@@ -104,10 +104,15 @@ def test_s16_wraps_and_extremes(gpu, oracle):
     _check(gpu, oracle, 70, 130, 520, 0, 0, 0, W.ACCUMULATE, 0, "min", seed=5)
 
 
-def test_s16_under_forced_kernels_and_a_misaligned_workspace(gpu, oracle):
-    for variant in ("dma128k128", "dma64", "tile64", "dma64x256", "simple"):
-        _check(gpu, oracle, 256, 384, 1024, 0, 0, 0, W.OVERWRITE, 0, "uniform", seed=6, variant=variant)
-    _check(gpu, oracle, 100, 90, 200, 0, 0, 0, W.OVERWRITE, 0, "uniform", seed=7, misalign=3)
+@pytest.mark.parametrize("variant", ["s16_64", "s16_128"])
+@pytest.mark.parametrize("ranges", [1, 2, 4])
+def test_s16_under_forced_kernels_and_a_misaligned_workspace(gpu, oracle, variant, ranges):
+    """Both tiles with k whole and in ranges; the workspace on a 256-byte boundary and three bytes behind one, with operands
+    used as stored and rewritten into it."""
+    with gpu.tuning(MIPGEMM_SPLITK=str(ranges)):
+        for misalign in (0, 3):
+            _check(gpu, oracle, 256, 384, 1024, 0, 0, 0, W.OVERWRITE, 0, "uniform", seed=6, variant=variant, misalign=misalign)
+            _check(gpu, oracle, 100, 90, 1100, 0, 0, 0, W.ACCUMULATE, 1, "uniform", seed=7, variant=variant, misalign=misalign)
 
 
 def test_s16_a_large_product_as_dispatched(gpu, oracle):
@@ -173,6 +178,30 @@ def test_s16_rows_further_apart_than_32_bit_offsets(gpu, oracle):
                           workspace=ws, workspace_bytes=ws.numel())
     want = (A2.astype(np.int64) @ B2.astype(np.int64)).astype(np.int32)
     assert np.array_equal(C.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("variant", ["s16_64", "s16_128"])
+def test_s16_rows_of_k_further_apart_than_32_bit_offsets(gpu, variant):
+    """The same for operands with k strided: the 64 rows of a block end 4.5 GB behind its first."""
+    import torch
+    m, n, k, ld = 136, 72, 70, (1 << 25) + (1 << 21)
+    A2, B2 = _operands(m, n, k, "uniform", 16)
+    C = torch.zeros((m, n), dtype=torch.int32, device="cuda")
+    ws = torch.empty(gpu.mipgemm_workspace_size_s16(m, n, k), dtype=torch.uint8, device="cuda")
+    far = torch.empty(k * ld, dtype=torch.int16, device="cuda")
+    want = (A2.astype(np.int64) @ B2.astype(np.int64)).astype(np.int32)
+    with gpu.tuning(MIPGEMM_VARIANT=variant):
+        far.view(k, ld)[:, :m] = torch.from_numpy(A2.T.copy()).cuda()
+        B = torch.from_numpy(B2).cuda()
+        gpu.mipgemm_s16s16s32(m, n, k, far, ld, W.COL_MAJOR, B, n, W.ROW_MAJOR, C, n, W.ROW_MAJOR, W.OVERWRITE,
+                              workspace=ws, workspace_bytes=ws.numel())
+        assert np.array_equal(C.cpu().numpy(), want)
+        C.zero_()
+        far.view(k, ld)[:, :n] = torch.from_numpy(B2).cuda()
+        A = torch.from_numpy(A2).cuda()
+        gpu.mipgemm_s16s16s32(m, n, k, A, k, W.ROW_MAJOR, far, ld, W.ROW_MAJOR, C, n, W.ROW_MAJOR, W.OVERWRITE,
+                              workspace=ws, workspace_bytes=ws.numel())
+        assert np.array_equal(C.cpu().numpy(), want)
 
 
 def test_s16_replayed_from_a_graph(gpu):
