@@ -543,7 +543,7 @@ size_t mipgemm_workspace_size(int64_t m, int64_t n, int64_t k,
  * workgroup per tile and runs up to twice as long on long-k, few-tile shapes.
  * (The per-tile counters of that scheme live in a 4 MiB static device array of
  * the library, handed out in rotation, so that concurrent calls use different
- * ones; a call under stream capture keeps its own of a second array of 2 MiB, and
+ * ones; a call under stream capture keeps its own of a second array as large, and
  * when that is used up has them in its workspace, behind the slots, or keeps k whole where they do not
  * fit; the int32 entry points add their k ranges into C with atomics and need
  * no slots.)

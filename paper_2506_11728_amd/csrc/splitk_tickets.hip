@@ -18,7 +18,7 @@ namespace mip {
 namespace {
 
 constexpr int64_t TICKETS = 1 << 20;   // 4 MiB per device
-constexpr int64_t CAPTURED = 1 << 19;  // some thousands of captured calls
+constexpr int64_t CAPTURED = 1 << 20;  // as much again, for some ten thousand captured calls
 static __device__ unsigned g_tickets[TICKETS], g_captured[CAPTURED];
 
 constexpr int MAX_DEVICES = 64;
@@ -44,7 +44,7 @@ bool being_captured(hipStream_t s) {
 }
 
 hipError_t splitk_tickets(int64_t count, hipStream_t s, unsigned *own, unsigned **out) {
-  if (count < 1 || count > CAPTURED / 4) return hipErrorInvalidValue;
+  if (count < 1 || count > TICKETS / 4) return hipErrorInvalidValue;
   int device = 0;
   hipError_t e = hipGetDevice(&device);
   if (e != hipSuccess) return e;

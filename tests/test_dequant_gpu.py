@@ -291,7 +291,7 @@ def _use_up_the_counters(gpu):
     stream.wait_stream(torch.cuda.current_stream())
     with gpu.tuning(MIPGEMM_VARIANT="dma64", MIPGEMM_SPLITK=2):
         with torch.cuda.graph(graph, stream=stream):
-            for side, calls in ((64 * 32, 512), (64, 1024)):
+            for side, calls in ((64 * 32, 1024), (64, 1024)):
                 for _ in range(calls):
                     gpu.mipgemm_s8s8f32(side, side, 128, A, 128, 0, A, 128, 1, C, side, 0, W.OVERWRITE, workspace=ws,
                                         workspace_bytes=ws.numel())
