@@ -579,10 +579,10 @@ def run_packed_weights_table(M):
 
 
 def run_s16_table(M):
-    """int16 x int16 -> int32 through byte planes against the 8-bit product of the same size."""
+    """int16 x int16 -> int32 against the 8-bit product of the same size."""
     import torch
     print()
-    print("16-bit operands (int16 x int16 -> int32: byte planes, three s8 x s8 GEMMs and a combining pass),")
+    print("16-bit operands (int16 x int16 -> int32, split into byte planes on the way to the matrix instructions),")
     print("us per call (warm, graph replays), TOPS counted as 2 m n k:")
     print()
     print("| m | n | k | s8 x s8 -> s32 | s16 x s16 -> s32 | ratio | TOPS (s16) |")

@@ -204,10 +204,20 @@ def _run(check, name, *args):
 
 
 def _tell_stream_source(torch):
-    """From the first call on (which has initialised torch's runtime), None as a stream is looked up without torch.cuda.current_stream's Stream object."""
+    """From the first call on (which has initialised torch's runtime), None as a stream is looked up
+    without torch.cuda.current_stream's Stream object."""
     device, handle = (getattr(torch._C, n, None) for n in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
     if _native is not None and device is not None and handle is not None:
         _native.stream_source(device, handle)
+
+
+def _forget_stream_source():
+    """In a forked child torch refuses the device; asking its runtime directly would go past that."""
+    if _native is not None:
+        _native.stream_source(None, None)
+
+
+os.register_at_fork(after_in_child=_forget_stream_source)
 
 
 def _ptr(x):

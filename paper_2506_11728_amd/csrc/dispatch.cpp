@@ -68,8 +68,9 @@ const char *plan_name(const Plan &plan) {
 }
 
 // The tuning value MIPGEMM_VARIANT pins the kernel (tuning and tests): "simple", "dma256k128",
-// "dma128k128" (the same kernel on 128 x 128 tiles), "dma128k128split" (its general form with k ranges), "dma256k128ragged" (the general form on 256 x 256 tiles),
-// "slab16" / "slab32" (the skinny-m kernel with that slab width),
+// "dma128k128" (the same kernel on 128 x 128 tiles), "dma128k128split" (its general form with k
+// ranges), "dma256k128ragged", "dma256x192k128", "dma192x256k128", "dma192k128" (the general form on
+// tiles of those sides), "slab16" / "slab32" / "slab64" (the skinny-m kernel with that slab width),
 // "tile<shape>" (register-staged) or "dma<shape>" (direct-to-LDS) with <shape> one of
 // 256, 128, 64, 64x256, 256x64, 64x128, 128x64.  A dma variant only applies to problems it is
 // eligible for; others fall back to the staged kernel of the same shape.

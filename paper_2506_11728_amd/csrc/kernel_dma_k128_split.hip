@@ -1,6 +1,6 @@
 // The kernel with 128-deep k blocks (dma_k128.h) in its general form: ragged m and n on
-// unpadded operands, on 256 x 256 or 128 x 128 tiles (those of 192 have files of their own); on the latter k may be cut into ranges,
-// for problems whose tiles are too few to occupy the device while k is long: every range of a
+// unpadded operands, on 256 x 256 or 128 x 128 tiles (those with a side of 192 have files of
+// their own); on the latter k may be cut into ranges, for problems whose tiles are too few to occupy the device while k is long: every range of a
 // tile is a workgroup of its own, and the ranges add their partial sums into C with integer
 // atomics.
 #include "dma_k128_general.h"

@@ -267,7 +267,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
   };
 
   // The matrix instructions are inline assembly with the accumulators bound to the accumulation
-  // registers: the register allocator otherwise moves some of the 192 to and fro inside the
+  // registers: the register allocator otherwise moves some of the 96 (48) to and fro inside the
   // loop.  The compiler therefore inserts no wait states for them: an operand is written long
   // before its first use (the s_nop before the first and the last block see to the rest), and
   // the two that share an accumulator are five apart.
@@ -436,9 +436,9 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
       for (int p = 0; p < 8; ++p) {
         const int r = 2 * p + (lane >> 5);
         const int64_t row = mw + row0 + r;
+        const uint32_t val = patch[r * PITCH + (lane & 31)] + colc + rows[wm * WM + row0 + r];
         if (row < P.m && col < P.n)
-          __hip_atomic_fetch_add(P.C + row * P.ldc + col, patch[r * PITCH + (lane & 31)] + colc + rows[wm * WM + row0 + r],
-                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_fetch_add(P.C + row * P.ldc + col, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
     return;
@@ -633,7 +633,8 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
     // The ranges meet in slots, where the workspace has room for at least half of them.  (A captured
     // call, whose counters are never handed out again, does as well without.)
     const int64_t room = (end - ws) / (count * side * side * 4), fit = room < splits ? room : splits;
-    if (fit > 1 && 2 * fit >= splits && !being_captured(s) && splitk_tickets(count, s, nullptr, &P.tickets) == hipSuccess) {
+    if (fit > 1 && 2 * fit >= splits && !being_captured(s) &&
+        splitk_tickets(count, s, nullptr, &P.tickets) == hipSuccess) {
       P.slots = reinterpret_cast<int32_t *>(ws);
       splits = fit;
     } else if (!p.accumulate) {

@@ -359,7 +359,8 @@ hipError_t launch_slab(const Problem &p, int nt, hipStream_t s) {
   if (nt == 1 && mt == 1) rings = few_steps || (many && P.nsteps < 16) ? FEW : (many ? HALF : DEEP);
   else if ((nt == 4 && mt == 1) || (nt == 1 && mt == 2)) rings = many || few_steps ? FEW : DEEP;
   if (rings == HALF) kern = pick<1, 1, HALF>(b_kc, uns);
-  else if (rings == FEW) kern = nt == 4 ? pick<1, 4, FEW>(b_kc, uns) : (mt == 1 ? pick<1, 1, FEW>(b_kc, uns) : pick<2, 1, FEW>(b_kc, uns));
+  else if (rings == FEW && nt == 4) kern = pick<1, 4, FEW>(b_kc, uns);
+  else if (rings == FEW) kern = mt == 1 ? pick<1, 1, FEW>(b_kc, uns) : pick<2, 1, FEW>(b_kc, uns);
   else if (nt == 1) kern = mt == 1 ? pick<1, 1>(b_kc, uns) : (mt == 2 ? pick<2, 1>(b_kc, uns) : pick<4, 1>(b_kc, uns));
   else if (nt == 2) kern = mt == 1 ? pick<1, 2>(b_kc, uns) : (mt == 2 ? pick<2, 2>(b_kc, uns) : pick<4, 2>(b_kc, uns));
   else kern = mt == 1 ? pick<1, 4>(b_kc, uns) : (mt == 2 ? pick<2, 4>(b_kc, uns) : pick<4, 4>(b_kc, uns));

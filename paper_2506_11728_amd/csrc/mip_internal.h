@@ -70,14 +70,17 @@ enum Kind {
   KIND_STAGED,    // MFMA tiles, operands staged through registers: any alignment, any size
   KIND_DMA,       // MFMA tiles, operands streamed global -> LDS directly (aligned, k % 64 == 0)
   KIND_DMA_K128,  // 256 x 256 (or, shape SHAPE_128, 128 x 128) tiles, 128-deep k blocks: large aligned problems
-  KIND_DMA_K128_SPLIT,  // the same kernel, ragged edges allowed: 128 x 128 tiles with k cut into `splits` ranges, or (shape SHAPE_256) 256 x 256 tiles
-  KIND_SLAB       // m <= 64: one workgroup per 16- or 32-column slab of B, all of k (splits = 1 or 2: slab width / 16)
+  // the same kernel, ragged edges allowed: 128 x 128 tiles with k cut into `splits` ranges, or 256 x 256
+  // tiles or those with a side of 192, by the shape
+  KIND_DMA_K128_SPLIT,
+  // m <= 64: one workgroup per slab of 16, 32 or 64 columns of B, all of k (splits = 1, 2 or 4: width / 16)
+  KIND_SLAB
 };
 
 struct Plan {
   Kind kind;
-  Shape shape;  // KIND_STAGED and KIND_DMA
-  int splits;   // k ranges worked on by separate workgroups (1 = no split)
+  Shape shape;  // of tile kernels
+  int splits;   // k ranges worked on by separate workgroups (1 = no split); KIND_SLAB: the width
 };
 
 Plan choose_plan(const Problem &p);
@@ -109,7 +112,7 @@ hipError_t launch_dma_k128_256x192(const Problem &p, hipStream_t s);
 hipError_t launch_dma_k128_192x256(const Problem &p, hipStream_t s);
 hipError_t launch_dma_k128_192x192(const Problem &p, hipStream_t s);
 
-bool slab_eligible(const Problem &p, int nt);  // nt: slab width in blocks of 16 columns, 1 or 2
+bool slab_eligible(const Problem &p, int nt);  // nt: slab width in blocks of 16 columns, 1, 2 or 4
 hipError_t launch_slab(const Problem &p, int nt, hipStream_t s);
 
 #define MIP_DECLARE_DMA(BM, BN)                        \
@@ -178,8 +181,8 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s);
 bool being_captured(hipStream_t s);
 hipError_t splitk_tickets(int64_t count, hipStream_t s, unsigned *own, unsigned **out);
 
-// Bytes of partial-sum slots, and of counters behind them, that the plan's split k wants (0: no split, or a kernel that adds
-// into C with atomics whatever it is given).
+// Bytes of partial-sum slots, and of counters behind them, that the plan's split k wants (0: no
+// split, or a kernel that adds into C with atomics whatever it is given).
 size_t splitk_slot_bytes(const Problem &p, const Plan &plan);
 
 bool dma_eligible(const Problem &p, Shape shape);

@@ -172,13 +172,15 @@ static PyObject *register_entry(PyObject *self, PyObject *args) {
   Py_RETURN_NONE;
 }
 
-/* stream_source(current_device, raw_stream): where None as a stream is looked up from now on */
+/* stream_source(current_device, raw_stream): where None as a stream is looked up from now on; None, None:
+ * no longer here */
 static PyObject *stream_source(PyObject *self, PyObject *args) {
   PyObject *device, *handle, *old_device = current_device, *old_handle = raw_stream;
   (void)self;
   if (!PyArg_ParseTuple(args, "OO", &device, &handle)) return NULL;
-  Py_INCREF(device);
-  Py_INCREF(handle);
+  if (device == Py_None || handle == Py_None) device = handle = NULL;
+  Py_XINCREF(device);
+  Py_XINCREF(handle);
   raw_stream = handle;
   current_device = device;
   Py_XDECREF(old_device);

@@ -349,6 +349,27 @@ def test_binding_built_after_the_package_was_imported(tmp_path):
     assert out.stdout.strip().endswith("_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
+def test_a_forked_child_asks_torch_for_the_stream(M):
+    """torch refuses its device in a forked child: a call without a stream has to reach that refusal there."""
+    from paper_2506_11728_amd import binding
+    if binding._native is None:
+        pytest.skip("built without Python headers")
+    call = lambda: M.mipgemm_s8s8s32(-1, 4, 4, 0, 4, 0, 0, 4, 0, 0, 4, 0, 0, check=False)   # refused: m
+    binding._native.stream_source(lambda: 0, lambda device: 0)
+    try:
+        assert call() == -1
+        pid = os.fork()
+        if pid == 0:
+            asked = []
+            binding._stream = lambda stream: asked.append(stream)
+            rc = call()
+            os._exit(0 if rc == -1 and asked == [None] else 1)
+        assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+        assert call() == -1
+    finally:
+        binding._native.stream_source(None, None)
+
+
 # (m, n, k, order of B, mode, kernel): either side of the rules of the skinny kernel, where slabs were
 # measured slower than tiles, or slabs of another width slower than these
 @pytest.mark.parametrize("m,n,k,order,mode,name", [
