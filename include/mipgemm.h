@@ -37,8 +37,9 @@
  * (no memory-set or copy operations), so a call may be recorded into a HIP
  * graph by stream capture and replayed.  Calls from several threads are safe:
  * the only state the library keeps is a table of kernels that have been granted
- * a large dynamic LDS size (guarded), the device's compute-unit count (read once)
- * and the tuning values below.
+ * a large dynamic LDS size (guarded), the device's compute-unit count (read once),
+ * the counters that products with a split k meet at (no two calls in flight share
+ * one) and the tuning values below.
  *
  * Tuning values.  Four process-wide overrides exist for tests, tuning runs and
  * profiles; unset, the dispatcher decides.  They are taken from the environment

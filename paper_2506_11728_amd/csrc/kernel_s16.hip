@@ -19,8 +19,8 @@
 // many of LDS traffic per compute unit, and about 900 of ordinary vector instructions (splits, sums,
 // addresses) per SIMD; together, with a barrier per block, they take about 2000.
 // (Splitting into planes in memory first, three 8-bit products and a pass that combined them were
-// nine launches and five passes over C-sized data: (1024, 3072, 768) 43 us, this kernel 16 us;
-// 64 x 64 of wave tile instead of 64 x 32, one wave to a SIMD: 19 us.)
+// nine launches and five passes over C-sized data: (1024, 3072, 768) 43 us, this kernel 16.5 us
+// (17.7 under a profiler, 18 in a graph); 64 x 64 of wave tile instead of 64 x 32, one wave to a SIMD: 19 us.)
 #include <cstring>
 
 #include "dma_common.h"

@@ -15,7 +15,8 @@
 // What bounds it is how much of B is in flight and in what pieces: a step is 128 deep so that a
 // k-contiguous B (and A) comes in whole 128-byte lines, and eight waves keep up to 128 KB of B
 // per workgroup on its way.  Against four waves with 64-deep steps (half lines, at most 64 KB in
-// flight), us: (1, 4096, 4096) 6.6 -> 6.0, (16, 11008, 4096) 12.5 -> 10.2.  (Loading the fragments
+// flight), us: (1, 4096, 4096) 6.6 -> 6.0 a call, (16, 11008, 4096) 12.5 -> 10.2 (the kernel alone
+// 12.3 -> 9.4: 4.9 TB/s), (1, 11008, 4096) 10.9 -> 9.5 (the kernel).  (Loading the fragments
 // of a k-contiguous B straight into registers, half lines of sixteen columns at a time, takes
 // twice as long: 10.2 -> 21.)
 //
