@@ -52,22 +52,48 @@ __device__ __forceinline__ uint32_t lds_address(const uint8_t *p) {
   return (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const uint8_t *)p);
 }
 
+// Kernel arguments fetched here, together: left to the compiler, each is loaded in the block that first
+// needs it, and a workgroup waits for three or four such loads (about 500 clocks each) one after the
+// other before its first operand load.
+template <typename T>
+__device__ __forceinline__ void fetch_argument(const T &x) {
+  asm volatile("" ::"s"(x));
+}
+__device__ __forceinline__ void fetch_argument(const TileWalk &w) {
+  asm volatile("" ::"s"(w.tiles_m), "s"(w.tiles_n), "s"(w.group.d), "s"(w.group.inv), "s"(w.last.d), "s"(w.last.inv));
+}
+template <typename... T>
+__device__ __forceinline__ void fetch_arguments(const T &...x) {
+  (fetch_argument(x), ...);
+}
+
+// n / d, d and the range of n known to the host (one multiplication on the scalar unit, where the
+// compiler's division takes some forty dependent instructions, a third of a microsecond or more at the start of a
+// workgroup, before its first load).
+__device__ __forceinline__ unsigned divided(unsigned n, Divisor d) {
+  if (__builtin_expect(d.inv != 0, 1)) return __umulhi(n, d.inv);
+  return d.d == 1 ? n : n / d.d;
+}
+
+// First block of range y of those that k is cut into: `per` blocks each, one more in the first `longer`.
+__device__ __forceinline__ int first_of_range(int y, int per, int longer) { return y * per + (y < longer ? y : longer); }
+
 // Workgroup -> tile.  Consecutive workgroup ids land on different XCDs (8 of
 // them, each with its own L2), so every XCD gets a contiguous run of tiles, and
 // the tiles are walked in groups of 8 tile-rows so that the workgroups resident
 // on one XCD share A row-panels and B column-panels.  Returns false for the
 // padding workgroups at the end of the grid.
-__device__ __forceinline__ bool tile_of_workgroup(int tiles_m, int tiles_n, int *tm, int *tn) {
-  const int ntiles = tiles_m * tiles_n;
+__device__ __forceinline__ bool tile_of_workgroup(const TileWalk &w, int *tm, int *tn) {
+  const int ntiles = w.tiles_m * w.tiles_n;
   const int per_xcd = (ntiles + 7) / 8;
   const int lid = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (blockIdx.x / 8 >= per_xcd || lid >= ntiles) return false;
   constexpr int GROUP = 8;
-  const int per_group = GROUP * tiles_n;
-  const int first_m = (lid / per_group) * GROUP;
-  const int gsz = tiles_m - first_m < GROUP ? tiles_m - first_m : GROUP;
-  *tm = first_m + (lid % per_group) % gsz;
-  *tn = (lid % per_group) / gsz;
+  const int group = (int)divided((unsigned)lid, w.group), at = lid - group * (int)w.group.d;
+  const int first_m = group * GROUP;
+  const bool whole = w.tiles_m - first_m >= GROUP;
+  *tn = whole ? at / GROUP : (int)divided((unsigned)at, w.last);
+  *tm = first_m + at - *tn * (whole ? GROUP : (int)w.last.d);
   return true;
 }
 

@@ -25,7 +25,7 @@ struct DmaParams {
   int32_t *C;
   int64_t lda, ldb, ldc;  // the one stride of each operand that is not 1
   int64_t m, n;           // rows and columns of C (RAGGED form only)
-  int tiles_m, tiles_n;
+  TileWalk walk;
   int nkt;                // k / 128
   int accumulate;         // C += instead of C =
   int out_float;          // 1 dequantised output: float(sum) * scale; 2 requantised int8 output
@@ -39,10 +39,11 @@ struct DmaParams {
   // unit) start late by their row in the XCD's patch of tiles times stagger_ticks (10 ns
   // each); 0 = all at once.
   int first_round, stagger_ticks;
-  // GENERAL form: k is cut into `splits` ranges of whole blocks, one per blockIdx.y; with
+  // GENERAL form: k is cut into ranges of whole blocks, one per blockIdx.y; with
   // `atomic` set the partial sums are added into C with integer atomics (C zeroed or holding
   // the values to add to beforehand).
-  int splits, atomic;
+  int per_range, longer;  // blocks of a range; the first `longer` have one more
+  int atomic;
 };
 
 // ---------------------------------------------------------------------------
@@ -197,8 +198,10 @@ __global__ __launch_bounds__(NTHREADS) void dma128_kernel(DmaParams P) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
+  fetch_arguments(P.walk, P.A, P.B, P.C, P.m, P.n, P.lda, P.ldb, P.ldc, P.nkt, P.accumulate, P.out_float, P.scale,
+                  P.clocks, P.first_round, P.stagger_ticks, P.per_range, P.longer, P.atomic);
   int tm, tn;
-  if (!tile_of_workgroup(P.tiles_m, P.tiles_n, &tm, &tn)) return;
+  if (!tile_of_workgroup(P.walk, &tm, &tn)) return;
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
   // With several rounds of tiles all compute units would reach their write-backs at the
   // same moments, round after round, and the 32 of one XCD share one path to memory: a tile's
@@ -231,9 +234,9 @@ __global__ __launch_bounds__(NTHREADS) void dma128_kernel(DmaParams P) {
   }
   const int64_t stepA = A_KC ? KD2 : KD2 * P.lda;
   const int64_t stepB = B_KC ? KD2 : KD2 * P.ldb;
-  // this workgroup's k blocks: all of them, or range blockIdx.y of P.splits
-  const int block0 = GENERAL ? (int)((int64_t)blockIdx.y * P.nkt / P.splits) : 0;
-  const int nkt = GENERAL ? (int)((int64_t)(blockIdx.y + 1) * P.nkt / P.splits) - block0 : P.nkt;  // k / 128
+  // this workgroup's k blocks: all of them, or range blockIdx.y
+  const int block0 = GENERAL ? first_of_range(blockIdx.y, P.per_range, P.longer) : 0;
+  const int nkt = GENERAL ? P.per_range + ((int)blockIdx.y < P.longer) : P.nkt;  // k / 128
   const uint8_t *gA = P.A + (A_KC ? m0 * P.lda : m0) + block0 * stepA;
   const uint8_t *gB = P.B + (B_KC ? n0 * P.ldb : n0) + block0 * stepB;
 

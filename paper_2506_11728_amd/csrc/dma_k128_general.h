@@ -19,21 +19,21 @@ hipError_t launch_general(const Problem &p, int splits, hipStream_t s) {
   P.ldc = p.ldc;
   P.m = p.m;
   P.n = p.n;
-  P.tiles_m = (int)((p.m + BM - 1) / BM);
-  P.tiles_n = (int)((p.n + BN - 1) / BN);
+  P.walk = tile_walk((p.m + BM - 1) / BM, (p.n + BN - 1) / BN);
   P.nkt = (int)(p.k / KD2);
   // k ranges on the small tile only, and only into an int32 C (float sums must not be combined
   // in arbitrary order, and an int8 C holds no partial sums)
   if (splits < 1 || BM != 128 || p.out_float) splits = 1;
   if (splits > P.nkt) splits = P.nkt;       // every range holds at least one block
   if (splits > 65535) splits = 65535;
-  P.splits = splits;
+  P.per_range = P.nkt / splits;
+  P.longer = P.nkt % splits;
   P.atomic = splits > 1;
   P.accumulate = p.accumulate;
   P.out_float = p.out_float;
   P.scale = p.scale;
   P.ksum = nullptr;
-  const int ntiles = P.tiles_m * P.tiles_n;
+  const int ntiles = P.walk.tiles_m * P.walk.tiles_n;
   P.first_round = (int)compute_units();
   // (the large tile's rows of an XCD's patch start apart, as in the form for whole tiles)
   P.stagger_ticks = BM != 128 && ntiles >= 2 * P.first_round ? STAGGER_TICKS : 0;

@@ -34,7 +34,7 @@ struct DmaTileParams {
   int32_t *C;
   int64_t m, n;
   int64_t lda, ldb, ldc;  // the one stride of each operand that is not 1
-  int tiles_m, tiles_n;
+  TileWalk walk;
   int nkt;                // k / 64 in the whole problem
   int kt_per_split;       // k blocks per workgroup (blockIdx.y picks the range)
   int accumulate;         // C += instead of C =
@@ -48,6 +48,7 @@ struct DmaTileParams {
   float scale;
   const int32_t *ksum;    // UNS 3 and 4: the k sums of the signed operand (see Problem::ksum)
   ConvGeom conv;          // CONV kernels only
+  Divisor per_image, per_row;  // by the output positions of an image and of a row of one
   int64_t a_sb, b_sb, c_sb;  // byte / element offsets of problem z of a batch (blockIdx.z)
 };
 
@@ -76,8 +77,15 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(DmaTileParams P) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
+  fetch_arguments(P.walk, P.A, P.B, P.C, P.m, P.n, P.lda, P.ldb, P.ldc, P.nkt, P.kt_per_split, P.accumulate, P.atomic, P.slots,
+                  P.out_float, P.scale);
+  if constexpr (CONV)
+    fetch_arguments(P.per_image.d, P.per_image.inv, P.per_row.d, P.per_row.inv, P.conv.hi, P.conv.wi, P.conv.ci,
+                    P.conv.wf, P.conv.ho, P.conv.wo, P.conv.stride, P.conv.pad);
+  else
+    fetch_arguments(P.a_sb, P.b_sb, P.c_sb);
   int tm, tn;
-  if (!tile_of_workgroup(P.tiles_m, P.tiles_n, &tm, &tn)) return;
+  if (!tile_of_workgroup(P.walk, &tm, &tn)) return;
   if (!CONV) {  // problem of the batch
     const int64_t z = blockIdx.z;
     P.A += z * P.a_sb;
@@ -138,17 +146,19 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(DmaTileParams P) {
       int64_t row = m0 + a;
       if (row >= P.m) row = P.m - 1;  // past the edge: repeat the last position, never stored
       const int per_image = G.ho * G.wo;
-      const int g = (int)(row / per_image), r = (int)(row - (int64_t)g * per_image);
-      const int oy = r / G.wo, ox = r - oy * G.wo;
+      const int g = (int)divided((unsigned)row, P.per_image), r = (int)row - g * per_image;
+      const int oy = (int)divided((unsigned)r, P.per_row), ox = r - oy * G.wo;
       conv_iy[i] = oy * G.stride - G.pad;
       conv_ix[i] = ox * G.stride - G.pad;
       conv_at[i] = ((g * G.hi + conv_iy[i]) * G.wi + conv_ix[i]) * G.ci + ((c ^ SA::kswz(a)) << 4);
     }
-    const int per_tap = G.ci / BK, tap = kt_begin / per_tap;
-    cur_c = (kt_begin - tap * per_tap) * BK;
-    cur_y = tap / G.wf;
-    cur_x = tap - cur_y * G.wf;
-    cur_at = (cur_y * G.wi + cur_x) * G.ci + cur_c;
+    if (kt_begin > 0) {
+      const int per_tap = G.ci / BK, tap = kt_begin / per_tap;
+      cur_c = (kt_begin - tap * per_tap) * BK;
+      cur_y = tap / G.wf;
+      cur_x = tap - cur_y * G.wf;
+      cur_at = (cur_y * G.wi + cur_x) * G.ci + cur_c;
+    }
   }
 
   const uint32_t lds0 = lds_address(smem) + wave * 1024;
@@ -317,7 +327,7 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(DmaTileParams P) {
   // spills registers that the rest of the kernel pays for)
   if constexpr (BM * BN < 256 * 256) {
     if (P.slots) {  // only the workgroup that draws the tile's last ticket writes C
-      const int64_t tile = ((int64_t)blockIdx.z * P.tiles_m + tm) * P.tiles_n + tn;
+      const int64_t tile = ((int64_t)blockIdx.z * P.walk.tiles_m + tm) * P.walk.tiles_n + tn;
       if (!combine_k_ranges<FM, FN>(acc, P.slots + tile * P.splits * (int64_t)(BM * BN), blockIdx.y,
                                     P.splits, P.tickets + tile, wave, lane, tid,
                                     reinterpret_cast<int *>(smem)))
@@ -386,8 +396,7 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   P.lda = a_kc ? p.a_sm : p.a_sk;
   P.ldb = b_kc ? p.b_sn : p.b_sk;
   P.ldc = p.ldc;
-  P.tiles_m = (int)((p.m + BM - 1) / BM);
-  P.tiles_n = (int)((p.n + BN - 1) / BN);
+  P.walk = tile_walk((p.m + BM - 1) / BM, (p.n + BN - 1) / BN);
   P.nkt = (int)(p.k / BK);
   if (splits < 1) splits = 1;
   if (splits > P.nkt) splits = P.nkt;
@@ -397,7 +406,7 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   P.accumulate = p.accumulate;
   P.out_float = p.out_float;
   P.scale = p.scale;
-  const int64_t all_tiles = (int64_t)P.tiles_m * P.tiles_n * (p.batch > 1 ? p.batch : 1);
+  const int64_t all_tiles = (int64_t)P.walk.tiles_m * P.walk.tiles_n * (p.batch > 1 ? p.batch : 1);
   P.slots = nullptr;
   P.tickets = nullptr;
   P.splits = splits;
@@ -428,7 +437,7 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   P.a_sb = p.a_sb;
   P.b_sb = p.b_sb;
   P.c_sb = p.c_sb;
-  const int ntiles = P.tiles_m * P.tiles_n;
+  const int ntiles = P.walk.tiles_m * P.walk.tiles_n;
   if (splits == 1) {  // (a float output that found no room for slots)
     P.kt_per_split = P.nkt;
     P.splits = 1;
@@ -462,6 +471,8 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
 #undef MIP_PICK
   if (p.conv) {
     P.conv = *p.conv;
+    P.per_image = divisor((int64_t)p.conv->ho * p.conv->wo, p.m);
+    P.per_row = divisor(p.conv->wo, (int64_t)p.conv->ho * p.conv->wo);
     // (the gathered matrix is the unsigned A, the filters the signed, k-contiguous B)
     const bool filter_sums = p.ksum != nullptr;
     P.ksum = filter_sums ? p.ksum : nullptr;

@@ -36,15 +36,15 @@ hipError_t launch_for(const Problem &p, hipStream_t s, unsigned long long *clock
   P.ldc = p.ldc;
   P.m = p.m;
   P.n = p.n;
-  P.tiles_m = (int)((p.m + BM - 1) / BM);
-  P.tiles_n = (int)((p.n + BN - 1) / BN);
+  P.walk = tile_walk((p.m + BM - 1) / BM, (p.n + BN - 1) / BN);
   P.nkt = (int)(p.k / KD2);
   P.accumulate = p.accumulate;
   P.out_float = p.out_float;
   P.scale = p.scale;
-  P.splits = 1;
+  P.per_range = P.nkt;
+  P.longer = 0;
   P.atomic = 0;
-  const int ntiles = P.tiles_m * P.tiles_n;
+  const int ntiles = P.walk.tiles_m * P.walk.tiles_n;
   dim3 grid((unsigned)(((ntiles + 7) / 8) * 8));
   // (measured at 8192^3, four rounds: 326 -> 310 us on constant operands, 452 -> 444 us on
   // random ones; the 7 us of late start are not earned back by a single round; the 128 x 128

@@ -47,9 +47,10 @@ struct S16Params {
   int64_t lda, ldb;  // bytes: the one stride of each operand that is not one element
   int64_t ldc;
   int64_t m, n, k;
-  int tiles_m, tiles_n;
+  TileWalk walk;
   int nkt;        // blocks of 64 k, the last one filled up with zeros
   int splits;     // ranges of k, one per blockIdx.y
+  int per_range, longer;  // their blocks; the first `longer` have one more
   int accumulate;
   int wide_offsets;  // rows of a tile reach further than 32-bit offsets do
   // splits > 1: `splits` slots of partial sums per tile and one zeroed counter per tile; null: the
@@ -142,11 +143,13 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WC, wn = wave % WC;
+  fetch_arguments(P.walk, P.A, P.B, P.C, P.lda, P.ldb, P.ldc, P.m, P.n, P.k, P.nkt, P.splits, P.per_range, P.longer,
+                  P.accumulate, P.wide_offsets, P.slots);
   int tm, tn;
-  if (!tile_of_workgroup(P.tiles_m, P.tiles_n, &tm, &tn)) return;
+  if (!tile_of_workgroup(P.walk, &tm, &tn)) return;
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  const int block0 = (int)((int64_t)blockIdx.y * P.nkt / P.splits);
-  const int nkt = (int)((int64_t)(blockIdx.y + 1) * P.nkt / P.splits) - block0;
+  const int block0 = first_of_range(blockIdx.y, P.per_range, P.longer);
+  const int nkt = P.per_range + ((int)blockIdx.y < P.longer);
 
   const int rows_a = (int)(P.m - m0 < BM ? P.m - m0 : BM), rows_b = (int)(P.n - n0 < BN ? P.n - n0 : BN);
   uint32_t offA[SA::LOADS], offB[SB::LOADS];
@@ -378,7 +381,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
     // them; the workgroup that draws the tile's last ticket adds the other slots to its own
     // registers.  Slot accesses are device-scope, the ticket is drawn after the stores
     // are acknowledged and the other slots are read after it has come back.
-    const int64_t tile = (int64_t)tm * P.tiles_n + tn;
+    const int64_t tile = (int64_t)tm * P.walk.tiles_n + tn;
     int32_t *slots = P.slots + tile * P.splits * (int64_t)(BM * BN) + wave * (WM * WN);
     unsigned *ticket = P.tickets + tile;
 #pragma unroll
@@ -543,9 +546,11 @@ bool streamable(const int16_t *X, int64_t s_r, int64_t s_k, int64_t rows, int64_
 template <int WR, int WC, int FM, int FN>
 hipError_t launch_tiles(S16Params P, bool a_kc, bool b_kc, hipStream_t s) {
   constexpr int BM = 16 * FM * WR, BN = 16 * FN * WC;
-  const int64_t tiles = (int64_t)P.tiles_m * P.tiles_n;
+  const int64_t tiles = (int64_t)P.walk.tiles_m * P.walk.tiles_n;
   if (tiles > ((int64_t)1 << 30)) return hipErrorInvalidValue;
   auto far = [](int64_t ld, int rows) { return (int64_t)(rows - 1) * ld + 2 * KB >= ((int64_t)1 << 32); };
+  P.per_range = P.nkt / P.splits;
+  P.longer = P.nkt % P.splits;
   P.wide_offsets = far(P.lda, a_kc ? BM : KB) || far(P.ldb, b_kc ? BN : KB);
   void (*kern)(S16Params) =
       a_kc ? (b_kc ? s16_kernel<WR, WC, FM, FN, true, true> : s16_kernel<WR, WC, FM, FN, true, false>)
@@ -613,8 +618,7 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
   if (!std::strcmp(tuning().variant, "s16_128")) large = true;  // pinned by tests and tuning runs
   if (!std::strcmp(tuning().variant, "s16_64")) large = false;
   const int64_t side = large ? 128 : 64, count = tiles(side);
-  P.tiles_m = (int)((p.m + side - 1) / side);
-  P.tiles_n = (int)((p.n + side - 1) / side);
+  P.walk = tile_walk((p.m + side - 1) / side, (p.n + side - 1) / side);
   // Ranges of k, where that gives a compute unit at most three workgroups (a wave alone on its SIMD
   // issues at half rate): at most four, eight of few tiles, sixteen of very few with a very long k,
   // each of enough blocks to pay for the exchange.  Measured through slots, us, with 1 / 2 / 4 / 8 / 16

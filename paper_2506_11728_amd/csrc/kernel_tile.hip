@@ -26,15 +26,13 @@
 // unsigned x is staged as the signed byte x - 128 (x ^ 0x80), and the epilogue
 // adds 128 * sum_p y(p) of the other (signed) operand, which the waves
 // accumulate from the fragments they already hold.  Exact modulo 2^32.
-#include "epilogue.h"
-#include "lds_layout.h"
-#include "mip_internal.h"
+#include "dma_common.h"
 
 namespace mip {
 
 struct TileParams {
   Problem p;
-  int tiles_m, tiles_n;
+  TileWalk walk;
   int kt_per_split;  // k blocks of 64 handled by one workgroup (blockIdx.y picks the range)
   int atomic;        // several workgroups add into the same tile of C (split k)
 };
@@ -50,6 +48,9 @@ __global__ __launch_bounds__(NTHREADS) void tile_kernel(TileParams tp) {
       2 * STAGE_BYTES > 4 * STORE_PATCH_BYTES ? 2 * STAGE_BYTES : 4 * STORE_PATCH_BYTES;
   __shared__ __attribute__((aligned(16))) uint8_t smem[SMEM_BYTES];
 
+  fetch_arguments(tp.walk, tp.kt_per_split, tp.atomic, tp.p.m, tp.p.n, tp.p.k, tp.p.A, tp.p.a_sm, tp.p.a_sk, tp.p.B,
+                  tp.p.b_sk, tp.p.b_sn, tp.p.C, tp.p.ldc, tp.p.a_unsigned, tp.p.b_unsigned, tp.p.accumulate,
+                  tp.p.out_float, tp.p.scale, tp.p.a_sb, tp.p.b_sb, tp.p.c_sb);
   Problem p = tp.p;
   {  // problem of the batch
     const int64_t z = blockIdx.z;
@@ -60,20 +61,8 @@ __global__ __launch_bounds__(NTHREADS) void tile_kernel(TileParams tp) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
 
-  // Workgroup -> tile.  Consecutive workgroup ids land on different XCDs (8 of
-  // them, each with its own L2), so give every XCD a contiguous run of tiles,
-  // and walk the tiles in groups of 8 tile-rows so that the workgroups resident
-  // on one XCD share A row-panels and B column-panels.
-  const int ntiles = tp.tiles_m * tp.tiles_n;
-  const int per_xcd = (ntiles + 7) / 8;
-  int lid = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (lid >= ntiles) return;
-  constexpr int GROUP = 8;
-  const int per_group = GROUP * tp.tiles_n;
-  const int first_m = (lid / per_group) * GROUP;
-  const int gsz = tp.tiles_m - first_m < GROUP ? tp.tiles_m - first_m : GROUP;
-  const int tm = first_m + (lid % per_group) % gsz;
-  const int tn = (lid % per_group) / gsz;
+  int tm, tn;
+  if (!tile_of_workgroup(tp.walk, &tm, &tn)) return;
 
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
   const uint8_t *A = static_cast<const uint8_t *>(p.A);
@@ -199,8 +188,7 @@ static hipError_t launch_cfg(const Problem &p, int splits, hipStream_t s) {
   tp.p = p;
   int64_t tiles_m = (p.m + BM - 1) / BM, tiles_n = (p.n + BN - 1) / BN;
   if (tiles_m * tiles_n > (int64_t)1 << 30) return hipErrorInvalidValue;
-  tp.tiles_m = (int)tiles_m;
-  tp.tiles_n = (int)tiles_n;
+  tp.walk = tile_walk(tiles_m, tiles_n);
   const int64_t nkt = (p.k + BK - 1) / BK;
   if (splits < 1 || p.out_float) splits = 1;  // float sums must not be combined in arbitrary order
   if (splits > nkt) splits = (int)nkt;
@@ -213,7 +201,7 @@ static hipError_t launch_cfg(const Problem &p, int splits, hipStream_t s) {
     hipError_t e = launch_fill_zero(p, s);
     if (e != hipSuccess) return e;
   }
-  int ntiles = tp.tiles_m * tp.tiles_n;
+  const int ntiles = (int)(tiles_m * tiles_n);
   dim3 grid((unsigned)(((ntiles + 7) / 8) * 8), (unsigned)splits, (unsigned)p.batch);
   const bool a_kc = p.a_sk == 1, b_kc = p.b_sk == 1;
   if (a_kc && b_kc) hipLaunchKernelGGL((tile_kernel<BM, BN, true, true>), grid, dim3(NTHREADS), 0, s, tp);

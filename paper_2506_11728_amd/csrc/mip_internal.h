@@ -57,6 +57,32 @@ struct Problem {
   bool packed_weights = false;  // one operand is the library's packed weights
 };
 
+// Division by a number that the host knows: n / d = high word of n * inv, exact for every n <= most
+// (inv * d exceeds 2^32 by less than d).  inv == 0: d == 1, or no such inv; the kernel divides.
+struct Divisor {
+  unsigned d, inv;
+};
+inline Divisor divisor(int64_t d, int64_t most) {
+  Divisor r{(unsigned)d, 0};
+  if (d > 1 && d < ((int64_t)1 << 31) && most < ((int64_t)1 << 32)) {
+    const uint64_t inv = (((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d;
+    const uint64_t over = inv * (uint64_t)d - ((uint64_t)1 << 32);  // below d
+    if (over == 0 || (uint64_t)most < ((uint64_t)1 << 32) / over) r.inv = (unsigned)inv;
+  }
+  return r;
+}
+
+// The tiles of a product in the order in which workgroups take them (tile_of_workgroup).
+struct TileWalk {
+  int tiles_m, tiles_n;
+  Divisor group, last;  // by the tiles of eight tile rows, and by the rows of the last, incomplete such group
+};
+inline TileWalk tile_walk(int64_t tiles_m, int64_t tiles_n) {
+  const int64_t rest = tiles_m % 8 ? tiles_m % 8 : 8;
+  const int64_t group = tiles_n < ((int64_t)1 << 27) ? 8 * tiles_n : ((int64_t)1 << 30) + 1;  // (at most 2^30 tiles)
+  return {(int)tiles_m, (int)tiles_n, divisor(group, tiles_m * tiles_n), divisor(rest, rest * tiles_n)};
+}
+
 // Workgroup tile of the MFMA kernels (rows x columns of C).
 enum Shape {
   SHAPE_256, SHAPE_128, SHAPE_64, SHAPE_64X256, SHAPE_256X64, SHAPE_64X128, SHAPE_128X64, SHAPE_COUNT,
