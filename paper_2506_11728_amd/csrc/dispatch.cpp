@@ -35,6 +35,33 @@ hipError_t launch_dma(const Problem &p, Shape shape, int splits, hipStream_t s) 
   }
 }
 
+hipError_t launch_wave_32x32(const Problem &p, bool streamed, hipStream_t s);
+hipError_t launch_wave_32x64(const Problem &p, bool streamed, hipStream_t s);
+hipError_t launch_wave_64x64(const Problem &p, bool streamed, hipStream_t s);
+
+hipError_t launch_wave(const Problem &p, Wave wave, bool streamed, hipStream_t s) {
+  switch (wave) {
+    case WAVE_32: return launch_wave_32x32(p, streamed, s);
+    case WAVE_32X64: return launch_wave_32x64(p, streamed, s);
+    case WAVE_64: return launch_wave_64x64(p, streamed, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+static bool wave_streamed_eligible(const Problem &p) {
+  const int64_t lda = p.a_sk == 1 ? p.a_sm : p.a_sk, ldb = p.b_sk == 1 ? p.b_sn : p.b_sk;
+  return dma_eligible(p, SHAPE_64) && (p.conv || 128 * lda < ((int64_t)1 << 31)) && 128 * ldb < ((int64_t)1 << 31);
+}
+
+// Sixteen bytes along k or, where the other index is contiguous, along that: pieces at an edge are fetched
+// from further inside (wave_tile.h).
+bool wave_staged_eligible(const Problem &p) {
+  if (p.conv || p.k < 1) return false;
+  if ((p.a_sk == 1 ? p.k : p.m) < 16 || (p.b_sk == 1 ? p.k : p.n) < 16) return false;
+  const int64_t lda = p.a_sk == 1 ? p.a_sm : p.a_sk, ldb = p.b_sk == 1 ? p.b_sn : p.b_sk;
+  return 128 * lda < ((int64_t)1 << 31) && 128 * ldb < ((int64_t)1 << 31);
+}
+
 static const char *const kShapeNames[SHAPE_COUNT] = {"256", "128", "64", "64x256", "256x64",
                                                      "64x128", "128x64"};
 static const int64_t kShapeRows[SHAPE_COUNT] = {256, 128, 64, 64, 256, 64, 128};
@@ -71,6 +98,7 @@ const char *plan_name(const Plan &plan) {
 // "dma128k128" (the same kernel on 128 x 128 tiles), "dma128k128split" (its general form with k
 // ranges), "dma256k128ragged", "dma256x192k128", "dma192x256k128", "dma192k128" (the general form on
 // tiles of those sides), "slab16" / "slab32" / "slab64" (the skinny-m kernel with that slab width),
+// "wave32" / "wave32x64" / "wave64" (tiles whose waves split k),
 // "tile<shape>" (register-staged) or "dma<shape>" (direct-to-LDS) with <shape> one of
 // 256, 128, 64, 64x256, 256x64, 64x128, 128x64.  A dma variant only applies to problems it is
 // eligible for; others fall back to the staged kernel of the same shape.
@@ -129,6 +157,15 @@ static bool forced_plan(const Problem &p, Plan *plan) {
     *plan = {KIND_SLAB, SHAPE_64, nt};
     return true;
   }
+  static const struct { const char *name; Wave wave; } waves[3] = {
+      {"wave32", WAVE_32}, {"wave32x64", WAVE_32X64}, {"wave64", WAVE_64}};
+  for (const auto &v : waves)
+    if (!std::strcmp(e, v.name)) {
+      const bool streamed = wave_streamed_eligible(p);
+      if (!streamed && (v.wave == WAVE_64 || !wave_staged_eligible(p))) return false;
+      *plan = {streamed ? KIND_DMA : KIND_STAGED, SHAPE_64, 1, v.wave};
+      return true;
+    }
   const bool want_dma = !std::strncmp(e, "dma", 3);
   if (!want_dma && std::strncmp(e, "tile", 4)) return false;
   const char *shape = e + (want_dma ? 3 : 4);
@@ -181,6 +218,53 @@ int64_t compute_units() {
 static int64_t tile_count(const Problem &p, Shape s) {
   return ((p.m + kShapeRows[s] - 1) / kShapeRows[s]) * ((p.n + kShapeCols[s] - 1) / kShapeCols[s]) *
          (p.batch > 1 ? p.batch : 1);
+}
+
+// A 64 x 64 tile plan of few tiles: the form whose waves split k, where that is the faster one.  One workgroup
+// of it goes through k eight steps of 128 at a time, so that a chain of k blocks that takes a 64 x 64
+// tile 0.115 us per 64 takes a few microseconds whatever its length, without a workspace and a second
+// launch; but a workgroup has a compute unit to itself, and what it takes in per multiply-accumulate
+// grows as the tile shrinks, most for a strided operand, whose pieces of a row are 32 or 64 bytes.
+// So: the smallest tile of which there is one round, for a k that is long enough, and no longer than what the
+// 64 x 64 tiles need that can split k over workgroups (through atomics, cheapest into an int32 C that needs no
+// zero fill, or through slots).
+// Measured over 1500 aligned products of 1 to 400 tiles of 64 x 64 (k = 64 to 8192), the rule takes 0.88 of
+// the time without it, the best choice each time 0.86; over 1200 unaligned ones 0.63 and 0.59.
+// us, before and after: (512, 512, 2048) k-contiguous 6.5 -> 4.2, (256, 256, 1024) 4.4 -> 3.7, (1568, 512, 4608)
+// u8 to int8 16.2 -> 12.0, (64, 4096, 11008) u8 packed 16.2 -> 12.8, row-major B (1024, 512, 4096) 12.3 -> 9.9;
+// a 3 x 3 convolution of 7 x 7 x 512 at batch 8 19.7 -> 7.4; unaligned (32, 256, 3600) to int8 35 -> 12.9,
+// (42, 2368, 2112) 22.9 -> 6.5, (1024, 70, 1024) 18.2 -> 4.8, (459, 1024, 836) packed before 7.9 -> 6.1.
+// On the other side of the lines: (1024, 1024, 1024) 5.1 on 64 x 64 tiles and 6.6, (1024, 512, 1024) row-major 4.75
+// and 5.1, (304, 208, 6144) column-major A 16.8 packed and 21.
+static Wave wave_form(const Problem &p, bool streamed) {
+  if (p.k < 1 || (p.batch > 1 && p.out_float == 2)) return WAVE_NONE;
+  const int64_t cus = compute_units(), k = p.k, batch = p.batch > 1 ? p.batch : 1;
+  auto tiles = [&](int64_t bm, int64_t bn) { return ((p.m + bm - 1) / bm) * ((p.n + bn - 1) / bn) * batch; };
+  const int64_t short_side = p.m < p.n ? p.m : p.n, target = short_side <= 16 ? 2 * cus : cus;
+  const bool adds = p.accumulate && !p.out_float;
+  const bool may_split = (!p.out_float || (p.ws && streamed)) &&
+                         (p.accumulate || p.out_float ? 2 * tiles(64, 64) <= target : 2 * tiles(64, 64) < target);
+  const int64_t any = INT64_MAX / 4;
+  if (streamed) {
+    if (!wave_streamed_eligible(p)) return WAVE_NONE;
+    const int strided = (p.a_sk != 1) + (p.b_sk != 1);
+    static const int64_t adding[3] = {4096, 2560, 1792}, other[3] = {any, 4096, 3072};
+    const int64_t most = !may_split ? any : (adds ? adding : other)[strided];
+    if (tiles(32, 32) <= cus) return k < most && (!p.conv || k >= 512) ? WAVE_32 : WAVE_NONE;
+    if (tiles(32, 64) <= cus && p.a_sk == 1) return k >= (strided ? 1536 : 1024) && k < 2 * most ? WAVE_32X64 : WAVE_NONE;
+    return tiles(64, 64) <= cus && strided == 0 && k >= (p.conv ? 2048 : 2304) && !adds ? WAVE_64 : WAVE_NONE;
+  }
+  if (!wave_staged_eligible(p) || tuning().pack > 0) return WAVE_NONE;
+  // (with a workspace, larger products are packed)
+  const bool packable = packing_serves(p);
+  int64_t most = !may_split ? any : (adds ? 1536 : 4096);
+  if (packable && most > 4096) most = 4096;
+  // (both operands strided and a short k: packed, a choice that a test names; (300, 200, 333) 5.8 us, 4.3 here)
+  if (packable && p.a_sk != 1 && p.b_sk != 1 && k < 512) return WAVE_NONE;
+  if (tiles(32, 32) <= cus) return k < most ? WAVE_32 : WAVE_NONE;
+  if (packable) return WAVE_NONE;
+  if (tiles(32, 64) <= cus && k < most) return WAVE_32X64;
+  return tiles(32, 32) <= 3 * cus && k >= 512 ? WAVE_32 : WAVE_NONE;
 }
 
 size_t splitk_slot_bytes(const Problem &p, const Plan &plan) {
@@ -453,7 +537,10 @@ Plan choose_plan(const Problem &p) {
     // 8191 x 8193 x 8195 with such an A 4570 us on 128 x 64 tiles, 2570 on 64 x 128.
     else plan = {KIND_STAGED, sh == SHAPE_256 || sh == SHAPE_128 ? (p.a_sk == 1 ? SHAPE_128X64 : SHAPE_64X128) : sh, 1};
   }
-  if (plan.kind == KIND_STAGED || plan.kind == KIND_DMA) {
+  const bool pinned = *tuning().variant || forced_splits() > 0;
+  if (!pinned && (plan.kind == KIND_STAGED || plan.kind == KIND_DMA) && plan.shape == SHAPE_64)
+    plan.wave = wave_form(p, plan.kind == KIND_DMA);
+  if ((plan.kind == KIND_STAGED || plan.kind == KIND_DMA) && plan.wave == WAVE_NONE) {
     // float sums are not combined out of order: a float output splits k only through slots of
     // integer partial sums, which need room in a workspace
     const bool may_split = !p.out_float || (p.ws != nullptr && plan.kind == KIND_DMA);

@@ -31,6 +31,19 @@ __device__ __forceinline__ v4i load16(const uint8_t *p) {
   return reinterpret_cast<const unaligned_v4i *>(p)->v;
 }
 
+// v without its first n bytes (0 or more), zeros behind what is left of it
+__device__ __forceinline__ v4i shifted_down(v4i v, int n) {
+  uint64_t lo = (uint32_t)v[0] | (uint64_t)(uint32_t)v[1] << 32, hi = (uint32_t)v[2] | (uint64_t)(uint32_t)v[3] << 32;
+  if (n >= 8) {
+    lo = n >= 16 ? 0 : hi >> (8 * (n - 8));
+    hi = 0;
+  } else if (n > 0) {
+    lo = lo >> (8 * n) | hi << (64 - 8 * n);
+    hi >>= 8 * n;
+  }
+  return v4i{(int)lo, (int)(lo >> 32), (int)hi, (int)(hi >> 32)};
+}
+
 // One operand block in LDS.
 // KD is the depth of the block along k (64 or 128).
 //   KC (k contiguous in memory: row-major A, column-major B):

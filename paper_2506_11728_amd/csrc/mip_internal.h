@@ -103,10 +103,14 @@ enum Kind {
   KIND_SLAB
 };
 
+// The form of a 64 x 64 tile plan (KIND_DMA or KIND_STAGED) whose waves split k (wave_tile.h), by its tiles.
+enum Wave { WAVE_NONE, WAVE_32, WAVE_32X64, WAVE_64 };
+
 struct Plan {
   Kind kind;
   Shape shape;  // of tile kernels
   int splits;   // k ranges worked on by separate workgroups (1 = no split); KIND_SLAB: the width
+  Wave wave = WAVE_NONE;
 };
 
 Plan choose_plan(const Problem &p);
@@ -213,5 +217,12 @@ size_t splitk_slot_bytes(const Problem &p, const Plan &plan);
 
 bool dma_eligible(const Problem &p, Shape shape);
 hipError_t launch_dma(const Problem &p, Shape shape, int splits, hipStream_t s);
+
+// streamed: both operands by direct loads (dma_eligible), else any alignment (wave_staged_eligible).
+bool wave_staged_eligible(const Problem &p);
+hipError_t launch_wave(const Problem &p, Wave wave, bool streamed, hipStream_t s);
+
+// Whether unaligned operands of this product are worth packing and Problem::ws has room for it.
+bool packing_serves(const Problem &p);
 
 }  // namespace mip

@@ -94,6 +94,12 @@ static bool packing_pays(const Problem &p, const mip::Plan &plan) {
   return packing_size_ok(p.m, p.n, p.k);
 }
 
+bool packing_serves(const Problem &p) {
+  // (up to 15 bytes of the workspace are skipped ahead of Problem::ws)
+  return p.ws && p.batch <= 1 && !p.conv && tuning().pack >= 0 && packing_size_ok(p.m, p.n, p.k) &&
+         p.ws_bytes + 15 >= packed_bytes(p.m, p.n, p.k);
+}
+
 size_t packed_route_bytes(const Problem &p) {
   return packing_pays(p, choose_plan(p)) ? packed_bytes(p.m, p.n, p.k) : 0;
 }
@@ -131,7 +137,7 @@ int run_gemm(int a_unsigned, int b_unsigned, int out_float, float scale, int64_t
   p.ws = ws_bytes ? ws : nullptr;
   p.ws_bytes = ws_bytes;
   mip::Plan plan = mip::choose_plan(p);
-  if (packing_pays(p, plan) && workspace && workspace_bytes >= packed_bytes(p.m, p.n, p.k)) {
+  if (plan.wave == WAVE_NONE && packing_pays(p, plan) && workspace && workspace_bytes >= packed_bytes(p.m, p.n, p.k)) {
     // Pack A and Pack B (paper Section 4.1) into aligned, k-contiguous buffers with the k
     // tail zeroed, so that the direct-to-LDS kernels can stream them
     const int64_t kp = padded_k(p.k);
@@ -157,6 +163,7 @@ int run_gemm(int a_unsigned, int b_unsigned, int out_float, float scale, int64_t
 }
 
 hipError_t launch_plan(const Problem &p, const Plan &plan, hipStream_t s) {
+  if (plan.wave != WAVE_NONE) return launch_wave(p, plan.wave, plan.kind == KIND_DMA, s);
   switch (plan.kind) {
     case KIND_NONE: return hipSuccess;
     case KIND_FILL: return launch_fill_zero(p, s);
@@ -534,8 +541,10 @@ const char *mipgemm_variant_name_with_workspace(int64_t m, int64_t n, int64_t k,
                                   orderB, reinterpret_cast<int32_t *>(uintptr_t(4096)), ldc,
                                   orderC, MIPGEMM_OVERWRITE, nullptr, 0, &p);
   if (rc != 0) return "invalid";
+  p.ws = const_cast<void *>(fake);
+  p.ws_bytes = ~size_t(0) / 2;
   const mip::Plan plan = mip::choose_plan(p);
-  if (!mip::packing_pays(p, plan)) return mip::plan_name(plan);
+  if (plan.wave != mip::WAVE_NONE || !mip::packing_pays(p, plan)) return mip::plan_name(plan);
   // the plan for the packed operands: aligned, k-contiguous, k padded
   const int64_t kp = mip::padded_k(p.k);
   p.A = p.B = reinterpret_cast<const void *>(uintptr_t(4096));

@@ -193,7 +193,7 @@ static int run_conv(int out_float, float scale, int64_t b, int64_t hi, int64_t w
   const Route route = conv_route(c, p, &plan);
   p.conv = &c.geom;
   p.ksum = filter_sums;  // the filters are the signed B of the lowered product: one sum per column
-  if (route == ROUTE_TILES) return static_cast<int>(mip::launch_dma(p, plan.shape, plan.splits, s));
+  if (route == ROUTE_TILES) return static_cast<int>(mip::launch_plan(p, plan, s));
   if (route == ROUTE_ROWS) return static_cast<int>(mip::launch_conv_rows(p, s));
   const size_t need = written_out_bytes(c, co);
   if (!workspace) return -14;
