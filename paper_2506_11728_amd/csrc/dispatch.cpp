@@ -248,8 +248,9 @@ static Wave wave_form(const Problem &p, bool streamed) {
   if (streamed) {
     if (!wave_streamed_eligible(p)) return WAVE_NONE;
     const int strided = (p.a_sk != 1) + (p.b_sk != 1);
-    static const int64_t adding[3] = {4096, 2560, 1792}, other[3] = {any, 4096, 3072};
-    const int64_t most = !may_split ? any : (adds ? adding : other)[strided];
+    // (row-major (192, 448, 3904), 84 tiles of 32 x 32: 8.2 us on 21 of 64 x 64 in four ranges, 10.0 here)
+    static const int64_t adding[3] = {4096, 2560, 1792}, few[3] = {any, 4096, 3072}, other[3] = {any, 3072, 2048};
+    const int64_t most = !may_split ? any : (adds ? adding : (4 * tiles(32, 32) <= cus ? few : other))[strided];
     if (tiles(32, 32) <= cus) return k < most && (!p.conv || k >= 512) ? WAVE_32 : WAVE_NONE;
     if (tiles(32, 64) <= cus && p.a_sk == 1) return k >= (strided ? 1536 : 1024) && k < 2 * most ? WAVE_32X64 : WAVE_NONE;
     return tiles(64, 64) <= cus && strided == 0 && k >= (p.conv ? 2048 : 2304) && !adds ? WAVE_64 : WAVE_NONE;

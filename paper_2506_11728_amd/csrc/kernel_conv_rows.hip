@@ -14,9 +14,11 @@
 //     (a few KB; zero where outside the image, every byte turned into the signed x - 128
 //     on the way), into one of two stages, one tile ahead of the computation;
 //   * its four compute waves build their operand fragments (32 positions x 32 k each)
-//     from those segments: 16 consecutive k are at most two runs of bytes, fetched as two
-//     16-byte LDS reads at whatever alignment and merged by a byte mask (filter rows
-//     shorter than 16 bytes: byte by byte),
+//     from those segments.  Where k is padded so that every filter row takes whole 16-byte
+//     pieces (zeros in the filter meet whatever the image holds there), a
+//     fragment is one 16-byte LDS read at whatever alignment; else 16 consecutive k are at most two runs of
+//     bytes, fetched as two such reads and merged by a byte mask (filter rows shorter than 16
+//     bytes: byte by byte),
 //   * multiply them with the filter fragments, laid out in LDS in register order once at
 //     the workgroup's start (64 filters per workgroup, grid.y walks c_o),
 //   * and write their 32 x 64 patches of O, starting the accumulators from the unsigned
@@ -47,7 +49,8 @@ struct RowsParams {
   ConvGeom G;
   int hf;
   int k;              // hf * wf * ci
-  int ksteps;         // k in steps of 32, rounded up
+  int ksteps;         // k (padded: the pieces) in steps of 32, rounded up
+  int row_pieces;     // padded: 16-byte pieces of a filter row
   int n;              // c_o
   int tiles_per_row;  // tiles along one output row
   int64_t tiles;      // b * ho * tiles_per_row
@@ -102,7 +105,10 @@ __device__ __forceinline__ void store_rows_via_lds(const v16i (&acc)[1][2], int3
 }
 
 // TO_FLOAT, ACCUMULATE: what the write-back does, fixed at compile time.
-template <bool TO_FLOAT, bool ACCUMULATE>
+// PADDED: filter rows in whole pieces.  The 7 x 7 x 3 filters of a network's first layer take seven steps instead
+// of five, but one unaligned LDS read instead of two and none of some thirty mask instructions each:
+// @STEM@.
+template <bool TO_FLOAT, bool ACCUMULATE, bool PADDED>
 __global__ __launch_bounds__(NTHREADS_ROWS) void conv_rows_kernel(RowsParams P) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   // two image stages, the filter fragments, then the small tables and the write-back patches
@@ -121,6 +127,19 @@ __global__ __launch_bounds__(NTHREADS_ROWS) void conv_rows_kernel(RowsParams P) 
   for (int slot = tid; slot < P.ksteps * 128; slot += NTHREADS_ROWS) {
     const int l = slot & 63, j = (slot >> 6) & 1, ks = slot >> 7;
     const int co = n0 + 32 * j + (l & 31);
+    if constexpr (PADDED) {
+      const int e = 2 * ks + (l >> 5), y = e / P.row_pieces, at = 16 * (e - y * P.row_pieces);
+      const int have = y < P.hf && co < P.n ? (wfci - at < 16 ? wfci - at : 16) : 0;
+      const uint8_t *piece = P.F + (int64_t)(co < P.n ? co : P.n - 1) * P.k + (y < P.hf ? y * wfci + at : 0);
+      v4i f = {0, 0, 0, 0};
+#pragma unroll
+      for (int b = 0; b < 16; ++b) {
+        const uint32_t x = piece[b < have ? b : 0];
+        f[b >> 2] |= (int)((b < have ? x : 0u) << (8 * (b & 3)));
+      }
+      ffrag[slot] = f;
+      continue;
+    }
     const int kk0 = 32 * ks + 16 * (l >> 5);
     // every load unconditional (clamped into the filter tensor, zeroed afterwards), so that
     // they are all in flight together
@@ -166,10 +185,13 @@ __global__ __launch_bounds__(NTHREADS_ROWS) void conv_rows_kernel(RowsParams P) 
   }
   // where the 16 bytes k = 32 ks + 16 h .. + 15 of a position start in the stage (first run:
   // offset and length; second run: offset less the first run's length, relative to the first)
-  if (tid >= 64 && tid < 64 + 2 * P.ksteps && wfci >= 16) {
+  if (tid >= 64 && tid < 64 + 2 * P.ksteps && (PADDED || wfci >= 16)) {
     const int e = tid - 64, kk0 = 16 * e;  // e = 2 ks + h
     v4i run = {0, 16, 0, 0};
-    if (kk0 < P.k) {
+    if (PADDED) {
+      const int y = e / P.row_pieces;
+      run[0] = y < P.hf ? y * P.row_bytes + 16 * (e - y * P.row_pieces) : 0;
+    } else if (kk0 < P.k) {
       const int y0 = kk0 / wfci, r = kk0 - y0 * wfci;
       run[0] = y0 * P.row_bytes + r;
       run[1] = wfci - r;
@@ -290,7 +312,7 @@ __global__ __launch_bounds__(NTHREADS_ROWS) void conv_rows_kernel(RowsParams P) 
     };
     for (int ks = 0; ks < P.ksteps; ++ks) {
       const int kk0 = 32 * ks + 16 * (lane >> 5);
-      const v4i fa = wfci >= 16 ? gather_runs(ks) : gather_bytes(kk0);
+      const v4i fa = PADDED ? load16(img + runs[2 * ks + (lane >> 5)][0] + lane_base) : wfci >= 16 ? gather_runs(ks) : gather_bytes(kk0);
       const v4i f0 = ffrag[(ks * 2) * 64 + lane], f1 = ffrag[(ks * 2 + 1) * 64 + lane];
       acc[0][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0, fa, acc[0][0], 0, 0, 0);
       acc[0][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f1, fa, acc[0][1], 0, 0, 0);
@@ -371,6 +393,12 @@ bool fill_params(const Problem &p, RowsParams *out) {
   P.hf = (int)hf;
   P.k = (int)p.k;
   P.ksteps = (int)ksteps;
+  P.row_pieces = 0;
+  const int64_t row_pieces = (wfci + 15) / 16, padded_steps = (hf * row_pieces + 1) / 2;
+  if (padded_steps <= 32 && (padded_steps <= 2 * ksteps || wfci < 16) && 2 * stage + padded_steps * 2048 + FIXED_LDS <= MAX_LDS) {
+    P.row_pieces = (int)row_pieces;
+    P.ksteps = (int)padded_steps;
+  }
   P.n = (int)p.n;
   P.tiles_per_row = (G.wo + TP - 1) / TP;
   P.tiles = p.m / G.wo * P.tiles_per_row;  // m = b * ho * wo
@@ -404,13 +432,15 @@ hipError_t launch_conv_rows(const Problem &p, hipStream_t s) {
   dim3 grid((unsigned)wgs, (unsigned)((P.n + TN - 1) / TN), 1);
   const size_t lds = 2 * (size_t)P.stage_bytes + (size_t)P.ksteps * 2048 + FIXED_LDS;
   const dim3 block(NTHREADS_ROWS);
-  if (P.out_float == 2) {  // (the integer instance: its int8 branch is taken at run time)
-    if (P.accumulate) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((conv_rows_kernel<false, false>), grid, block, lds, s, P);
-  } else if (P.out_float && P.accumulate) hipLaunchKernelGGL((conv_rows_kernel<true, true>), grid, block, lds, s, P);
-  else if (P.out_float) hipLaunchKernelGGL((conv_rows_kernel<true, false>), grid, block, lds, s, P);
-  else if (P.accumulate) hipLaunchKernelGGL((conv_rows_kernel<false, true>), grid, block, lds, s, P);
-  else hipLaunchKernelGGL((conv_rows_kernel<false, false>), grid, block, lds, s, P);
+  if (P.out_float == 2 && P.accumulate) return hipErrorInvalidValue;
+  // (an int8 output: the integer instance, whose int8 branch is taken at run time)
+  const bool to_float = P.out_float == 1, padded = P.row_pieces > 0;
+  void (*kern)(RowsParams) =
+      padded ? (to_float ? (P.accumulate ? conv_rows_kernel<true, true, true> : conv_rows_kernel<true, false, true>)
+                         : (P.accumulate ? conv_rows_kernel<false, true, true> : conv_rows_kernel<false, false, true>))
+             : (to_float ? (P.accumulate ? conv_rows_kernel<true, true, false> : conv_rows_kernel<true, false, false>)
+                         : (P.accumulate ? conv_rows_kernel<false, true, false> : conv_rows_kernel<false, false, false>));
+  hipLaunchKernelGGL(kern, grid, block, lds, s, P);
   return hipGetLastError();
 }
 
