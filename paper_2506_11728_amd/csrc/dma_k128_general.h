@@ -57,8 +57,7 @@ hipError_t launch_general(const Problem &p, int splits, hipStream_t s) {
 #undef MIP_PICK
   hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, grid, dim3(NTHREADS), lds, s, P);
-  return hipGetLastError();
+  return launch_with(reinterpret_cast<const void *>(kern), grid, NTHREADS, lds, s, &P);
 }
 
 }  // namespace

@@ -47,9 +47,11 @@ struct DmaTileParams {
   int out_float;          // 1 dequantised output: float(sum) * scale; 2 requantised int8 output
   float scale;
   const int32_t *ksum;    // UNS 3 and 4: the k sums of the signed operand (see Problem::ksum)
-  ConvGeom conv;          // CONV kernels only
-  Divisor per_image, per_row;  // by the output positions of an image and of a row of one
   int64_t a_sb, b_sb, c_sb;  // byte / element offsets of problem z of a batch (blockIdx.z)
+};
+struct DmaConvParams : DmaTileParams {
+  ConvGeom conv;
+  Divisor per_image, per_row;  // by the output positions of an image and of a row of one
 };
 
 // what a tap outside the image contributes
@@ -59,7 +61,7 @@ static __device__ __attribute__((aligned(16))) const uint8_t conv_zero_block[16]
 // of the signed operand read from P.ksum instead of being accumulated from the fragments
 // (with split k by the first range alone).
 template <int BM, int BN, bool A_KC, bool B_KC, int UNS, bool CONV = false>
-__global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(DmaTileParams P) {
+__global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<CONV, DmaConvParams, DmaTileParams> P) {
   constexpr bool FLIP_A = UNS == 1 || UNS == 3, FLIP_B = UNS == 2 || UNS == 4;
   constexpr bool SUM_A = UNS == 2, SUM_B = UNS == 1;
   static_assert(!CONV || (A_KC && B_KC), "the lowered matrix and the filters are k-contiguous");
@@ -386,7 +388,7 @@ bool dma_tile_eligible_for(const Problem &p) {
 
 template <int BM, int BN>
 hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
-  DmaTileParams P;
+  DmaConvParams P;
   const bool a_kc = p.a_sk == 1, b_kc = p.b_sk == 1;
   P.A = static_cast<const uint8_t *>(p.A);
   P.B = static_cast<const uint8_t *>(p.B);
@@ -469,6 +471,7 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   else if (b_kc) MIP_PICK(false, true);
   else MIP_PICK(false, false);
 #undef MIP_PICK
+  const void *kernel = reinterpret_cast<const void *>(kern);
   if (p.conv) {
     P.conv = *p.conv;
     P.per_image = divisor((int64_t)p.conv->ho * p.conv->wo, p.m);
@@ -476,16 +479,12 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
     // (the gathered matrix is the unsigned A, the filters the signed, k-contiguous B)
     const bool filter_sums = p.ksum != nullptr;
     P.ksum = filter_sums ? p.ksum : nullptr;
-    kern = filter_sums ? dma_tile_kernel<BM, BN, true, true, 3, true> : dma_tile_kernel<BM, BN, true, true, 1, true>;
-  } else {
-    P.conv = ConvGeom{};
+    void (*gather)(DmaConvParams) =
+        filter_sums ? dma_tile_kernel<BM, BN, true, true, 3, true> : dma_tile_kernel<BM, BN, true, true, 1, true>;
+    kernel = reinterpret_cast<const void *>(gather);
   }
-  {
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kern, grid, dim3(NTHREADS), lds, s, P);
-  return hipGetLastError();
+  const hipError_t e = allow_dynamic_lds(kernel, lds);
+  return e != hipSuccess ? e : launch_with(kernel, grid, NTHREADS, lds, s, &P);
 }
 
 }  // namespace mip

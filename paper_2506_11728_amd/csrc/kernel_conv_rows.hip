@@ -431,7 +431,6 @@ hipError_t launch_conv_rows(const Problem &p, hipStream_t s) {
   wgs = (P.tiles + per - 1) / per;
   dim3 grid((unsigned)wgs, (unsigned)((P.n + TN - 1) / TN), 1);
   const size_t lds = 2 * (size_t)P.stage_bytes + (size_t)P.ksteps * 2048 + FIXED_LDS;
-  const dim3 block(NTHREADS_ROWS);
   if (P.out_float == 2 && P.accumulate) return hipErrorInvalidValue;
   // (an int8 output: the integer instance, whose int8 branch is taken at run time)
   const bool to_float = P.out_float == 1, padded = P.row_pieces > 0;
@@ -440,8 +439,7 @@ hipError_t launch_conv_rows(const Problem &p, hipStream_t s) {
                          : (P.accumulate ? conv_rows_kernel<false, true, true> : conv_rows_kernel<false, false, true>))
              : (to_float ? (P.accumulate ? conv_rows_kernel<true, true, false> : conv_rows_kernel<true, false, false>)
                          : (P.accumulate ? conv_rows_kernel<false, true, false> : conv_rows_kernel<false, false, false>));
-  hipLaunchKernelGGL(kern, grid, block, lds, s, P);
-  return hipGetLastError();
+  return launch_with(reinterpret_cast<const void *>(kern), grid, NTHREADS_ROWS, lds, s, &P);
 }
 
 }  // namespace mip

@@ -80,8 +80,7 @@ hipError_t launch_for(const Problem &p, hipStream_t s, unsigned long long *clock
 #undef MIP_PICK
   hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, grid, dim3(NTHREADS), lds, s, P);
-  return hipGetLastError();
+  return launch_with(reinterpret_cast<const void *>(kern), grid, NTHREADS, lds, s, &P);
 }
 
 }  // namespace

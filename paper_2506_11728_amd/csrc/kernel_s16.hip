@@ -558,8 +558,8 @@ hipError_t launch_tiles(S16Params P, bool a_kc, bool b_kc, hipStream_t s) {
   const size_t lds = (size_t)STAGES * (BM + BN) * 2 * KB;
   hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + 7) / 8 * 8), (unsigned)P.splits), dim3(64 * WR * WC), lds, s, P);
-  return hipGetLastError();
+  return launch_with(reinterpret_cast<const void *>(kern), dim3((unsigned)((tiles + 7) / 8 * 8), (unsigned)P.splits), 64 * WR * WC,
+                     lds, s, &P);
 }
 
 }  // namespace

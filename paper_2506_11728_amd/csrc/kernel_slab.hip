@@ -374,8 +374,7 @@ hipError_t launch_slab(const Problem &p, int nt, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   dim3 grid((unsigned)(((P.tiles + 7) / 8) * 8));
-  hipLaunchKernelGGL(kern, grid, dim3(64 * waves), lds, s, P);
-  return hipGetLastError();
+  return launch_with(reinterpret_cast<const void *>(kern), grid, 64 * waves, lds, s, &P);
 }
 
 }  // namespace mip

@@ -204,11 +204,9 @@ static hipError_t launch_cfg(const Problem &p, int splits, hipStream_t s) {
   const int ntiles = (int)(tiles_m * tiles_n);
   dim3 grid((unsigned)(((ntiles + 7) / 8) * 8), (unsigned)splits, (unsigned)p.batch);
   const bool a_kc = p.a_sk == 1, b_kc = p.b_sk == 1;
-  if (a_kc && b_kc) hipLaunchKernelGGL((tile_kernel<BM, BN, true, true>), grid, dim3(NTHREADS), 0, s, tp);
-  else if (a_kc) hipLaunchKernelGGL((tile_kernel<BM, BN, true, false>), grid, dim3(NTHREADS), 0, s, tp);
-  else if (b_kc) hipLaunchKernelGGL((tile_kernel<BM, BN, false, true>), grid, dim3(NTHREADS), 0, s, tp);
-  else hipLaunchKernelGGL((tile_kernel<BM, BN, false, false>), grid, dim3(NTHREADS), 0, s, tp);
-  return hipGetLastError();
+  void (*kern)(TileParams) = a_kc ? (b_kc ? tile_kernel<BM, BN, true, true> : tile_kernel<BM, BN, true, false>)
+                                  : (b_kc ? tile_kernel<BM, BN, false, true> : tile_kernel<BM, BN, false, false>);
+  return launch_with(reinterpret_cast<const void *>(kern), grid, NTHREADS, 0, s, &tp);
 }
 
 hipError_t launch_staged(const Problem &p, Shape shape, int splits, hipStream_t s) {

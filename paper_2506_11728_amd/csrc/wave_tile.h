@@ -19,7 +19,9 @@ struct WaveTileParams {
   float scale;
   const int32_t *ksum;  // not null: the k sums of the signed operand (see Problem::ksum)
   int64_t a_sb, b_sb, c_sb;
-  ConvGeom conv;  // GATHERED only
+};
+struct WaveConvParams : WaveTileParams {
+  ConvGeom conv;
   // by the output positions of an image and of a row of one, the 64-channel blocks of a tap, and the taps of a filter row
   Divisor per_image, per_row, per_tap, per_filter_row;
 };
@@ -82,7 +84,7 @@ struct WaveOperand {
 // MT, NT: blocks of 16 rows and columns in a tile.  W: waves.
 // UNS: 0 both operands signed, 1 A unsigned, 2 B unsigned.
 template <int MT, int NT, int W, bool A_KC, bool B_KC, int UNS, Source SOURCE>
-__global__ __launch_bounds__(64 * W) void wave_tile_kernel(WaveTileParams P) {
+__global__ __launch_bounds__(64 * W) void wave_tile_kernel(std::conditional_t<SOURCE == GATHERED, WaveConvParams, WaveTileParams> P) {
   constexpr bool CONV = SOURCE == GATHERED, REGS = SOURCE == STAGED;
   static_assert(!CONV || (A_KC && B_KC && UNS == 1), "the lowered matrix is unsigned, it and the filters k-contiguous");
   using OA = WaveOperand<MT, A_KC>;
@@ -353,7 +355,7 @@ template <int MT, int NT, int W, Source SOURCE>
 hipError_t launch_wave_tile_for(const Problem &p, hipStream_t s) {
   constexpr int BM = 16 * MT, BN = 16 * NT;
   const bool a_kc = p.a_sk == 1, b_kc = p.b_sk == 1;
-  WaveTileParams P;
+  WaveConvParams P;
   P.A = static_cast<const uint8_t *>(p.A);
   P.B = static_cast<const uint8_t *>(p.B);
   P.C = p.C;
@@ -374,8 +376,6 @@ hipError_t launch_wave_tile_for(const Problem &p, hipStream_t s) {
   P.a_sb = p.a_sb;
   P.b_sb = p.b_sb;
   P.c_sb = p.c_sb;
-  P.conv = ConvGeom{};
-  P.per_image = P.per_row = P.per_tap = P.per_filter_row = Divisor{1, 0};
   void (*kern)(WaveTileParams) = nullptr;
 #define MIP_PICK(AK, BKC)                                                                      \
   kern = uns == 0 ? wave_tile_kernel<MT, NT, W, AK, BKC, 0, SOURCE>                            \
@@ -385,6 +385,7 @@ hipError_t launch_wave_tile_for(const Problem &p, hipStream_t s) {
   else if (a_kc) MIP_PICK(true, false);
   else if (b_kc) MIP_PICK(false, true);
   else MIP_PICK(false, false);
+  const void *kernel = reinterpret_cast<const void *>(kern);
   if constexpr (SOURCE == STREAMED) {
     if (p.conv) {
       const ConvGeom &g = *p.conv;
@@ -393,18 +394,18 @@ hipError_t launch_wave_tile_for(const Problem &p, hipStream_t s) {
       P.per_row = divisor(g.wo, (int64_t)g.ho * g.wo);
       P.per_tap = divisor(g.ci / 64, p.k / 64 + 1);
       P.per_filter_row = divisor(g.wf, p.k / g.ci + 1);
-      kern = wave_tile_kernel<MT, NT, W, true, true, 1, GATHERED>;
+      void (*gather)(WaveConvParams) = wave_tile_kernel<MT, NT, W, true, true, 1, GATHERED>;
+      kernel = reinterpret_cast<const void *>(gather);
     }
   }
 #undef MIP_PICK
   const size_t stages = (size_t)W * (MT + NT) * 2048, sums = (size_t)W * BM * (BN + 4) * 4;
   const size_t lds = stages > sums ? stages : sums;
-  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds);
+  hipError_t e = allow_dynamic_lds(kernel, lds);
   if (e != hipSuccess) return e;
   const int64_t tiles = (int64_t)P.walk.tiles_m * P.walk.tiles_n;
   dim3 grid((unsigned)(((tiles + 7) / 8) * 8), 1, (unsigned)p.batch);
-  hipLaunchKernelGGL(kern, grid, dim3(64 * W), lds, s, P);
-  return hipGetLastError();
+  return launch_with(kernel, grid, 64 * W, lds, s, &P);
 }
 
 }  // namespace mip
