@@ -48,11 +48,13 @@
  *     MIPGEMM_VARIANT  kernel variant for the GEMM calls: "simple" (one thread per
  *                      element of C: a cross-check, hundreds of times slower),
  *                      "dma256k128", "dma128k128", "dma128k128split" (its general form: ragged
- *                      edges, k in MIPGEMM_SPLITK ranges), "slab16", "slab32", "slab64", "tile<shape>" or
+ *                      edges, k in MIPGEMM_SPLITK ranges), "slab16", "slab32", "slab64", "wave32",
+ *                      "wave32x64" (tiles whose waves split k), "tile<shape>" or
  *                      "dma<shape>" with <shape> one of 256, 128, 64, 64x256,
  *                      256x64, 64x128, 128x64; a variant that cannot serve a
  *                      problem falls back (the names of mipgemm_variant_name say
- *                      what ran)
+ *                      what ran; "mfma_dma64" and "mfma_tile64" name their form
+ *                      whose waves split k as well)
  *     MIPGEMM_SPLITK   number of k ranges of the tile kernels
  *     MIPGEMM_PACK     "always" / "never": the packed route whenever / never
  *     MIPGEMM_CONV     "im2col" / "rows": the convolution route

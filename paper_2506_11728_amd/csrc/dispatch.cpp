@@ -37,13 +37,11 @@ hipError_t launch_dma(const Problem &p, Shape shape, int splits, hipStream_t s) 
 
 hipError_t launch_wave_32x32(const Problem &p, bool streamed, hipStream_t s);
 hipError_t launch_wave_32x64(const Problem &p, bool streamed, hipStream_t s);
-hipError_t launch_wave_64x64(const Problem &p, bool streamed, hipStream_t s);
 
 hipError_t launch_wave(const Problem &p, Wave wave, bool streamed, hipStream_t s) {
   switch (wave) {
     case WAVE_32: return launch_wave_32x32(p, streamed, s);
     case WAVE_32X64: return launch_wave_32x64(p, streamed, s);
-    case WAVE_64: return launch_wave_64x64(p, streamed, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -98,7 +96,7 @@ const char *plan_name(const Plan &plan) {
 // "dma128k128" (the same kernel on 128 x 128 tiles), "dma128k128split" (its general form with k
 // ranges), "dma256k128ragged", "dma256x192k128", "dma192x256k128", "dma192k128" (the general form on
 // tiles of those sides), "slab16" / "slab32" / "slab64" (the skinny-m kernel with that slab width),
-// "wave32" / "wave32x64" / "wave64" (tiles whose waves split k),
+// "wave32" / "wave32x64" (tiles whose waves split k),
 // "tile<shape>" (register-staged) or "dma<shape>" (direct-to-LDS) with <shape> one of
 // 256, 128, 64, 64x256, 256x64, 64x128, 128x64.  A dma variant only applies to problems it is
 // eligible for; others fall back to the staged kernel of the same shape.
@@ -157,12 +155,11 @@ static bool forced_plan(const Problem &p, Plan *plan) {
     *plan = {KIND_SLAB, SHAPE_64, nt};
     return true;
   }
-  static const struct { const char *name; Wave wave; } waves[3] = {
-      {"wave32", WAVE_32}, {"wave32x64", WAVE_32X64}, {"wave64", WAVE_64}};
+  static const struct { const char *name; Wave wave; } waves[2] = {{"wave32", WAVE_32}, {"wave32x64", WAVE_32X64}};
   for (const auto &v : waves)
     if (!std::strcmp(e, v.name)) {
       const bool streamed = wave_streamed_eligible(p);
-      if (!streamed && (v.wave == WAVE_64 || !wave_staged_eligible(p))) return false;
+      if (!streamed && !wave_staged_eligible(p)) return false;
       *plan = {streamed ? KIND_DMA : KIND_STAGED, SHAPE_64, 1, v.wave};
       return true;
     }
@@ -230,8 +227,8 @@ static int64_t tile_count(const Problem &p, Shape s) {
 // zero fill, or through slots).
 // Measured over 1500 aligned products of 1 to 400 tiles of 64 x 64 (k = 64 to 8192), the rule takes 0.88 of
 // the time without it, the best choice each time 0.86; over 1200 unaligned ones 0.63 and 0.59.
-// us, before and after: (512, 512, 2048) k-contiguous 6.5 -> 4.2, (256, 256, 1024) 4.4 -> 3.7, (1568, 512, 4608)
-// u8 to int8 16.2 -> 12.0, (64, 4096, 11008) u8 packed 16.2 -> 12.8, row-major B (1024, 512, 4096) 12.3 -> 9.9;
+// us, before and after: (512, 512, 2048) k-contiguous 6.5 -> 4.2, (256, 256, 1024) 4.4 -> 3.7, (64, 4096, 11008) u8
+// packed 16.2 -> 12.8, row-major B (1024, 512, 4096) 12.3 -> 9.9;
 // a 3 x 3 convolution of 7 x 7 x 512 at batch 8 19.7 -> 7.4; unaligned (32, 256, 3600) to int8 35 -> 12.9,
 // (42, 2368, 2112) 22.9 -> 6.5, (1024, 70, 1024) 18.2 -> 4.8, (459, 1024, 836) packed before 7.9 -> 6.1.
 // On the other side of the lines: (1024, 1024, 1024) 5.1 on 64 x 64 tiles and 6.6, (1024, 512, 1024) row-major 4.75
@@ -253,7 +250,7 @@ static Wave wave_form(const Problem &p, bool streamed) {
     const int64_t most = !may_split ? any : (adds ? adding : (4 * tiles(32, 32) <= cus ? few : other))[strided];
     if (tiles(32, 32) <= cus) return k < most && (!p.conv || k >= 512) ? WAVE_32 : WAVE_NONE;
     if (tiles(32, 64) <= cus && p.a_sk == 1) return k >= (strided ? 1536 : 1024) && k < 2 * most ? WAVE_32X64 : WAVE_NONE;
-    return tiles(64, 64) <= cus && strided == 0 && k >= (p.conv ? 2048 : 2304) && !adds ? WAVE_64 : WAVE_NONE;
+    return WAVE_NONE;
   }
   if (!wave_staged_eligible(p) || tuning().pack > 0) return WAVE_NONE;
   // (with a workspace, larger products are packed)

@@ -27,7 +27,11 @@
 
 namespace mip {
 
-constexpr int DMA_STAGES = 4;
+// One group of four waves works through blocks of 64 k in four LDS stages.  Two groups share blocks of 128, the
+// second half of each the second group's, and add their sums up at the end: half the barriers, and two
+// waves on a SIMD to cover each other's LDS latency.  64 of k of a 64 x 64 tile, one workgroup to a compute
+// unit, take 0.115 us with one group and 0.08 with two.
+constexpr int dma_stages(int bm, int bn, int groups) { return groups == 2 && bm * bn > 64 * 64 ? 3 : 4; }
 
 struct DmaTileParams {
   const uint8_t *A, *B;
@@ -35,7 +39,7 @@ struct DmaTileParams {
   int64_t m, n;
   int64_t lda, ldb, ldc;  // the one stride of each operand that is not 1
   TileWalk walk;
-  int nkt;                // k / 64 in the whole problem
+  int nkt;                // blocks in the whole problem
   int kt_per_split;       // k blocks per workgroup (blockIdx.y picks the range)
   int accumulate;         // C += instead of C =
   int atomic;             // several workgroups add into the same tile (split k)
@@ -60,23 +64,25 @@ static __device__ __attribute__((aligned(16))) const uint8_t conv_zero_block[16]
 // UNS: 0 both operands signed, 1 A unsigned, 2 B unsigned; 3 and 4: as 1 and 2 with the k sums
 // of the signed operand read from P.ksum instead of being accumulated from the fragments
 // (with split k by the first range alone).
-template <int BM, int BN, bool A_KC, bool B_KC, int UNS, bool CONV = false>
-__global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<CONV, DmaConvParams, DmaTileParams> P) {
+template <int BM, int BN, bool A_KC, bool B_KC, int UNS, bool CONV = false, int GROUPS = 1>
+__global__ __launch_bounds__(NTHREADS *GROUPS) void dma_tile_kernel(std::conditional_t<CONV, DmaConvParams, DmaTileParams> P) {
   constexpr bool FLIP_A = UNS == 1 || UNS == 3, FLIP_B = UNS == 2 || UNS == 4;
   constexpr bool SUM_A = UNS == 2, SUM_B = UNS == 1;
   static_assert(!CONV || (A_KC && B_KC), "the lowered matrix and the filters are k-contiguous");
-  using SA = Stage<BM, A_KC>;
-  using SB = Stage<BN, B_KC>;
+  constexpr int THREADS = NTHREADS * GROUPS, KD = BK * GROUPS, STAGES = dma_stages(BM, BN, GROUPS);
+  using SA = Stage<BM, A_KC, KD, THREADS>;
+  using SB = Stage<BN, B_KC, KD, THREADS>;
   constexpr int FM = BM / 64, FN = BN / 64;      // 32 x 32 blocks per wave, down and across
   constexpr int LA = SA::PER_THREAD, LB = SB::PER_THREAD;  // direct loads per thread per block
   constexpr int PER_BLOCK = LA + LB;
-  constexpr int STAGE_BYTES = (BM + BN) * BK;
+  constexpr int STAGE_BYTES = (BM + BN) * KD;
   constexpr int NM = FM * FN;                    // MFMAs per 32-deep sub-block
   constexpr int NF = FM + FN;                    // fragments per sub-block
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_of_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = GROUPS == 1 ? 0 : wave_of_all >> 2, wave = wave_of_all & 3;
   const int wm = wave >> 1, wn = wave & 1;
 
   fetch_arguments(P.walk, P.A, P.B, P.C, P.m, P.n, P.lda, P.ldb, P.ldc, P.nkt, P.kt_per_split, P.accumulate, P.atomic, P.slots,
@@ -129,8 +135,8 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
       offB[i] = (uint32_t)(a * P.ldb + ((piece * 16 < rows_b ? piece : 0) << 4));
     }
   }
-  const int64_t stepA = A_KC ? BK : BK * P.lda;
-  const int64_t stepB = B_KC ? BK : BK * P.ldb;
+  const int64_t stepA = A_KC ? KD : KD * P.lda;
+  const int64_t stepB = B_KC ? KD : KD * P.ldb;
   const uint8_t *gA = P.A + (A_KC ? m0 * P.lda : m0) + kt_begin * stepA;
   const uint8_t *gB = P.B + (B_KC ? n0 * P.ldb : n0) + kt_begin * stepB;
 
@@ -155,15 +161,15 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
       conv_at[i] = ((g * G.hi + conv_iy[i]) * G.wi + conv_ix[i]) * G.ci + ((c ^ SA::kswz(a)) << 4);
     }
     if (kt_begin > 0) {
-      const int per_tap = G.ci / BK, tap = kt_begin / per_tap;
-      cur_c = (kt_begin - tap * per_tap) * BK;
+      const int per_tap = G.ci / KD, tap = kt_begin / per_tap;
+      cur_c = (kt_begin - tap * per_tap) * KD;
       cur_y = tap / G.wf;
       cur_x = tap - cur_y * G.wf;
       cur_at = (cur_y * G.wi + cur_x) * G.ci + cur_c;
     }
   }
 
-  const uint32_t lds0 = lds_address(smem) + wave * 1024;
+  const uint32_t lds0 = lds_address(smem) + wave_of_all * 1024;
   // direct load q of a block: 0 .. LA-1 from A, then LB from B
   auto issue_one = [&](int stage, int q) {
     const uint32_t sa = lds0 + stage * STAGE_BYTES;
@@ -171,17 +177,17 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
       if constexpr (CONV) {
         const bool inside = (unsigned)(conv_iy[q] + cur_y) < (unsigned)P.conv.hi &&
                             (unsigned)(conv_ix[q] + cur_x) < (unsigned)P.conv.wi;
-        dma16_at(inside ? P.A + (conv_at[q] + cur_at) : conv_zero_block, sa + q * 4096);
+        dma16_at(inside ? P.A + (conv_at[q] + cur_at) : conv_zero_block, sa + q * (16 * THREADS));
       } else {
-        dma16(offA[q], gA, sa + q * 4096);
+        dma16(offA[q], gA, sa + q * (16 * THREADS));
       }
     } else {
-      dma16(offB[q - LA], gB, sa + BM * BK + (q - LA) * 4096);
+      dma16(offB[q - LA], gB, sa + BM * KD + (q - LA) * (16 * THREADS));
     }
   };
   auto advance = [&]() {
     if constexpr (CONV) {
-      cur_c += BK;
+      cur_c += KD;
       if (cur_c == P.conv.ci) {  // next filter tap
         cur_c = 0;
         if (++cur_x == P.conv.wf) {
@@ -211,7 +217,7 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
 
   // prologue: blocks 0 .. STAGES-2 in flight
 #pragma unroll
-  for (int s = 0; s < DMA_STAGES - 1; ++s)
+  for (int s = 0; s < STAGES - 1; ++s)
     if (s < nkt) {
 #pragma unroll
       for (int q = 0; q < PER_BLOCK; ++q) issue_one(s, q);
@@ -222,8 +228,8 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
   // fragment f of a k sub-block: 0 .. FM-1 rows of A, then FN columns of B
   auto read_frag = [&](int stage, int ks, int f, v4i (&a)[FM], v4i (&b)[FN]) {
     const uint8_t *sa = smem + stage * STAGE_BYTES;
-    if (f < FM) a[f] = SA::fragment(sa, wm * (BM / 2) + f * 32, ks, lane);
-    else b[f - FM] = SB::fragment(sa + BM * BK, wn * (BN / 2) + (f - FM) * 32, ks, lane);
+    if (f < FM) a[f] = SA::fragment(sa, wm * (BM / 2) + f * 32, 2 * group + ks, lane);
+    else b[f - FM] = SB::fragment(sa + BM * KD, wn * (BN / 2) + (f - FM) * 32, 2 * group + ks, lane);
   };
   // unsigned operand: bias its bytes to signed, and sum the other operand over k
   auto prepare = [&](v4i (&a)[FM], v4i (&b)[FN]) {
@@ -252,7 +258,7 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
   };
 
   // block 0 visible to everyone, its first fragments on their way
-  if (nkt > 2) publish_barrier<2 * PER_BLOCK>();
+  if (STAGES == 4 && nkt > 2) publish_barrier<2 * PER_BLOCK>();
   else if (nkt > 1) publish_barrier<PER_BLOCK>();
   else publish_barrier<0>();
 #pragma unroll
@@ -269,12 +275,12 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
   // complete; -1 marks the last block (nothing to publish).
   constexpr int SLOTS0 = NM > NF + PER_BLOCK ? NM : NF + PER_BLOCK;
   constexpr int SLOTS1 = NM > NF ? NM : NF;
-  auto step = [&](int t, auto issue_tag, auto newer_tag) {
+  int stage = 0;
+  auto step = [&](auto issue_tag, auto newer_tag) {
     constexpr bool ISSUE = decltype(issue_tag)::value;
     constexpr int NEWER = decltype(newer_tag)::value;
-    const int stage = t & (DMA_STAGES - 1);
-    const int fill = (t + DMA_STAGES - 1) & (DMA_STAGES - 1);
-    const int next = (t + 1) & (DMA_STAGES - 1);
+    const int fill = stage == 0 ? STAGES - 1 : stage - 1;  // read a step ago
+    const int next = stage == STAGES - 1 ? 0 : stage + 1;
     prepare(fa[0], fb[0]);
 #pragma unroll
     for (int s = 0; s < SLOTS0; ++s) {
@@ -296,15 +302,16 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
       if (NEWER >= 0 && s < NF) read_frag(next, 0, s, fa[0], fb[0]);
       __builtin_amdgcn_sched_barrier(0);
     }
+    stage = next;
   };
   using std::integral_constant;
   int t = 0;
-  for (; t + DMA_STAGES - 1 < nkt; ++t)  // blocks t+1, t+2, t+3 exist; t+2 and t+3 may fly
-    step(t, integral_constant<bool, true>{}, integral_constant<int, 2>{});
+  for (; t + STAGES - 1 < nkt; ++t)  // (four stages:) blocks t+1, t+2, t+3 exist; t+2 and t+3 may fly
+    step(integral_constant<bool, true>{}, integral_constant<int, STAGES - 2>{});
   // the last (up to) three blocks: nothing left to issue
-  if (t + 2 < nkt) { step(t, integral_constant<bool, false>{}, integral_constant<int, 1>{}); ++t; }
-  if (t + 1 < nkt) { step(t, integral_constant<bool, false>{}, integral_constant<int, 0>{}); ++t; }
-  step(t, integral_constant<bool, false>{}, integral_constant<int, -1>{});
+  if (STAGES == 4 && t + 2 < nkt) { step(integral_constant<bool, false>{}, integral_constant<int, 1>{}); ++t; }
+  if (t + 1 < nkt) { step(integral_constant<bool, false>{}, integral_constant<int, 0>{}); ++t; }
+  step(integral_constant<bool, false>{}, integral_constant<int, -1>{});
 
   // ---- write-back: unsigned-operand correction, then C = / += / atomic += ----
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // stages are dead from here on
@@ -314,20 +321,43 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       const int64_t col = n0 + wn * (BN / 2) + j * 32 + (lane & 31);
-      sumB[j] = lane < 32 && col < P.n && blockIdx.y == 0 ? P.ksum[col] : 0;
+      sumB[j] = lane < 32 && col < P.n && blockIdx.y == 0 && group == 0 ? P.ksum[col] : 0;
     }
   }
   if (UNS == 4) {
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       const int64_t row = m0 + wm * (BM / 2) + i * 32 + (lane & 31);
-      sumA[i] = lane < 32 && row < P.m && blockIdx.y == 0 ? P.ksum[row] : 0;
+      sumA[i] = lane < 32 && row < P.m && blockIdx.y == 0 && group == 0 ? P.ksum[row] : 0;
     }
   }
   unsigned_correction<FM, FN>(acc, sumA, sumB, FLIP_A, FLIP_B, lane);
+  uint8_t *patches = smem;  // of the write-back, one per wave
+  if constexpr (GROUPS == 2) {
+    v4i *theirs = reinterpret_cast<v4i *>(smem) + wave * (FM * FN * 256) + lane;
+    if (group == 1) {
+#pragma unroll
+      for (int b = 0; b < FM * FN; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          theirs[(b * 4 + q) * 64] = v4i{acc[b / FN][b % FN][4 * q], acc[b / FN][b % FN][4 * q + 1],
+                                         acc[b / FN][b % FN][4 * q + 2], acc[b / FN][b % FN][4 * q + 3]};
+    }
+    __syncthreads();
+    if (group == 1) return;
+#pragma unroll
+    for (int b = 0; b < FM * FN; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const v4i v = theirs[(b * 4 + q) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[b / FN][b % FN][4 * q + e] += v[e];
+      }
+    patches = smem + BM * BN * 4;
+  }
   // (not on 256 x 256 tiles, of which there are never too few: the exchange of their 256 accumulators
   // spills registers that the rest of the kernel pays for)
-  if constexpr (BM * BN < 256 * 256) {
+  if constexpr (BM * BN < 256 * 256 && GROUPS == 1) {
     if (P.slots) {  // only the workgroup that draws the tile's last ticket writes C
       const int64_t tile = ((int64_t)blockIdx.z * P.walk.tiles_m + tm) * P.walk.tiles_n + tn;
       if (!combine_k_ranges<FM, FN>(acc, P.slots + tile * P.splits * (int64_t)(BM * BN), blockIdx.y,
@@ -343,7 +373,7 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
       int8_t *Q = reinterpret_cast<int8_t *>(P.C) + mw * P.ldc + nw;
       if constexpr (FN >= 2) {
         if (m0 + BM <= P.m && n0 + BN <= P.n) {
-          store_blocks_q8_via_lds<FM, FN>(acc, Q, P.ldc, lane, smem + wave * STORE_PATCH_BYTES, P.scale);
+          store_blocks_q8_via_lds<FM, FN>(acc, Q, P.ldc, lane, patches + wave * STORE_PATCH_BYTES, P.scale);
           return;
         }
       }
@@ -353,12 +383,12 @@ __global__ __launch_bounds__(NTHREADS) void dma_tile_kernel(std::conditional_t<C
     int32_t *C = P.C + mw * P.ldc + nw;
     const bool full = m0 + BM <= P.m && n0 + BN <= P.n;
     const Finish fin = {P.scale, P.out_float};
-    if (P.atomic)
+    if (GROUPS == 1 && P.atomic)
       add_blocks_atomic<FM, FN>(acc, C, P.ldc, P.m - mw, P.n - nw, lane,
                                 reinterpret_cast<int32_t *>(smem + wave * ATOMIC_PATCH_BYTES));
     else if (full)
       store_blocks_via_lds<FM, FN>(acc, C, P.ldc, P.accumulate, lane,
-                                   reinterpret_cast<int32_t *>(smem + wave * STORE_PATCH_BYTES), fin);
+                                   reinterpret_cast<int32_t *>(patches + wave * STORE_PATCH_BYTES), fin);
     else store_blocks<FM, FN, false>(acc, C, P.ldc, P.m - mw, P.n - nw, P.accumulate, lane, fin);
   }
 }
@@ -386,8 +416,28 @@ bool dma_tile_eligible_for(const Problem &p) {
   return true;
 }
 
+// Whether two groups of waves serve an unsplit product: where the tiles do not give every compute unit
+// two workgroups anyway, which cover each other as well, and k pays for adding the groups' sums up.  us, one
+// group and two: 64 x 64 tiles (1024, 1024, 1024) 5.1 and 4.8, to float (1024, 1024, 2048) 8.3 and 7.0, a convolution of
+// (6272, 256, 2304), 392 tiles, 13.7 and 12.3, but (12544, 128, 512), 392 tiles, 5.65 and 6.25, sixteen of (64, 512, 512)
+// row-major 5.2 and 5.5; 64 x 128 tiles: a convolution of (12544, 128, 1152), 196 tiles, 8.6 and 7.5, but
+// (25088, 128, 512), 392 tiles, 7.9 and 8.7, row-major (3072, 512, 1024), 192 tiles, 6.75 and 6.9.
 template <int BM, int BN>
+bool two_groups_serve(const Problem &p) {
+  const int64_t lda = p.a_sk == 1 ? p.a_sm : p.a_sk, ldb = p.b_sk == 1 ? p.b_sn : p.b_sk;
+  if (p.k % (2 * BK) || (p.conv && p.conv->ci % (2 * BK))) return false;
+  if (2 * BK * lda >= ((int64_t)1 << 31) || 2 * BK * ldb >= ((int64_t)1 << 31)) return false;
+  const int64_t tiles = ((p.m + BM - 1) / BM) * ((p.n + BN - 1) / BN) * (p.batch > 1 ? p.batch : 1), cus = compute_units();
+  if (BM * BN > 64 * 64) return tiles <= cus && p.k >= (p.a_sk == 1 && p.b_sk == 1 ? 1024 : 1536);
+  return tiles <= cus ? p.k >= 768 : tiles <= 2 * cus && p.k >= 2304;
+}
+
+template <int BM, int BN, int GROUPS = 1>
 hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
+  if constexpr (GROUPS == 1 && BM * BN <= 128 * 64 && BM <= 128 && BN <= 128) {
+    if (splits <= 1 && two_groups_serve<BM, BN>(p)) return launch_dma_tile_for<BM, BN, 2>(p, 1, s);
+  }
+  constexpr int KD = BK * GROUPS, STAGES = dma_stages(BM, BN, GROUPS);
   DmaConvParams P;
   const bool a_kc = p.a_sk == 1, b_kc = p.b_sk == 1;
   P.A = static_cast<const uint8_t *>(p.A);
@@ -399,7 +449,7 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   P.ldb = b_kc ? p.b_sn : p.b_sk;
   P.ldc = p.ldc;
   P.walk = tile_walk((p.m + BM - 1) / BM, (p.n + BN - 1) / BN);
-  P.nkt = (int)(p.k / BK);
+  P.nkt = (int)(p.k / KD);
   if (splits < 1) splits = 1;
   if (splits > P.nkt) splits = P.nkt;
   if (splits > 65535) splits = 65535;
@@ -448,9 +498,10 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   // out, so that more workgroups of a short-k problem fit a compute unit (the write-back
   // patches, one per wave, must still fit)
   dim3 grid((unsigned)(((ntiles + 7) / 8) * 8), (unsigned)splits, (unsigned)p.batch);
-  const int stages = P.kt_per_split < DMA_STAGES ? P.kt_per_split : DMA_STAGES;
-  size_t lds = (size_t)stages * (BM + BN) * BK;
-  if (lds < 4 * (size_t)STORE_PATCH_BYTES) lds = 4 * (size_t)STORE_PATCH_BYTES;
+  const int stages = P.kt_per_split < STAGES ? P.kt_per_split : STAGES;
+  size_t lds = (size_t)stages * (BM + BN) * KD;
+  const size_t write_back = 4 * (size_t)STORE_PATCH_BYTES + (GROUPS == 2 ? BM * BN * 4 : 0);
+  if (lds < write_back) lds = write_back;
   const int uns = p.a_unsigned ? 1 : (p.b_unsigned ? 2 : 0);
   // supplied k sums (pre-packed weights): for a k-contiguous signed operand, which packed weights
   // always are; otherwise the sums are accumulated in the loop as usual
@@ -459,13 +510,13 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
   P.ksum = supplied ? p.ksum : nullptr;
   void (*kern)(DmaTileParams) = nullptr;
 #define MIP_PICK(AK, BKC)                                                          \
-  kern = uns == 0 ? dma_tile_kernel<BM, BN, AK, BKC, 0>                            \
-                  : (uns == 1 ? dma_tile_kernel<BM, BN, AK, BKC, 1>                \
-                              : dma_tile_kernel<BM, BN, AK, BKC, 2>)
+  kern = uns == 0 ? dma_tile_kernel<BM, BN, AK, BKC, 0, false, GROUPS>             \
+                  : (uns == 1 ? dma_tile_kernel<BM, BN, AK, BKC, 1, false, GROUPS> \
+                              : dma_tile_kernel<BM, BN, AK, BKC, 2, false, GROUPS>)
   if (supplied && uns == 1)
-    kern = a_kc ? dma_tile_kernel<BM, BN, true, true, 3> : dma_tile_kernel<BM, BN, false, true, 3>;
+    kern = a_kc ? dma_tile_kernel<BM, BN, true, true, 3, false, GROUPS> : dma_tile_kernel<BM, BN, false, true, 3, false, GROUPS>;
   else if (supplied)
-    kern = b_kc ? dma_tile_kernel<BM, BN, true, true, 4> : dma_tile_kernel<BM, BN, true, false, 4>;
+    kern = b_kc ? dma_tile_kernel<BM, BN, true, true, 4, false, GROUPS> : dma_tile_kernel<BM, BN, true, false, 4, false, GROUPS>;
   else if (a_kc && b_kc) MIP_PICK(true, true);
   else if (a_kc) MIP_PICK(true, false);
   else if (b_kc) MIP_PICK(false, true);
@@ -480,11 +531,11 @@ hipError_t launch_dma_tile_for(const Problem &p, int splits, hipStream_t s) {
     const bool filter_sums = p.ksum != nullptr;
     P.ksum = filter_sums ? p.ksum : nullptr;
     void (*gather)(DmaConvParams) =
-        filter_sums ? dma_tile_kernel<BM, BN, true, true, 3, true> : dma_tile_kernel<BM, BN, true, true, 1, true>;
+        filter_sums ? dma_tile_kernel<BM, BN, true, true, 3, true, GROUPS> : dma_tile_kernel<BM, BN, true, true, 1, true, GROUPS>;
     kernel = reinterpret_cast<const void *>(gather);
   }
   const hipError_t e = allow_dynamic_lds(kernel, lds);
-  return e != hipSuccess ? e : launch_with(kernel, grid, NTHREADS, lds, s, &P);
+  return e != hipSuccess ? e : launch_with(kernel, grid, NTHREADS * GROUPS, lds, s, &P);
 }
 
 }  // namespace mip

@@ -100,8 +100,6 @@ __global__ __launch_bounds__(64 * slab_waves(MT, NT, RINGS)) void slab_kernel(Sl
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  fetch_arguments(P.A, P.B, P.C, P.lda, P.ldb, P.ldc, P.m, P.nsteps, P.half_last, P.tiles, P.accumulate, P.out_float,
-                  P.scale);
   // consecutive workgroup ids sit on different XCDs: give each XCD a contiguous run
   // of slabs, so that neighbours, which share cache lines of a row-major B, share an L2
   const int per_xcd = (P.tiles + 7) / 8;

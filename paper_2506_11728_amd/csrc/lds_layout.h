@@ -52,10 +52,10 @@ __device__ __forceinline__ v4i shifted_down(v4i v, int n) {
 //     KD k-rows of R bytes; chunk c of k-row q sits at q*R + 16*(c ^ swz(q)).
 // Both XOR patterns spread the 16 lanes of one LDS access over all banks
 // (no bank conflicts measured).
-template <int R, bool KC, int KD = BK>
+template <int R, bool KC, int KD = BK, int THREADS = NTHREADS>
 struct Stage {
   static constexpr int CHUNKS = R * KD / 16;
-  static constexpr int PER_THREAD = CHUNKS / NTHREADS;
+  static constexpr int PER_THREAD = CHUNKS / THREADS;
   static constexpr int ROW_CHUNKS = R / 16;  // strided: chunks per k-row
   static constexpr int K_CHUNKS = KD / 16;   // KC: chunks per row
 
@@ -66,7 +66,7 @@ struct Stage {
 
   // chunk handled by this thread: (row, chunk-in-row) for KC, (k-row, chunk) for strided
   __device__ static __forceinline__ void chunk_of(int i, int tid, int &a, int &c) {
-    int q = tid + NTHREADS * i;
+    int q = tid + THREADS * i;
     if (KC) { a = q / K_CHUNKS; c = q % K_CHUNKS; }
     else { a = q / ROW_CHUNKS; c = q % ROW_CHUNKS; }
   }

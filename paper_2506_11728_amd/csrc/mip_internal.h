@@ -104,7 +104,7 @@ enum Kind {
 };
 
 // The form of a 64 x 64 tile plan (KIND_DMA or KIND_STAGED) whose waves split k (wave_tile.h), by its tiles.
-enum Wave { WAVE_NONE, WAVE_32, WAVE_32X64, WAVE_64 };
+enum Wave { WAVE_NONE, WAVE_32, WAVE_32X64 };
 
 struct Plan {
   Kind kind;

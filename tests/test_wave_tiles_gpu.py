@@ -39,13 +39,10 @@ def _operands(m, n, k, oa, ob, pad, au, bu, seed):
 
 
 @pytest.mark.parametrize("shape", ALIGNED + UNALIGNED, ids=lambda s: "x".join(map(str, s)))
-@pytest.mark.parametrize("variant", ["wave32", "wave32x64", "wave64"])
+@pytest.mark.parametrize("variant", ["wave32", "wave32x64"])
 def test_every_order_type_and_mode(gpu, variant, shape):
     import torch
     m, n, k, pad = shape
-    aligned = shape in ALIGNED
-    if variant == "wave64" and not aligned:
-        pytest.skip("64 x 64 tiles take direct loads only")
     for at, (oa, ob, kind) in enumerate((oa, ob, kind) for oa in (0, 1) for ob in (0, 1) for kind in ("ss", "us", "su")):
         au, bu = kind[0] == "u", kind[1] == "u"
         S, A, B = _operands(m, n, k, oa, ob, pad, au, bu, at)
@@ -73,12 +70,10 @@ def test_every_order_type_and_mode(gpu, variant, shape):
             assert np.array_equal(got, want), (oa, ob, kind, out, mode)
 
 
-@pytest.mark.parametrize("variant", ["wave32", "wave32x64", "wave64"])
+@pytest.mark.parametrize("variant", ["wave32", "wave32x64"])
 @pytest.mark.parametrize("pad", [0, 1])
 def test_batches(gpu, variant, pad):
     import torch
-    if variant == "wave64" and pad:
-        pytest.skip("64 x 64 tiles take direct loads only")
     m, n, k, batch = 48, 80, 320, 3
     parts = [_operands(m, n, k, 1, 0, pad, False, True, 50 + z) for z in range(batch)]
     dA, dB = (torch.from_numpy(np.stack([p[i] for p in parts])).cuda() for i in (1, 2))
@@ -89,7 +84,7 @@ def test_batches(gpu, variant, pad):
     assert np.array_equal(C.cpu().numpy(), np.stack([p[0] for p in parts]) + 7)
 
 
-@pytest.mark.parametrize("variant", ["wave32", "wave32x64", "wave64"])
+@pytest.mark.parametrize("variant", ["wave32", "wave32x64"])
 @pytest.mark.parametrize("shape", [(2, 9, 11, 64, 48, 3, 3, 1, 1), (1, 17, 23, 64, 96, 3, 5, 2, 2), (3, 7, 7, 192, 80, 3, 3, 1, 1),
                                    (2, 14, 14, 128, 64, 1, 1, 2, 0)], ids=lambda s: "x".join(map(str, s)))
 def test_convolutions(gpu, oracle, variant, shape):
