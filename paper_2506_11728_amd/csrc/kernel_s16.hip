@@ -132,7 +132,10 @@ struct StageS16 {
 // WR x WC waves over a tile of C, each on FM x FN blocks of 16 x 16.  Fragments of block t + 1 are
 // read and split while block t is multiplied; loads run two blocks further ahead.  Two waves to
 // a SIMD: one alone issues an ordinary vector instruction only every eight clocks.
-template <int WR, int WC, int FM, int FN, bool A_KC, bool B_KC>
+// STAGED: operands at any alignment, through registers: a block is loaded into them a step before it is stored to its
+// LDS stage; a 16-byte piece that an operand's edge cuts is fetched so far ahead that it ends there, and shifted
+// on its way.
+template <int WR, int WC, int FM, int FN, bool A_KC, bool B_KC, bool STAGED>
 __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
   constexpr int NT = 64 * WR * WC, WM = 16 * FM, WN = 16 * FN, BM = WR * WM, BN = WC * WN;
   using SA = StageS16<BM, A_KC, NT>;
@@ -164,6 +167,43 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
   // the block that has to be fetched chunk by chunk: the last one of k when k ends inside it
   const int ragged = P.k % KB ? P.nkt - 1 - block0 : -1;
 
+  v4i pieces[STAGED ? LOADS : 1];
+  auto load = [&](int t) {  // into the registers, blocks in order
+    const int left = t == ragged ? (int)(P.k % KB) : KB;
+    auto fetch = [&](auto stage, bool kc, const uint8_t *g, int64_t ld, int extent, v4i *to) {
+      using S = decltype(stage);
+#pragma unroll
+      for (int i = 0; i < S::LOADS; ++i) {
+        int a, c;
+        S::chunk_of(i, tid, a, c);
+        const int end = 2 * (kc ? left : extent), have = kc ? extent : left;
+        const int back = 16 * c + 16 > end ? 16 * c + 16 - end : 0;
+        to[i] = load16(g + (a < have ? a : have - 1) * ld + (16 * c - back));
+      }
+    };
+    fetch(SA{}, A_KC, gA, P.lda, rows_a, pieces);
+    fetch(SB{}, B_KC, gB, P.ldb, rows_b, pieces + SA::LOADS);
+    gA += stepA;
+    gB += stepB;
+  };
+  auto place = [&](int t) {  // what was loaded last, block t, into its stage
+    const int left = t == ragged ? (int)(P.k % KB) : KB;
+    uint8_t *to = smem + (t % STAGES) * STAGE + 16 * tid;
+    auto put = [&](auto stage, bool kc, int extent, const v4i *from, uint8_t *at) {
+      using S = decltype(stage);
+#pragma unroll
+      for (int i = 0; i < S::LOADS; ++i) {
+        int a, c;
+        S::chunk_of(i, tid, a, c);
+        const int end = 2 * (kc ? left : extent);
+        v4i v = 16 * c + 16 > end ? shifted_down(from[i], 16 * c + 16 - end) : from[i];
+        if (!kc && a >= left) v = v4i{0, 0, 0, 0};
+        *reinterpret_cast<v4i *>(at + i * (16 * NT)) = v;
+      }
+    };
+    put(SA{}, A_KC, rows_a, pieces, to);
+    put(SB{}, B_KC, rows_b, pieces + SA::LOADS, to + SA::BYTES);
+  };
   auto issue = [&](int t) {  // blocks in order
     const uint32_t to = lds0 + (uint32_t)(t % STAGES) * STAGE;
     if (t == ragged || P.wide_offsets) {
@@ -245,7 +285,15 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
   // prologue: the first blocks on their way, block 0 in registers
 #pragma unroll
   for (int t = 0; t < STAGES; ++t)
-    if (t < nkt) issue(t);
+    if (t < nkt) {
+      if constexpr (STAGED) {
+        if (t > 0) place(t - 1);
+        load(t);
+      } else {
+        issue(t);
+      }
+    }
+  if (STAGED && nkt < STAGES) place(nkt - 1);
   // (zeroed here, while the loads fly, and not right before the matrix instructions, which are
   // hidden from the compiler's wait states)
 #pragma unroll
@@ -255,7 +303,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
       hh[i][j] = mid[i][j] = ll[i][j] = v4i{0, 0, 0, 0};
       asm volatile("" : "+a"(hh[i][j]), "+a"(mid[i][j]), "+a"(ll[i][j]));
     }
-  if (nkt >= STAGES) publish_barrier<(STAGES - 1) * LOADS>();
+  if (STAGED) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  else if (nkt >= STAGES) publish_barrier<(STAGES - 1) * LOADS>();
   else publish_barrier<0>();
   auto first = [&](int set) {  // set is a constant at both calls
 #pragma unroll
@@ -300,9 +349,16 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void s16_kernel(S16Params P) {
   // what two waves to a SIMD leave beside the accumulators).
   auto step = [&](int t, auto cur_tag) {
     constexpr int cur = decltype(cur_tag)::value;
-    if (t + STAGES <= nkt) publish_barrier<(STAGES - 2) * LOADS>();
+    if (STAGED) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else if (t + STAGES <= nkt) publish_barrier<(STAGES - 2) * LOADS>();
     else publish_barrier<0>();
-    if (t + STAGES < nkt) issue(t + STAGES);
+    if constexpr (STAGED) {
+      // (the stage that block t - 1 left a step ago)
+      if (t + STAGES - 1 < nkt) place(t + STAGES - 1);
+      if (t + STAGES < nkt) load(t + STAGES);
+    } else if (t + STAGES < nkt) {
+      issue(t + STAGES);
+    }
     const uint32_t stage = (uint32_t)((t + 1) % STAGES) * STAGE;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -543,7 +599,7 @@ bool streamable(const int16_t *X, int64_t s_r, int64_t s_k, int64_t rows, int64_
   return s_k % 8 == 0 && rows % 8 == 0;
 }
 
-template <int WR, int WC, int FM, int FN>
+template <int WR, int WC, int FM, int FN, bool STAGED = false>
 hipError_t launch_tiles(S16Params P, bool a_kc, bool b_kc, hipStream_t s) {
   constexpr int BM = 16 * FM * WR, BN = 16 * FN * WC;
   const int64_t tiles = (int64_t)P.walk.tiles_m * P.walk.tiles_n;
@@ -553,8 +609,8 @@ hipError_t launch_tiles(S16Params P, bool a_kc, bool b_kc, hipStream_t s) {
   P.longer = P.nkt % P.splits;
   P.wide_offsets = far(P.lda, a_kc ? BM : KB) || far(P.ldb, b_kc ? BN : KB);
   void (*kern)(S16Params) =
-      a_kc ? (b_kc ? s16_kernel<WR, WC, FM, FN, true, true> : s16_kernel<WR, WC, FM, FN, true, false>)
-           : (b_kc ? s16_kernel<WR, WC, FM, FN, false, true> : s16_kernel<WR, WC, FM, FN, false, false>);
+      a_kc ? (b_kc ? s16_kernel<WR, WC, FM, FN, true, true, STAGED> : s16_kernel<WR, WC, FM, FN, true, false, STAGED>)
+           : (b_kc ? s16_kernel<WR, WC, FM, FN, false, true, STAGED> : s16_kernel<WR, WC, FM, FN, false, false, STAGED>);
   const size_t lds = (size_t)STAGES * (BM + BN) * 2 * KB;
   hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds);
   if (e != hipSuccess) return e;
@@ -577,9 +633,20 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
   int64_t s_r[2] = {p.a_sm, p.b_sn}, s_k[2] = {p.a_sk, p.b_sk};
   const int64_t rows[2] = {p.m, p.n};
   uint8_t *ws = static_cast<uint8_t *>(p.ws), *const end = ws + p.ws_bytes;
+  const int64_t cus = compute_units();
+  auto tiles = [&](int64_t side) { return ((p.m + side - 1) / side) * ((p.n + side - 1) / side); };
+  // Operands that cannot be streamed are read at their own alignment where that takes less than a launch that
+  // rewrites them and one more pass over them: 64 x 64 tiles each read theirs again, so up to a product of
+  // tiles and k.  Over 160 drawn products 0.78 of the time; us, rewritten and as they are: (128, 204, 64) 8.8 and 4.9,
+  // (799, 757, 602) 17.6 and 13.1, (512, 1603, 1792) 27.2 and 27.0, but (682, 2790, 2848) 54 and 60,
+  // (2965, 1216, 2153) 58 and 74.
+  bool staged = !streamable(X[0], s_r[0], s_k[0], rows[0], p.k) || !streamable(X[1], s_r[1], s_k[1], rows[1], p.k);
+  for (int i = 0; i < 2; ++i) staged = staged && (s_k[i] == 1 ? p.k : rows[i]) >= 8;
+  staged = staged && (!std::strcmp(tuning().variant, "s16_staged") ||
+                      (!*tuning().variant && tuning().splitk == 0 && (double)tiles(64) * (double)p.k <= 1600.0 * (double)cus));
   // what cannot be streamed is rewritten into the front of the workspace first
   Pack16Job job[2] = {};
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < 2 && !staged; ++i) {
     if (streamable(X[i], s_r[i], s_k[i], rows[i], p.k)) continue;
     const size_t bytes = (size_t)((rows[i] * kp * 2 + 255) / 256 * 256);
     if (bytes > (size_t)(end - ws)) return hipErrorInvalidValue;
@@ -612,11 +679,9 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
   // (256 tiles of 128: one round) 14.0 and 15.3, 4096^2 x 1024 (four rounds) 84 and 91; but
   // (1024, 3072, 768) (three quarters of a round) 17.0 and 15.7, 2304^2 x 1024 (1.27) 40 and 34,
   // 3000^2 x 1000 (2.25) 68 and 58.  A fourth or fifth stage changes neither.
-  const int64_t cus = compute_units();
-  auto tiles = [&](int64_t side) { return ((p.m + side - 1) / side) * ((p.n + side - 1) / side); };
   bool large = 10 * tiles(128) >= 9 * cus * ((tiles(128) + cus - 1) / cus);
   if (!std::strcmp(tuning().variant, "s16_128")) large = true;  // pinned by tests and tuning runs
-  if (!std::strcmp(tuning().variant, "s16_64")) large = false;
+  if (!std::strcmp(tuning().variant, "s16_64") || staged) large = false;
   const int64_t side = large ? 128 : 64, count = tiles(side);
   P.walk = tile_walk((p.m + side - 1) / side, (p.n + side - 1) / side);
   // Ranges of k, where that gives a compute unit at most three workgroups (a wave alone on its SIMD
@@ -657,6 +722,7 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
     }
     P.splits = (int)splits;
   }
+  if (staged) return launch_tiles<2, 2, 2, 2, true>(P, a_kc, b_kc, s);
   return large ? launch_tiles<2, 4, 4, 2>(P, a_kc, b_kc, s) : launch_tiles<2, 2, 2, 2>(P, a_kc, b_kc, s);
 }
 

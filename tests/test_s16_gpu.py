@@ -321,3 +321,32 @@ def test_s16_rewritten_operands_of_very_many_blocks(gpu):
     gpu.mipgemm_s16s16s32(1, 1, k, A, k, W.ROW_MAJOR, B, k, W.COL_MAJOR, C, 1, W.ROW_MAJOR, W.OVERWRITE,
                           workspace=ws, workspace_bytes=ws.numel())
     assert (C.item() - want) % (1 << 32) == 0
+
+
+@pytest.mark.parametrize("shape", [(8, 8, 8), (16, 17, 9), (31, 65, 63), (64, 130, 65), (65, 64, 191), (129, 40, 200), (70, 96, 1000)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("mode", [0, 1])
+def test_unaligned_operands_read_as_they_are(gpu, shape, mode):
+    """Through registers: pieces that an edge of k, m or n cuts, rows beyond it, one to sixteen blocks of k, every order."""
+    import torch
+    m, n, k = shape
+    rng = np.random.default_rng(m + k)
+    for oa, ob, oc in ((a, b, c) for a in (0, 1) for b in (0, 1) for c in (0, 1)):
+        for pad in (0, 3):
+            X, Y = rng.integers(-32768, 32768, (m, k)), rng.integers(-32768, 32768, (k, n))
+
+            def stored(x, order):
+                y = x if order == 0 else x.T
+                out = np.full((y.shape[0], y.shape[1] + pad), 0x5A5A, dtype=np.int16)
+                out[:, :y.shape[1]] = y
+                return torch.from_numpy(out).cuda(), y.shape[1] + pad
+            (A, lda), (B, ldb) = stored(X, oa), stored(Y, ob)
+            C0 = rng.integers(-100, 100, (m, n) if oc == 0 else (n, m)).astype(np.int32)
+            S = X @ Y if oc == 0 else (X @ Y).T
+            want = (S + (C0 if mode else 0)).astype(np.int64).astype(np.uint32).view(np.int32)
+            C = torch.from_numpy(C0).cuda()
+            ws = torch.empty(gpu.mipgemm_workspace_size_s16(m, n, k), dtype=torch.uint8, device="cuda")
+            with gpu.tuning(MIPGEMM_VARIANT="s16_staged"):
+                gpu.mipgemm_s16s16s32(m, n, k, A, lda, oa, B, ldb, ob, C, C0.shape[1], oc, mode, workspace=ws,
+                                      workspace_bytes=ws.numel())
+            assert np.array_equal(C.cpu().numpy(), want), (oa, ob, oc, pad)
