@@ -107,7 +107,7 @@ __device__ __forceinline__ void store_rows_via_lds(const v16i (&acc)[1][2], int3
 // TO_FLOAT, ACCUMULATE: what the write-back does, fixed at compile time.
 // PADDED: filter rows in whole pieces.  The 7 x 7 x 3 filters of a network's first layer take seven steps instead
 // of five, but one unaligned LDS read instead of two and none of some thirty mask instructions each:
-// @STEM@.
+// 30.9 -> 29.2 us for a batch of 32 images of 224 x 224.
 template <bool TO_FLOAT, bool ACCUMULATE, bool PADDED>
 __global__ __launch_bounds__(NTHREADS_ROWS) void conv_rows_kernel(RowsParams P) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];

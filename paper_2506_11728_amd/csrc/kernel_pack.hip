@@ -55,7 +55,8 @@ __device__ __forceinline__ void store_piece(uint8_t *dst, v4i v, int64_t left, b
 // block: this workgroup's number within the job.  A tile of E x E bytes is staged row by row (k), its
 // 16-byte chunk c of k-row q at q * E + 16 * (c ^ swz(q)), and read back column by column with the
 // transposing LDS read (see WaveOperand and Stage16 for the layout).  Sixteen single-byte LDS reads per
-// piece, on 64 x 64 tiles with one load in flight, took 17.5 us for both operands of 4095 x 4097 x 4099.
+// piece, on 64 x 64 tiles with one load in flight, took 17.5 us for both operands of
+// 4095 x 4097 x 4099; this takes 15.0.
 template <int E>
 __device__ __forceinline__ void pack_transpose_body(const PackJob &J, unsigned block, uint8_t *tile) {
   constexpr int CHUNKS = E / 16, PIECES = E * E / 16 / NTHREADS;  // per thread

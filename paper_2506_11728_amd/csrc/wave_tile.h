@@ -83,6 +83,11 @@ struct WaveOperand {
 
 // MT, NT: blocks of 16 rows and columns in a tile.  W: waves.
 // UNS: 0 both operands signed, 1 A unsigned, 2 B unsigned.
+// A workgroup of W waves has one tile of 16 MT x 16 NT; wave w takes steps w, w + W, ... of 128 k through LDS
+// stages of its own, so that nothing but its own loads holds a wave up and the only barriers are those of the final
+// sum over LDS.  What bounds it is the rate at which a compute unit takes direct loads, 63 bytes a clock (more of
+// them per product the smaller the tile), and for a short k the latency of the first load and of the sum, some 3 us.
+// (512, 512, 2048) on 64 x 64 tiles that share each block among four waves took 6.5 us and takes 4.2 on these.
 template <int MT, int NT, int W, bool A_KC, bool B_KC, int UNS, Source SOURCE>
 __global__ __launch_bounds__(64 * W) void wave_tile_kernel(std::conditional_t<SOURCE == GATHERED, WaveConvParams, WaveTileParams> P) {
   constexpr bool CONV = SOURCE == GATHERED, REGS = SOURCE == STAGED;
