@@ -408,6 +408,93 @@ static Shape shape_with_192(const Problem &p, Shape chosen) {
   return chosen;
 }
 
+// What an unsplit product takes on tiles of one form, us: rounds of workgroups, per_cu of them on each compute unit,
+// each a time per 128 of k and one for its two ends that grow with how many run side by side; more for an
+// unsigned operand whose partner's k sums the kernel has to add up, and for strided operands; and
+// what the words of C and the bytes of the operands add.
+struct TileForm {
+  Kind kind;
+  Shape shape;
+  int bm, bn, per_cu;
+  double block[4], ends[4];           // with 1 .. per_cu workgroups on a compute unit
+  double a_unsigned, b_unsigned;      // parts of the time per block,
+  double a_strided, b_strided, whole; // the last where no tile reaches over an edge
+  double words, old_words, operands;  // per million words written, words added to, bytes read
+};
+
+// Fitted to 2400 products of 128 to 13000 rows and columns, k = 512 to 8192, in every order, signedness, mode
+// and output type, each timed on every form; the median error is 6 %, nine in ten are within 15 %.
+static const TileForm kTileForms[] = {
+    {KIND_DMA, SHAPE_64, 64, 64, 4, {0.234, 0.424, 0.728, 0.994}, {3.3, 3.3, 3.27, 1.62},
+     0.133, 0.109, 0.149, 0.16, -0.0909, 0.163, 0.548, 0.058},
+    {KIND_DMA, SHAPE_128X64, 128, 64, 3, {0.334, 0.698, 1.15}, {3.99, 3.78, 2.96},
+     0.152, 0.138, 0.00605, 0.106, -0.0873, 0.191, 0.732, 0.0453},
+    {KIND_DMA, SHAPE_64X128, 64, 128, 3, {0.332, 0.678, 1.1}, {3.9, 3.83, 3.28},
+     0.202, 0.126, 0.12, 0.0112, -0.11, 0.17, 0.752, 0.0623},
+    {KIND_DMA, SHAPE_128, 128, 128, 2, {0.462, 0.996}, {4.34, 5.89},
+     0.358, 0.292, 0.0212, 0.00768, -0.0929, 0.258, 0.914, 0.0679},
+    {KIND_DMA_K128_SPLIT, SHAPE_128, 128, 128, 2, {0.413, 0.786}, {5.27, 6.24},
+     0.197, 0.198, 0.0685, 0.0555, -0.161, -0.039, 0.944, 0.0514},
+};
+
+static double predicted_us(const TileForm &f, const Problem &p, int64_t cus) {
+  const int64_t tiles = ((p.m + f.bm - 1) / f.bm) * ((p.n + f.bn - 1) / f.bn);
+  const int64_t full = tiles / (f.per_cu * cus), rest = (tiles % (f.per_cu * cus) + cus - 1) / cus;
+  const bool whole = p.m % f.bm == 0 && p.n % f.bn == 0;
+  // (rows of C that do not start on 16 bytes cost the 128-deep kernels more: (1372, 1583, 1094) packed, accumulating,
+  // 31 us on 128 x 128 tiles of theirs, 20 on 64 x 128 ones; (3151, 3795, 633), overwriting, 30 and 27 on 128 x 128 ones)
+  const bool unaligned_c = p.ldc * (p.out_float == 2 ? 1 : 4) % 16 || reinterpret_cast<uintptr_t>(p.C) % 16;
+  // (the 64-deep kernels and the form for whole tiles read the sums that packed weights bring)
+  const bool sums = !(p.ksum && (f.kind == KIND_DMA || dma_k128_eligible(p, true)));
+  const double slower = 1 + (sums && p.a_unsigned ? f.a_unsigned : 0) + (sums && p.b_unsigned ? f.b_unsigned : 0) +
+                        (p.a_sk == 1 ? 0 : f.a_strided) + (p.b_sk == 1 ? 0 : f.b_strided) + (whole ? f.whole : 0);
+  const double blocks = (double)p.k / 128 * slower, words = 1e-6 * (double)p.m * (double)p.n;
+  return (double)full * (f.block[f.per_cu - 1] * blocks + f.ends[f.per_cu - 1]) +
+         (rest ? f.block[rest - 1] * blocks + f.ends[rest - 1] : 0) + words * (p.out_float == 2 ? 0 : f.words) +
+         (p.accumulate ? words * f.old_words : 0) +
+         (unaligned_c && f.kind != KIND_DMA ? words * (p.accumulate ? 4 : 0.3) : 0) +
+         1e-6 * (double)(p.m + p.n) * (double)p.k * f.operands;
+}
+
+// The form that takes least by these times, if that is an eighth under those of the plan chosen so far.  The rules of
+// choose_plan were each measured at a few products on either side of their lines; between them one tile more than a
+// round, or a side a little over a multiple of a tile, costs up to a half.  Over 2500 other products, half
+// of them cold, with packed weights and unaligned operands among them, it takes 0.976 of the time without it: 373
+// are faster by more than 3 %, up to 1.8 times, 69 slower by more than that, 3 by more than a tenth.
+// Measured, us, before and after: (512, 5760, 6400) with an unsigned A 65 -> 36 (180 tiles of 128 x 128 for 360 of
+// 128 x 64), (3840, 640, 2176) cold 18.8 -> 12.9, (496, 4432, 3840) 29 -> 19, (3440, 8992, 640) 61 -> 43 (128-deep blocks),
+// row-major B (736, 3856, 5120) to int8 40 -> 24.
+// From 200 tiles of 64 x 64 on: fewer are a matter of splitting k, as are forms with less than half a round of tiles.
+// Between the tiles of 128 x 128 and less: whether sides of 192 or 256 pay is settled before.
+static Plan fastest_tiles(const Problem &p, Plan plan) {
+  const int64_t cus = compute_units();
+  if (p.conv || p.batch > 1 || p.k < 512 || p.m < 128 || p.n < 128 || plan.splits != 1 || tile_count(p, SHAPE_64) < 200)
+    return plan;
+  const TileForm *now = nullptr;
+  for (const TileForm &f : kTileForms)
+    if (f.shape == plan.shape && (f.kind == KIND_DMA) == (plan.kind == KIND_DMA)) now = &f;
+  if (!now || plan.kind == KIND_STAGED) return plan;
+  const double before = predicted_us(*now, p, cus);
+  double best = before;
+  // What the model, fitted to operands that partly come from the last-level cache, does not see: 64 x 64 tiles depend most
+  // on where theirs come from ((1200, 6752, 640) strided, cold, 18.9 us on 128 x 128, 23.7 on these), two groups
+  // of waves on them serve k-contiguous ones best ((2160, 688, 6656) cold 25.3 us, 29.9 on 128 x 64), and whole
+  // 128 x 128 tiles hold at a short k ((2304, 1536, 512) to int8 7.4 us, 8.5 on 64 x 64).
+  if (plan.shape == SHAPE_64 && p.a_sk == 1 && p.b_sk == 1) return plan;
+  if (plan.kind == KIND_DMA_K128 && p.k < 1024) return plan;
+  for (const TileForm &f : kTileForms) {
+    const bool deep = f.kind != KIND_DMA;
+    const double margin = f.shape == SHAPE_64 ? 0.8 : 0.88;
+    if (2 * ((p.m + f.bm - 1) / f.bm) * ((p.n + f.bn - 1) / f.bn) <= cus) continue;
+    if (deep ? !dma_k128_split_eligible(p) : !dma_eligible(p, f.shape)) continue;
+    if (const double us = predicted_us(f, p, cus); us < best && us < margin * before) {
+      best = us;
+      plan = {deep && dma_k128_eligible(p, true) ? KIND_DMA_K128 : f.kind, f.shape, 1};
+    }
+  }
+  return plan;
+}
+
 Plan choose_plan(const Problem &p) {
   const int64_t kComputeUnits = compute_units();
   if (p.m == 0 || p.n == 0) return {KIND_NONE, SHAPE_64, 1};
@@ -534,6 +621,7 @@ Plan choose_plan(const Problem &p) {
     // The wide side goes across the operand that is dearer to fetch again, a column-major A:
     // 8191 x 8193 x 8195 with such an A 4570 us on 128 x 64 tiles, 2570 on 64 x 128.
     else plan = {KIND_STAGED, sh == SHAPE_256 || sh == SHAPE_128 ? (p.a_sk == 1 ? SHAPE_128X64 : SHAPE_64X128) : sh, 1};
+    plan = fastest_tiles(p, plan);
   }
   const bool pinned = *tuning().variant || forced_splits() > 0;
   if (!pinned && (plan.kind == KIND_STAGED || plan.kind == KIND_DMA) && plan.shape == SHAPE_64)
