@@ -107,7 +107,7 @@ __device__ __forceinline__ void store_rows_via_lds(const v16i (&acc)[1][2], int3
 // TO_FLOAT, ACCUMULATE: what the write-back does, fixed at compile time.
 // PADDED: filter rows in whole pieces.  The 7 x 7 x 3 filters of a network's first layer take seven steps instead
 // of five, but one unaligned LDS read instead of two and none of some thirty mask instructions each:
-// 30.9 -> 29.2 us for a batch of 32 images of 224 x 224.
+// 31.0 -> 25.3 us for a batch of 32 images of 224 x 224.
 template <bool TO_FLOAT, bool ACCUMULATE, bool PADDED>
 __global__ __launch_bounds__(NTHREADS_ROWS) void conv_rows_kernel(RowsParams P) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -130,12 +130,17 @@ __global__ __launch_bounds__(NTHREADS_ROWS) void conv_rows_kernel(RowsParams P) 
     if constexpr (PADDED) {
       const int e = 2 * ks + (l >> 5), y = e / P.row_pieces, at = 16 * (e - y * P.row_pieces);
       const int have = y < P.hf && co < P.n ? (wfci - at < 16 ? wfci - at : 16) : 0;
-      const uint8_t *piece = P.F + (int64_t)(co < P.n ? co : P.n - 1) * P.k + (y < P.hf ? y * wfci + at : 0);
-      v4i f = {0, 0, 0, 0};
+      // Sixteen bytes wherever the piece lies, what follows it masked off (a piece at the end of the
+      // tensor: the tensor's last sixteen, shifted).  Sixteen loads of a byte took up to 4 us more a call: 2 images of
+      // 28 x 56 x 10 under 128 filters of 4 x 4 took 10.9 us, 6.6 unpadded; 8 such images under 96
+      // filters to float take 7.4 so, 8.2 unpadded.
+      const int64_t off = (int64_t)(co < P.n ? co : P.n - 1) * P.k + (y < P.hf ? y * wfci + at : 0);
+      const int64_t last = (int64_t)P.n * P.k - 16;  // (not negative: see fill_params)
+      v4i f = shifted_down(load16(P.F + (off < last ? off : last)), off < last ? 0 : (int)(off - last));
 #pragma unroll
-      for (int b = 0; b < 16; ++b) {
-        const uint32_t x = piece[b < have ? b : 0];
-        f[b >> 2] |= (int)((b < have ? x : 0u) << (8 * (b & 3)));
+      for (int d = 0; d < 4; ++d) {
+        const int cnt = have - 4 * d;  // bytes of this word that belong to the piece
+        f[d] &= cnt >= 4 ? -1 : (cnt <= 0 ? 0 : (1 << (8 * cnt)) - 1);
       }
       ffrag[slot] = f;
       continue;
@@ -394,8 +399,12 @@ bool fill_params(const Problem &p, RowsParams *out) {
   P.k = (int)p.k;
   P.ksteps = (int)ksteps;
   P.row_pieces = 0;
+  // Padded wherever the steps fit beside the image.  Over 700 geometries (1 to 24 channels, filters from 1 x 1 to
+  // 11 x 11, batches of 1 to 32) that takes 0.87 of the time of the unpadded form, by how many times its steps: 0.86
+  // as many to 1.5 times, 0.90 at twice (filter rows below 16 bytes, which that form reads byte by
+  // byte), 1.00 at four times (7 x 1 filters over 2 channels); one is slower by more than 3 %.
   const int64_t row_pieces = (wfci + 15) / 16, padded_steps = (hf * row_pieces + 1) / 2;
-  if (padded_steps <= 32 && (padded_steps <= 2 * ksteps || wfci < 16) && 2 * stage + padded_steps * 2048 + FIXED_LDS <= MAX_LDS) {
+  if (padded_steps <= 32 && p.n * p.k >= 16 && 2 * stage + padded_steps * 2048 + FIXED_LDS <= MAX_LDS) {
     P.row_pieces = (int)row_pieces;
     P.ksteps = (int)padded_steps;
   }

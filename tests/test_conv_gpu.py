@@ -578,3 +578,39 @@ def test_supplied_filter_sums_with_ranges_of_k(gpu, oracle, splits):
     with gpu.tuning(MIPGEMM_SPLITK=str(splits)):
         gpu.mipgemm_conv_s8u8s32_with_sums(b, hi, hi, ci, co, hf, hf, stride, pad, dF, dI, dO, W.OVERWRITE, sums)
     assert np.array_equal(dO.cpu().numpy(), want.reshape(-1))
+
+
+# ---------------------------------------------------------------------------
+# the row-segment kernel's forms: filter rows padded to whole 16-byte pieces, and not
+# ---------------------------------------------------------------------------
+
+def _rows_in_every_output(gpu, oracle, shape, seed):
+    """The row-segment kernel into int32 (both modes), float and int8, against the direct convolution."""
+    import torch
+    b, hi, wi, ci, co, hf, wf, s, p = shape
+    I, F = tensors(shape, seed)
+    want = oracle.conv_direct(I, F, s, p)
+    O0 = np.random.default_rng(seed).integers(-1000, 1000, size=want.shape, dtype=np.int32)
+    for mode in (0, 1):
+        got = run_conv(gpu, shape, I, F, O0, mode, MIPGEMM_CONV="rows")
+        assert np.array_equal(got, want + (O0 if mode else 0)), (shape, mode)
+    scale = float(np.float32(100.0 / (np.abs(want).max() + 1)))
+    dI, dF = torch.from_numpy(I).cuda(), torch.from_numpy(F.view(np.uint8)).cuda()
+    quotient = want.astype(np.float32) * np.float32(scale)
+    with Env(MIPGEMM_CONV="rows"):
+        dO = torch.full(want.shape, 7.0, dtype=torch.float32, device="cuda")
+        gpu.mipgemm_conv_s8u8f32(b, hi, wi, ci, co, hf, wf, s, p, dF, dI, dO, 0, scale=scale)
+        assert np.array_equal(dO.cpu().numpy(), quotient), shape
+        dQ = torch.full(want.shape, 7, dtype=torch.int8, device="cuda")
+        gpu.mipgemm_conv_s8u8s8(b, hi, wi, ci, co, hf, wf, s, p, dF, dI, dQ, 0, scale=scale)
+        assert np.array_equal(dQ.cpu().numpy(), np.clip(np.rint(quotient), -128, 127).astype(np.int8)), shape
+
+
+@pytest.mark.parametrize("shape", [
+    # filter tensors of fewer than 16 bytes, of exactly 16, and of one more: pieces are read 16 bytes wide
+    (1, 9, 9, 1, 3, 2, 2, 1, 0), (1, 9, 9, 5, 1, 3, 1, 1, 1), (1, 9, 9, 2, 2, 2, 2, 1, 0), (1, 9, 20, 17, 1, 1, 1, 1, 0),
+    # last pieces of 1, 8 and 15 bytes, whole pieces, an odd number of them, filters past one workgroup's 64
+    (1, 9, 9, 1, 70, 3, 17, 1, 8), (1, 12, 40, 8, 65, 2, 3, 1, 0), (1, 12, 40, 5, 5, 3, 3, 2, 1), (1, 12, 40, 16, 3, 3, 2, 1, 1)],
+    ids=lambda s: "x".join(map(str, s)))
+def test_row_segment_kernel_with_filters_that_end_in_a_piece(gpu, oracle, shape):
+    _rows_in_every_output(gpu, oracle, shape, 31)
