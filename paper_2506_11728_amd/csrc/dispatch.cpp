@@ -182,17 +182,17 @@ hipError_t allow_dynamic_lds(const void *kernel, size_t bytes) {
   static std::vector<Granted> granted;  // a few dozen kernels at most
   int device = 0;
   hipError_t e = hipGetDevice(&device);
-  if (e != hipSuccess) return e;
-  std::lock_guard<std::mutex> guard(lock);
-  for (Granted &g : granted)
-    if (g.kernel == kernel && g.device == device) {
-      if (g.bytes >= bytes) return hipSuccess;
-      e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-      if (e == hipSuccess) g.bytes = bytes;
-      return e;
-    }
-  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess) granted.push_back({kernel, device, bytes});
+  if (e == hipSuccess) {
+    std::lock_guard<std::mutex> guard(lock);
+    Granted *known = nullptr;
+    for (Granted &g : granted)
+      if (g.kernel == kernel && g.device == device) known = &g;
+    if (known && known->bytes >= bytes) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess && known) known->bytes = bytes;
+    else if (e == hipSuccess) granted.push_back({kernel, device, bytes});
+  }
+  if (e != hipSuccess) (void)hipGetLastError();  // (as in launch_with)
   return e;
 }
 

@@ -126,7 +126,9 @@ hipError_t allow_dynamic_lds(const void *kernel, size_t bytes);
 // convolution needs are at the end of a structure of their own.
 inline hipError_t launch_with(const void *kernel, dim3 grid, unsigned threads, size_t lds, hipStream_t s, const void *args) {
   void *list[] = {const_cast<void *>(args)};
-  return hipLaunchKernel(kernel, grid, dim3(threads), list, lds, s);
+  const hipError_t e = hipLaunchKernel(kernel, grid, dim3(threads), list, lds, s);
+  if (e != hipSuccess) (void)hipGetLastError();  // (the caller gets it; the next check of theirs must not find it again)
+  return e;
 }
 
 const char *plan_name(const Plan &plan);  // static string

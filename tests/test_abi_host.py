@@ -408,3 +408,29 @@ def test_products_that_keep_tiles_with_sides_of_128_and_256(M, m, n, k, oa, ob, 
 def test_names_of_convolutions_through_the_written_out_matrix(M, shape, name):
     b, hw, ci, co, f = shape
     assert M.mipgemm_conv_variant_name(b, hw, hw, ci, co, f, f, 1, f // 2) == name
+
+
+def test_a_refused_launch_is_reported_once(tmp_path):
+    """The runtime keeps the error of a refused call for the next hipGetLastError: the entry points return it and clear it."""
+    import shutil
+    import subprocess
+    from paper_2506_11728_amd import build
+    if not shutil.which("g++") or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("nothing to build it with")
+    source = tmp_path / "refused.cpp"
+    source.write_text("""
+#include "mip_internal.h"
+#include <cstdio>
+static hipError_t last = hipSuccess;   // a runtime that refuses every launch
+extern "C" hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { return last = hipErrorInvalidConfiguration; }
+extern "C" hipError_t hipGetLastError() { const hipError_t e = last; last = hipSuccess; return e; }
+int main() {
+  int args = 0;
+  const hipError_t e = mip::launch_with(&args, dim3(1), 64, 0, nullptr, &args);
+  std::printf("%d %d", e == hipErrorInvalidConfiguration, hipGetLastError() == hipSuccess);
+}
+""")
+    program = tmp_path / "refused"
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(build.HERE, "csrc"),
+                    str(source), "-o", str(program)], check=True, timeout=120)
+    assert subprocess.run([str(program)], capture_output=True, text=True, timeout=60).stdout == "1 1"
