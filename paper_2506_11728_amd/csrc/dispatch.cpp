@@ -621,7 +621,8 @@ Plan choose_plan(const Problem &p) {
     // The wide side goes across the operand that is dearer to fetch again, a column-major A:
     // 8191 x 8193 x 8195 with such an A 4570 us on 128 x 64 tiles, 2570 on 64 x 128.
     else plan = {KIND_STAGED, sh == SHAPE_256 || sh == SHAPE_128 ? (p.a_sk == 1 ? SHAPE_128X64 : SHAPE_64X128) : sh, 1};
-    plan = fastest_tiles(p, plan);
+    // (a pinned number of ranges holds for the 64-deep tiles: nothing else may take their place then)
+    if (forced_splits() == 0) plan = fastest_tiles(p, plan);
   }
   const bool pinned = *tuning().variant || forced_splits() > 0;
   if (!pinned && (plan.kind == KIND_STAGED || plan.kind == KIND_DMA) && plan.shape == SHAPE_64)

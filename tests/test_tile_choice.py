@@ -27,6 +27,13 @@ def test_choice(shape, name):
     assert _name(*shape) == name
 
 
+def test_pinned_ranges_keep_the_tiles_that_take_them():
+    """A pinned number of k ranges names the 64-deep tiles it is for: forms that do not split k stay out."""
+    with M.tuning(MIPGEMM_SPLITK="4"):
+        assert _name(512, 5760, 6400, 0, 1) == "mfma_dma64x128"
+        assert _name(496, 4432, 3840, 0, 0) == "mfma_dma64x128"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", [(496, 1776, 640), (1376, 1584, 1152), (752, 2704, 1600), (416, 2048, 1664), (1371, 1583, 1094)],
                          ids=lambda s: "x".join(map(str, s)))
