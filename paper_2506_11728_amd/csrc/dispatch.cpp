@@ -224,15 +224,19 @@ static int64_t tile_count(const Problem &p, Shape s) {
 // grows as the tile shrinks, most for a strided operand, whose pieces of a row are 32 or 64 bytes.
 // So: the smallest tile of which there is one round, for a k that is long enough, and no longer than what the
 // 64 x 64 tiles need that can split k over workgroups (through atomics, cheapest into an int32 C that needs no
-// zero fill, or through slots).
-// Measured over 1500 aligned products of 1 to 400 tiles of 64 x 64 (k = 64 to 8192), the rule takes 0.88 of
-// the time without it, the best choice each time 0.86; over 1200 unaligned ones 0.63 and 0.59.
+// zero fill and into one of few rows, or through slots).  The fewer the tiles, the more ranges of k
+// there is room for, and the shorter the k up to which one workgroup to a tile keeps up.
+// Measured over 16000 products, batches and convolutions of up to 1200 tiles of 32 x 32 (k = 16 to 60000), aligned and
+// not, the rule takes 0.793 of the time without it; 304 are slower by more than 5 %, 88 by more than a tenth.
 // us, before and after: (512, 512, 2048) k-contiguous 6.5 -> 4.2, (256, 256, 1024) 4.4 -> 3.7, (64, 4096, 11008) u8
-// packed 16.2 -> 12.8, row-major B (1024, 512, 4096) 12.3 -> 9.9;
+// packed 14.8 -> 12.9, row-major B (1024, 512, 4096) 12.3 -> 9.9;
 // a 3 x 3 convolution of 7 x 7 x 512 at batch 8 19.7 -> 7.4; unaligned (32, 256, 3600) to int8 35 -> 12.9,
 // (42, 2368, 2112) 22.9 -> 6.5, (1024, 70, 1024) 18.2 -> 4.8, (459, 1024, 836) packed before 7.9 -> 6.1.
-// On the other side of the lines: (1024, 1024, 1024) 5.1 on 64 x 64 tiles and 6.6, (1024, 512, 1024) row-major 4.75
-// and 5.1, (304, 208, 6144) column-major A 16.8 packed and 21.
+// On the other side of the lines, us without this form and with it: (1024, 1024, 1024) 5.1 and 6.6, (1024, 512, 1024)
+// row-major 4.75 and 5.1, (304, 208, 6144) column-major A 16.8 packed and 21; a long k: (14, 512, 11136) 6.1 and 7.6, 11 x 11
+// filters over 448 channels, 176 positions and 7 filters, 11.0 and 38, (64, 1162, 53696) 28 and 46; adding into C:
+// (2, 246, 3712) 3.6 and 5.2, (206, 32, 3584) 4.1 and 5.2, unaligned (128, 128, 1472) with both operands strided
+// 4.9 and 8.5; 21 unaligned products of (357, 64, 64) 4.2 and 7.8.
 static Wave wave_form(const Problem &p, bool streamed) {
   if (p.k < 1 || (p.batch > 1 && p.out_float == 2)) return WAVE_NONE;
   const int64_t cus = compute_units(), k = p.k, batch = p.batch > 1 ? p.batch : 1;
@@ -241,28 +245,38 @@ static Wave wave_form(const Problem &p, bool streamed) {
   const bool adds = p.accumulate && !p.out_float;
   const bool may_split = (!p.out_float || (p.ws && streamed)) &&
                          (p.accumulate || p.out_float ? 2 * tiles(64, 64) <= target : 2 * tiles(64, 64) < target);
-  const int64_t any = INT64_MAX / 4;
+  const int64_t any = INT64_MAX / 4, small = tiles(32, 32);
+  const int strided = (p.a_sk != 1) + (p.b_sk != 1);
   if (streamed) {
     if (!wave_streamed_eligible(p)) return WAVE_NONE;
-    const int strided = (p.a_sk != 1) + (p.b_sk != 1);
     // (row-major (192, 448, 3904), 84 tiles of 32 x 32: 8.2 us on 21 of 64 x 64 in four ranges, 10.0 here)
-    static const int64_t adding[3] = {4096, 2560, 1792}, few[3] = {any, 4096, 3072}, other[3] = {any, 3072, 2048};
-    const int64_t most = !may_split ? any : (adds ? adding : (4 * tiles(32, 32) <= cus ? few : other))[strided];
-    if (tiles(32, 32) <= cus) return k < most && (!p.conv || k >= 512) ? WAVE_32 : WAVE_NONE;
+    int64_t most = any;
+    if (may_split && adds) {
+      most = strided == 2 ? 1792 : (strided ? 2560 : (4 * small <= cus ? 2048 : 4096));
+    } else if (may_split && strided) {
+      most = 4 * small <= cus ? (strided == 2 ? 3072 : 4096) : (strided == 2 ? 2048 : 3072);
+    } else if (may_split && short_side <= 16) {
+      if (4 * small <= cus) most = 5120;
+    } else if (may_split && 2 * small <= cus) {
+      most = 16 * small <= cus ? 10240 : 16384;
+    }
+    if (small <= cus) return k < most && (!p.conv || k >= 512) ? WAVE_32 : WAVE_NONE;
     if (tiles(32, 64) <= cus && p.a_sk == 1) return k >= (strided ? 1536 : 1024) && k < 2 * most ? WAVE_32X64 : WAVE_NONE;
     return WAVE_NONE;
   }
   if (!wave_staged_eligible(p) || tuning().pack > 0) return WAVE_NONE;
   // (with a workspace, larger products are packed)
-  const bool packable = packing_serves(p);
-  int64_t most = !may_split ? any : (adds ? 1536 : 4096);
+  const bool packable = packing_serves(p), whole = p.m % 64 == 0 && p.n % 64 == 0, few = 64 * small <= cus;
+  int64_t most = !may_split ? any : (adds ? (few ? 1024 : (strided == 2 && whole ? 512 : 1536)) : (few ? 3072 : 4096));
   if (packable && most > 4096) most = 4096;
   // (both operands strided and a short k: packed, a choice that a test names; (300, 200, 333) 5.8 us, 4.3 here)
-  if (packable && p.a_sk != 1 && p.b_sk != 1 && k < 512) return WAVE_NONE;
-  if (tiles(32, 32) <= cus) return k < most ? WAVE_32 : WAVE_NONE;
+  if (packable && strided == 2 && k < 512) return WAVE_NONE;
+  // A batch of short sums is a matter of how many workgroups start, and these have twice the threads.
+  if (small <= cus) return k < most && (batch == 1 || k > 64) ? WAVE_32 : WAVE_NONE;
   if (packable) return WAVE_NONE;
-  if (tiles(32, 64) <= cus && k < most) return WAVE_32X64;
-  return tiles(32, 32) <= 3 * cus && k >= 512 ? WAVE_32 : WAVE_NONE;
+  if (tiles(32, 64) <= cus && k < most)
+    return k >= (batch > 1 ? (p.accumulate ? 768 : 192) : 96) ? WAVE_32X64 : WAVE_NONE;
+  return small <= 3 * cus && k >= 512 ? WAVE_32 : WAVE_NONE;
 }
 
 size_t splitk_slot_bytes(const Problem &p, const Plan &plan) {

@@ -17,3 +17,21 @@ def oracle():
     import oracle as _oracle
     _oracle.build()
     return _oracle
+
+
+@pytest.fixture(scope="session")
+def kernels_of():
+    """The names of the kernels that a call launches, in order, as the profiler reports them (template arguments included)."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    def names(call):
+        call()  # (once outside, so that nothing is set up inside)
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            call()
+            torch.cuda.synchronize()
+        found = [e.name for e in p.events() if "mip::" in e.name]
+        assert found, [e.name for e in p.events()]
+        return found
+    return names

@@ -138,3 +138,42 @@ def test_what_the_dispatcher_sends_there(gpu):
                 getattr(gpu, "mipgemm_s8s8" + out)(m, n, k, A, k, 0, B, k, 1, C, n, 0, 0, **({} if out == "s32" else {"scale": 0.0005}))
             results.append(C.cpu())
         assert torch.equal(*results), (m, n, k, out)
+
+
+# (m, n, k, accumulate, pad, whether this form serves): both sides of the limits of k, which are the lower the fewer rows and
+# tiles there are, lower still for a call that adds into C
+@pytest.mark.parametrize("m,n,k,mode,pad,served", [
+    (512, 512, 2048, 0, 0, True), (14, 512, 4096, 0, 0, True), (14, 512, 11136, 0, 0, False), (64, 512, 8192, 0, 0, True),
+    (64, 1152, 53696, 0, 0, False), (206, 32, 1536, 1, 0, True), (206, 32, 3584, 1, 0, False), (512, 512, 3584, 1, 0, True),
+    (40, 50, 900, 1, 1, True), (40, 50, 1200, 1, 1, False), (40, 50, 2900, 0, 1, True), (40, 50, 3500, 0, 1, False)])
+def test_which_products_the_dispatcher_sends_there(gpu, kernels_of, m, n, k, mode, pad, served):
+    import torch
+    A = torch.zeros((m, k + pad), dtype=torch.int8, device="cuda")
+    B = torch.zeros((n, k + pad), dtype=torch.int8, device="cuda")
+    C = torch.zeros((m, n), dtype=torch.int32, device="cuda")
+    names = kernels_of(lambda: gpu.mipgemm_s8s8s32(m, n, k, A, k + pad, 0, B, k + pad, 1, C, n, 0, mode))
+    assert any("wave_tile_kernel" in x for x in names) == served, names
+
+
+@pytest.mark.parametrize("m,n,k,batch,mode,served", [
+    (357, 64, 64, 21, 0, False), (357, 64, 320, 21, 0, True), (357, 64, 320, 21, 1, False), (16, 16, 64, 44, 0, False),
+    (16, 16, 96, 44, 0, True)])
+def test_which_batches_the_dispatcher_sends_there(gpu, kernels_of, m, n, k, batch, mode, served):
+    import torch
+    A = torch.zeros((batch, m, k + 1), dtype=torch.int8, device="cuda")
+    B = torch.zeros((batch, n, k + 1), dtype=torch.int8, device="cuda")
+    C = torch.zeros((batch, m, n), dtype=torch.int32, device="cuda")
+    names = kernels_of(lambda: gpu.mipgemm_s8s8s32_batched(m, n, k, A, k + 1, 0, m * (k + 1), B, k + 1, 1, n * (k + 1), C, n, 0,
+                                                           m * n, batch, mode))
+    assert any("wave_tile_kernel" in x for x in names) == served, names
+
+
+@pytest.mark.parametrize("shape,served", [((8, 7, 7, 512, 512, 3, 3, 1, 1), True), ((22, 7, 16, 448, 7, 11, 11, 4, 5), False)])
+def test_which_convolutions_the_dispatcher_sends_there(gpu, kernels_of, shape, served):
+    import torch
+    b, hi, wi, ci, co, hf, wf, stride, pad = shape
+    I = torch.zeros(b * hi * wi * ci, dtype=torch.uint8, device="cuda")
+    F = torch.zeros(co * hf * wf * ci, dtype=torch.int8, device="cuda")
+    O = torch.zeros(b * ((hi + 2 * pad - hf) // stride + 1) * ((wi + 2 * pad - wf) // stride + 1) * co, dtype=torch.int32, device="cuda")
+    names = kernels_of(lambda: gpu.mipgemm_conv_s8u8s32(*shape, F, I, O, 0))
+    assert any("wave_tile_kernel" in x for x in names) == served, names
