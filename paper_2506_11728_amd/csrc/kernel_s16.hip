@@ -639,11 +639,14 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
   // rewrites them and one more pass over them: 64 x 64 tiles each read theirs again, so up to a product of
   // tiles and k.  Over 160 drawn products 0.78 of the time; us, rewritten and as they are: (128, 204, 64) 8.8 and 4.9,
   // (799, 757, 602) 17.6 and 13.1, (512, 1603, 1792) 27.2 and 27.0, but (682, 2790, 2848) 54 and 60,
-  // (2965, 1216, 2153) 58 and 74.
+  // (2965, 1216, 2153) 58 and 74.  One or two tiles under a very long k pay more for a block through registers than the
+  // rewriting costs: over 5000 products, those of one tile, k = 4096 to 8192, 1.01 of the time overwriting and 0.88
+  // accumulating, up to 16384 1.07 and 0.97; (10, 10, 14213) 21.9 and 28.2, accumulating (14, 15, 14340) 21.4 and 27.4.
   bool staged = !streamable(X[0], s_r[0], s_k[0], rows[0], p.k) || !streamable(X[1], s_r[1], s_k[1], rows[1], p.k);
   for (int i = 0; i < 2; ++i) staged = staged && (s_k[i] == 1 ? p.k : rows[i]) >= 8;
   staged = staged && (!std::strcmp(tuning().variant, "s16_staged") ||
-                      (!*tuning().variant && tuning().splitk == 0 && (double)tiles(64) * (double)p.k <= 1600.0 * (double)cus));
+                      (!*tuning().variant && tuning().splitk == 0 && (double)tiles(64) * (double)p.k <= 1600.0 * (double)cus &&
+                       p.k <= (p.accumulate ? 8192 : 4096) * tiles(64)));
   // what cannot be streamed is rewritten into the front of the workspace first
   Pack16Job job[2] = {};
   for (int i = 0; i < 2 && !staged; ++i) {
@@ -702,7 +705,9 @@ hipError_t launch_s16(const S16Problem &p, hipStream_t s) {
     // The ranges meet in slots, where the workspace has room for at least half of them.  (A captured
     // call, whose counters are never handed out again, does as well without.)
     const int64_t room = (end - ws) / (count * side * side * 4), fit = room < splits ? room : splits;
-    if (fit > 1 && 2 * fit >= splits && !being_captured(s) &&
+    // (Accumulating into C from operands read as they are: without slots, which cost 0.84 of the time of rewritten operands
+    // over 2494 products where adding takes 0.77; (72, 151, 1289) 9.2 rewritten, 14.3 through slots.)
+    if (!(staged && p.accumulate) && fit > 1 && 2 * fit >= splits && !being_captured(s) &&
         splitk_tickets(count, s, nullptr, &P.tickets) == hipSuccess) {
       P.slots = reinterpret_cast<int32_t *>(ws);
       splits = fit;

@@ -350,3 +350,25 @@ def test_unaligned_operands_read_as_they_are(gpu, shape, mode):
                 gpu.mipgemm_s16s16s32(m, n, k, A, lda, oa, B, ldb, ob, C, C0.shape[1], oc, mode, workspace=ws,
                                       workspace_bytes=ws.numel())
             assert np.array_equal(C.cpu().numpy(), want), (oa, ob, oc, pad)
+
+
+@pytest.mark.parametrize("m,n,k,mode,rewritten", [(10, 10, 14213, 0, True), (10, 10, 14213, 1, True), (10, 10, 4003, 0, False),
+                                                  (10, 10, 8001, 1, False), (70, 70, 14213, 0, False), (799, 757, 602, 0, False),
+                                                  (1216, 2965, 2153, 0, True)])
+def test_which_unaligned_operands_are_rewritten(gpu, kernels_of, m, n, k, mode, rewritten):
+    import torch
+    A = torch.zeros(m * (k + 1), dtype=torch.int16, device="cuda")
+    B = torch.zeros(n * (k + 1), dtype=torch.int16, device="cuda")
+    C = torch.zeros(m * n, dtype=torch.int32, device="cuda")
+    size = gpu.mipgemm_workspace_size_s16(m, n, k)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    names = kernels_of(lambda: gpu.mipgemm_s16s16s32(m, n, k, A, k + 1, 0, B, k + 1, 1, C, n, 0, mode, workspace=ws, workspace_bytes=size))
+    assert any("pack16" in x for x in names) == rewritten, names
+
+
+@pytest.mark.parametrize("m,n,k", [(72, 151, 1289), (6, 7, 4315), (139, 223, 572)])
+def test_adding_in_ranges_of_k_from_unaligned_operands(gpu, oracle, m, n, k):
+    """The ranges meet in C, whatever room for slots the workspace has."""
+    for oa in (0, 1):
+        for ob in (0, 1):
+            _check(gpu, oracle, m, n, k, oa, ob, 0, 1, 1)
