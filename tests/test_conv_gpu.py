@@ -614,3 +614,21 @@ def _rows_in_every_output(gpu, oracle, shape, seed):
     ids=lambda s: "x".join(map(str, s)))
 def test_row_segment_kernel_with_filters_that_end_in_a_piece(gpu, oracle, shape):
     _rows_in_every_output(gpu, oracle, shape, 31)
+
+
+@pytest.mark.parametrize("shape", [
+    # the padded filters of these do not fit beside the image: filter rows of 16 bytes and more, read as two runs (27, 35, 75 bytes),
+    (1, 12, 560, 3, 70, 9, 9, 4, 4), (2, 15, 40, 5, 64, 7, 7, 3, 3), (1, 9, 133, 15, 65, 5, 5, 1, 2),
+    # and shorter ones, read byte by byte
+    (1, 15, 60, 7, 66, 7, 1, 3, 3), (2, 13, 40, 9, 5, 6, 1, 3, 0)],
+    ids=lambda s: "x".join(map(str, s)))
+def test_row_segment_kernel_without_room_for_padded_filters(gpu, oracle, kernels_of, shape):
+    import torch
+    _rows_in_every_output(gpu, oracle, shape, 32)
+    b, hi, wi, ci, co, hf, wf, s, p = shape
+    I, F = (torch.from_numpy(x.view(np.uint8)).cuda() for x in tensors(shape, 32))
+    O = torch.zeros(b * oracle.conv_out_extent(hi, hf, s, p) * oracle.conv_out_extent(wi, wf, s, p) * co,
+                    dtype=torch.int32, device="cuda")
+    with Env(MIPGEMM_CONV="rows"):
+        names = kernels_of(lambda: gpu.mipgemm_conv_s8u8s32(*shape, F, I, O, 0))
+    assert any("conv_rows_kernel<false, false, false>" in x for x in names), names  # (the last: not padded)
