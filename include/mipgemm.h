@@ -180,6 +180,12 @@ int mipgemm_s8u8s32(int64_t m, int64_t n, int64_t k,
  * K^T Q and V E_1 for every head i and sequence j), made one launch, because
  * each of those products alone is far too small to occupy the device.  Everything
  * else is as for mipgemm_s8s8s32.  batch <= 65535; batch == 0 does nothing.
+ * A batch that shares B while A and C continue from problem to problem as the rows
+ * of one matrix would (strideA = m*lda and strideC = m*ldc row-major, m column-major),
+ * or shares A while B and C continue as the columns of one would, runs as the one
+ * product of batch*m rows (batch*n columns), which takes the packed route as such:
+ * the workspace that can serve it is mipgemm_workspace_size of that product.  Other
+ * batches use no workspace.
  * Argument numbers: m=1 n=2 k=3 A=4 lda=5 orderA=6 strideA=7 B=8 ldb=9 orderB=10
  * strideB=11 C=12 ldc=13 orderC=14 strideC=15 batch=16 mode=17 workspace=18
  * workspace_bytes=19 stream=20.
@@ -530,7 +536,9 @@ int mipgemm_u8s8s32_packed(int64_t m, int64_t n, int64_t k,
  * 96, k below 192, m*n*k below 2^22), and for invalid sizes.  Operands with other leading
  * dimensions or pointers need (round_up(m, 256) + round_up(n, 256)) * kp bytes,
  * kp = k rounded up to a multiple of 128 (of 64 when k < 1024); a call uses the packed route whenever
- * it would pay and the workspace it is given is that large.
+ * it would pay and the workspace it is given is that large.  (The sizes do not say everything: a call may be
+ * served faster from its operands as they are, by its mode or its output type, and then leaves
+ * the workspace alone.)
  */
 size_t mipgemm_workspace_size(int64_t m, int64_t n, int64_t k,
                               int orderA, int orderB, int orderC);

@@ -127,25 +127,6 @@ static int use_packed(Problem *p, const void *Ap, const void *Bp) {
   return which;
 }
 
-// A batch that shares one operand and steps through the other and through C as one matrix would is one
-// product with that many times the rows (or columns): it may be packed, and takes tiles by its whole size.
-// (Three products of 1024 x 641 x 1024 with one unaligned B: 18.1 -> 9.5 us.)
-static void fold_batch(Problem *p) {
-  const int64_t batch = p->batch;
-  if (batch <= 1 || p->m == 0 || p->n == 0 || p->k == 0) return;
-  if (p->b_sb == 0 && p->c_sb == p->m * p->ldc && p->m * batch <= MIPGEMM_MAX_DIM &&
-      (p->a_sk == 1 ? p->a_sb == p->m * p->a_sm : p->a_sb == p->m && p->a_sk >= p->m * batch)) {
-    p->m *= batch;
-  } else if (p->a_sb == 0 && p->c_sb == p->n && p->ldc >= p->n * batch && p->n * batch <= MIPGEMM_MAX_DIM &&
-             (p->b_sk == 1 ? p->b_sb == p->n * p->b_sn : p->b_sb == p->n && p->b_sk >= p->n * batch)) {
-    p->n *= batch;
-  } else {
-    return;
-  }
-  p->batch = 1;
-  p->a_sb = p->b_sb = p->c_sb = 0;
-}
-
 int run_gemm(int a_unsigned, int b_unsigned, int out_float, float scale, int64_t m, int64_t n,
         int64_t k, const void *A, int64_t lda, int orderA, const void *B, int64_t ldb, int orderB,
         void *C, int64_t ldc, int orderC, int mode, void *workspace, size_t workspace_bytes,
