@@ -228,6 +228,8 @@ static int64_t tile_count(const Problem &p, Shape s) {
 // there is room for, and the shorter the k up to which one workgroup to a tile keeps up.
 // Measured over 16000 products, batches and convolutions of up to 1200 tiles of 32 x 32 (k = 16 to 60000), aligned and
 // not, the rule takes 0.793 of the time without it; 304 are slower by more than 5 %, 88 by more than a tenth.
+// (Limits for unaligned operands drawn again after that: of 4300 such products of up to 768 tiles, k = 512 to 6000, 54 are
+// slower by more than 6 % than before there was this form, 31 by more than a tenth; on average they take 0.61 of the time.)
 // us, before and after: (512, 512, 2048) k-contiguous 6.5 -> 4.2, (256, 256, 1024) 4.4 -> 3.7, (64, 4096, 11008) u8
 // packed 14.8 -> 12.9, row-major B (1024, 512, 4096) 12.3 -> 9.9;
 // a 3 x 3 convolution of 7 x 7 x 512 at batch 8 19.7 -> 7.4; unaligned (32, 256, 3600) to int8 35 -> 12.9,
@@ -266,8 +268,14 @@ static Wave wave_form(const Problem &p, bool streamed) {
   }
   if (!wave_staged_eligible(p) || tuning().pack > 0) return WAVE_NONE;
   // (with a workspace, larger products are packed)
-  const bool packable = packing_serves(p), whole = p.m % 64 == 0 && p.n % 64 == 0, few = 64 * small <= cus;
-  int64_t most = !may_split ? any : (adds ? (few ? 1024 : (strided == 2 && whole ? 512 : 1536)) : (few ? 3072 : 4096));
+  const bool packable = packing_serves(p), whole = p.m % 64 == 0 && p.n % 64 == 0, few = 4 * small <= cus;
+  // (the 64 x 64 tiles lose most where a strided operand ends inside a 16-byte piece)
+  const bool whole_pieces = (p.a_sk == 1 || p.m % 16 == 0) && (p.b_sk == 1 || p.n % 16 == 0);
+  int64_t most = any;
+  if (may_split && adds)
+    most = few ? (strided && whole_pieces ? 768 : 1024) : (strided == 2 && whole ? 512 : 1536);
+  else if (may_split)
+    most = few && strided && whole_pieces ? 2048 : (64 * small <= cus || (8 * small <= cus && !strided) ? 3072 : 4096);
   if (packable && most > 4096) most = 4096;
   // (both operands strided and a short k: packed, a choice that a test names; (300, 200, 333) 5.8 us, 4.3 here)
   if (packable && strided == 2 && k < 512) return WAVE_NONE;
@@ -276,6 +284,14 @@ static Wave wave_form(const Problem &p, bool streamed) {
   if (packable) return WAVE_NONE;
   if (tiles(32, 64) <= cus && k < most)
     return k >= (batch > 1 ? (p.accumulate ? 768 : 192) : 96) ? WAVE_32X64 : WAVE_NONE;
+  // Two or three rounds of these, against one of 64 x 64 tiles, which keep up where strided operands fill them: in ranges of k,
+  // adding into C ((512, 640, 3097) with both operands strided 14.5 us, 25.7 here, 17 of 24 such products slower; one
+  // strided, k = 1536 to 4096, 1.14 of the time over 33, 0.81 below) or under a long k (1.08 of the time over 25 from
+  // k = 4096 on, 0.55 below); and under a short k with an unsigned operand, whose partner every wave
+  // sums up ((512, 1152, 640) 8.4 and 10.7; 48 such 1.04, all others 0.51).
+  const bool filled = strided == 2 ? whole : strided && (p.a_sk != 1 ? p.m : p.n) % 128 == 0;
+  if (may_split && filled && (adds ? strided == 2 || k >= 1536 : k >= 4096)) return WAVE_NONE;
+  if (small > 2 * cus && k < 2048 && whole_pieces && p.n % 64 == 0 && (p.a_unsigned || p.b_unsigned || strided == 2)) return WAVE_NONE;
   return small <= 3 * cus && k >= 512 ? WAVE_32 : WAVE_NONE;
 }
 

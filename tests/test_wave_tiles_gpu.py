@@ -177,3 +177,21 @@ def test_which_convolutions_the_dispatcher_sends_there(gpu, kernels_of, shape, s
     O = torch.zeros(b * ((hi + 2 * pad - hf) // stride + 1) * ((wi + 2 * pad - wf) // stride + 1) * co, dtype=torch.int32, device="cuda")
     names = kernels_of(lambda: gpu.mipgemm_conv_s8u8s32(*shape, F, I, O, 0))
     assert any("wave_tile_kernel" in x for x in names) == served, names
+
+
+# (m, n, k, signs, orders of A and B, accumulate, whether this form serves), unaligned rows, no workspace: the limits are lower where
+# every strided operand is made of whole 16-byte pieces, and two or three rounds of these tiles stand beside one of 64 x 64 ones
+@pytest.mark.parametrize("m,n,k,signs,oa,ob,mode,served", [
+    (8, 624, 1900, "s8u8", 0, 0, 0, True), (8, 624, 2500, "s8s8", 0, 0, 0, False), (8, 625, 2500, "s8s8", 0, 0, 0, True),
+    (32, 384, 700, "s8u8", 0, 0, 1, True), (32, 384, 900, "s8u8", 0, 0, 1, False), (32, 381, 900, "s8u8", 0, 0, 1, True),
+    (128, 1024, 1424, "s8u8", 0, 0, 1, True), (512, 640, 3097, "s8s8", 1, 0, 1, False), (512, 640, 3097, "s8s8", 1, 0, 0, True),
+    (512, 640, 3097, "s8s8", 0, 0, 1, False), (512, 633, 3097, "s8s8", 1, 0, 1, True), (512, 1152, 640, "u8s8", 1, 0, 0, False),
+    (512, 1152, 2100, "u8s8", 1, 0, 0, True), (512, 1152, 640, "s8s8", 0, 0, 0, True), (512, 1150, 640, "u8s8", 0, 0, 0, True)])
+def test_which_unaligned_products_the_dispatcher_sends_there(gpu, kernels_of, m, n, k, signs, oa, ob, mode, served):
+    import torch
+    lda, ldb = (m if oa else k) + 3, (k if ob else n) + 3
+    A = torch.zeros(((k if oa else m), lda), dtype=torch.uint8, device="cuda")
+    B = torch.zeros(((n if ob else k), ldb), dtype=torch.uint8, device="cuda")
+    C = torch.zeros((m, n), dtype=torch.int32, device="cuda")
+    names = kernels_of(lambda: getattr(gpu, "mipgemm_%ss32" % signs)(m, n, k, A, lda, oa, B, ldb, ob, C, n, 0, mode))
+    assert any("wave_tile_kernel" in x for x in names) == served, names
