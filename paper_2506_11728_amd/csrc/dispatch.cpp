@@ -471,26 +471,32 @@ static double predicted_us(const TileForm &f, const Problem &p, int64_t cus) {
   const int64_t tiles = ((p.m + f.bm - 1) / f.bm) * ((p.n + f.bn - 1) / f.bn);
   const int64_t full = tiles / (f.per_cu * cus), rest = (tiles % (f.per_cu * cus) + cus - 1) / cus;
   const bool whole = p.m % f.bm == 0 && p.n % f.bn == 0;
-  // (rows of C that do not start on 16 bytes cost the 128-deep kernels more: (1372, 1583, 1094) packed, accumulating,
-  // 31 us on 128 x 128 tiles of theirs, 20 on 64 x 128 ones; (3151, 3795, 633), overwriting, 30 and 27 on 128 x 128 ones)
-  const bool unaligned_c = p.ldc * (p.out_float == 2 ? 1 : 4) % 16 || reinterpret_cast<uintptr_t>(p.C) % 16;
+  const double words = 1e-6 * (double)p.m * (double)p.n;
+  // What the write-back of the 128-deep kernels takes more: a little per word where rows of C do not start on 16 bytes, and
+  // 8.5 us a call that adds to a C whose rows end inside four words, which the waves at that edge fetch one by one (over 600
+  // such calls, 172 of them with such rows, 128-deep blocks lost 9 us to the best 64-deep form there and 2 elsewhere;
+  // (1372, 1583, 1094) packed 31 us, 20 on 64 x 128 tiles, but (2816, 2752, 4048) to float 62 and 72).  Overwriting it costs nothing.
+  const bool unaligned_c = (4 * p.ldc % 16 || reinterpret_cast<uintptr_t>(p.C) % 16) && p.out_float != 2;
+  const double extra = f.kind == KIND_DMA ? 0
+                                          : (unaligned_c ? words * (p.accumulate ? 0.4 : 0.2) : 0) +
+                                                (p.accumulate && p.n % 4 ? 8.5 : 0);
   // (the 64-deep kernels and the form for whole tiles read the sums that packed weights bring)
   const bool sums = !(p.ksum && (f.kind == KIND_DMA || dma_k128_eligible(p, true)));
   const double slower = 1 + (sums && p.a_unsigned ? f.a_unsigned : 0) + (sums && p.b_unsigned ? f.b_unsigned : 0) +
                         (p.a_sk == 1 ? 0 : f.a_strided) + (p.b_sk == 1 ? 0 : f.b_strided) + (whole ? f.whole : 0);
-  const double blocks = (double)p.k / 128 * slower, words = 1e-6 * (double)p.m * (double)p.n;
+  const double blocks = (double)p.k / 128 * slower;
   return (double)full * (f.block[f.per_cu - 1] * blocks + f.ends[f.per_cu - 1]) +
          (rest ? f.block[rest - 1] * blocks + f.ends[rest - 1] : 0) + words * (p.out_float == 2 ? 0 : f.words) +
          (p.accumulate ? words * f.old_words : 0) +
-         (unaligned_c && f.kind != KIND_DMA ? words * (p.accumulate ? 4 : 0.3) : 0) +
-         1e-6 * (double)(p.m + p.n) * (double)p.k * f.operands;
+         extra + 1e-6 * (double)(p.m + p.n) * (double)p.k * f.operands;
 }
 
 // The form that takes least by these times, if that is an eighth under those of the plan chosen so far.  The rules of
 // choose_plan were each measured at a few products on either side of their lines; between them one tile more than a
 // round, or a side a little over a multiple of a tile, costs up to a half.  Over 2500 other products, half
 // of them cold, with packed weights and unaligned operands among them, it takes 0.976 of the time without it: 373
-// are faster by more than 3 %, up to 1.8 times, 69 slower by more than that, 3 by more than a tenth.
+// are faster by more than 3 %, up to 1.8 times, 69 slower by more than that.  Over 3400 unaligned ones, packed, half of them
+// adding to C, 5 are slower by more than 6 %, one by more than a tenth.
 // Measured, us, before and after: (512, 5760, 6400) with an unsigned A 65 -> 36 (180 tiles of 128 x 128 for 360 of
 // 128 x 64), (3840, 640, 2176) cold 18.8 -> 12.9, (496, 4432, 3840) 29 -> 19, (3440, 8992, 640) 61 -> 43 (128-deep blocks),
 // row-major B (736, 3856, 5120) to int8 40 -> 24.

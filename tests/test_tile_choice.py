@@ -27,6 +27,17 @@ def test_choice(shape, name):
     assert _name(*shape) == name
 
 
+@pytest.mark.parametrize("m,n,k,ldc,mode,name", [
+    # rows of C that end inside four words: added to by 64-deep tiles, unless k or the tiles are many; overwritten by 128-deep ones
+    (2461, 1101, 1664, 1101, 1, "mfma_dma128x64"), (2461, 1101, 1664, 1101, 0, "mfma_dma128_k128_split"),
+    (3152, 4321, 640, 4321, 1, "mfma_dma128"), (2816, 2753, 4096, 2753, 1, "mfma_dma128_k128_split"),
+    # whole rows, at whatever alignment
+    (2464, 1104, 1664, 1104, 1, "mfma_dma128_k128_split"), (3152, 4320, 640, 4324, 1, "mfma_dma128_k128_split"),
+    (2816, 2752, 4096, 2753, 1, "mfma_dma128_k128_split")])
+def test_choice_by_what_the_edge_of_c_costs(m, n, k, ldc, mode, name):
+    assert M.mipgemm_variant_name_for_mode(m, n, k, k, 0, k, 1, ldc, 0, False, False, True, mode) == name
+
+
 def test_pinned_ranges_keep_the_tiles_that_take_them():
     """A pinned number of k ranges names the 64-deep tiles it is for: forms that do not split k stay out."""
     with M.tuning(MIPGEMM_SPLITK="4"):
