@@ -40,6 +40,18 @@ __device__ __forceinline__ void dma16_at(const uint8_t *addr, uint32_t lds_addr)
       :);
 }
 
+// A pointer that is the same in every lane, said so that it stays in SGPRs (the
+// direct loads need a scalar base).
+__device__ __forceinline__ const uint8_t *wave_uniform(const uint8_t *p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
+}
+
+// what a filter tap outside the image contributes
+static __device__ __attribute__((aligned(16))) const uint8_t outside_image[16] = {};
+
 // "my loads of the next block have landed (N newer loads may still fly), my LDS
 // reads are complete; meet the other waves": after this the next stage is
 // visible to the whole workgroup and the stage read two steps ago may be refilled.

@@ -1,6 +1,7 @@
 // MFMA tile kernel with operands streamed global -> LDS directly
-// (global_load_lds_dwordx4), four LDS stages of 64-deep k blocks and one
-// workgroup barrier per block.  Tile shapes from 64 x 64 to 256 x 256, split k,
+// (global_load_lds_dwordx4), one workgroup barrier per block: four LDS stages of 64-deep
+// k blocks, or, where two groups of waves share a tile of at most 128 x 64, stages of 128-deep
+// ones (four on 64 x 64 tiles, three on the wider).  Tile shapes from 64 x 64 to 256 x 256, split k,
 // unsigned operands, accumulate mode and ragged m / n edges.
 //
 // In the paper's terms (Section 3 and Section 4.1): the BM x 64 block of A and
@@ -19,8 +20,8 @@
 // stored.  Everything else takes the register-staged tile kernel.
 //
 // CONV: A is the lowered matrix of a convolution (paper Section 7.2) that is never
-// written out: row i is an output position, and the 64 bytes of a k block are 64
-// channels of one filter tap (c_i a multiple of 64), read straight from the image
+// written out: row i is an output position, and the 64 (128) bytes of a k block are as many
+// channels of one filter tap (c_i a multiple of that), read straight from the image
 // tensor; a tap that falls outside the image reads a block of zeros instead.
 #pragma once
 #include "dma_common.h"
@@ -57,9 +58,6 @@ struct DmaConvParams : DmaTileParams {
   ConvGeom conv;
   Divisor per_image, per_row;  // by the output positions of an image and of a row of one
 };
-
-// what a tap outside the image contributes
-static __device__ __attribute__((aligned(16))) const uint8_t conv_zero_block[16] = {};
 
 // UNS: 0 both operands signed, 1 A unsigned, 2 B unsigned; 3 and 4: as 1 and 2 with the k sums
 // of the signed operand read from P.ksum instead of being accumulated from the fragments
@@ -177,7 +175,7 @@ __global__ __launch_bounds__(NTHREADS *GROUPS) void dma_tile_kernel(std::conditi
       if constexpr (CONV) {
         const bool inside = (unsigned)(conv_iy[q] + cur_y) < (unsigned)P.conv.hi &&
                             (unsigned)(conv_ix[q] + cur_x) < (unsigned)P.conv.wi;
-        dma16_at(inside ? P.A + (conv_at[q] + cur_at) : conv_zero_block, sa + q * (16 * THREADS));
+        dma16_at(inside ? P.A + (conv_at[q] + cur_at) : outside_image, sa + q * (16 * THREADS));
       } else {
         dma16(offA[q], gA, sa + q * (16 * THREADS));
       }

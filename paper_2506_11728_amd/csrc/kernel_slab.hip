@@ -67,15 +67,6 @@ struct SlabParams {
   float scale;
 };
 
-// A pointer that is the same in every lane, said so that it stays in SGPRs (the
-// direct loads need a scalar base).
-__device__ __forceinline__ const uint8_t *wave_uniform(const uint8_t *p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
-}
-
 template <int N>
 __device__ __forceinline__ void loads_landed() {  // all but the N newest direct loads
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

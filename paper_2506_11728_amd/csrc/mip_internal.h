@@ -51,8 +51,8 @@ struct Problem {
   // int32 per column of B (a_unsigned) or row of A (b_unsigned), as pre-packed weights carry
   // them.  A kernel may use them in place of the sums it would accumulate, or ignore them.
   const int32_t *ksum = nullptr;
-  // not null: A is never materialised, the kernel gathers it from the image tensor
-  // (only the direct-to-LDS tile kernels can; a_sm is then the nominal row length k)
+  // not null: A is never materialised, the kernel gathers it from the image tensor (the direct-to-LDS
+  // tile kernels, the tiles whose waves split k and the row-segment kernel can; a_sm is then the nominal row length k)
   const ConvGeom *conv = nullptr;
   bool packed_weights = false;  // one operand is the library's packed weights
 };

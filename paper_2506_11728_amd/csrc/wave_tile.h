@@ -31,16 +31,6 @@ struct WaveConvParams : WaveTileParams {
 // STAGED: any alignment, through registers.
 enum Source { STREAMED, GATHERED, STAGED };
 
-// what a tap outside the image contributes
-static __device__ __attribute__((aligned(16))) const uint8_t outside_image[16] = {};
-
-__device__ __forceinline__ const uint8_t *uniform_pointer(const uint8_t *p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
-}
-
 // One operand of a wave's step: 16 * T rows (m or n), 128 of k, 2 * T pieces of 16 bytes per lane, piece q of
 // the 64 lanes 1 KB of LDS.
 //   KC: row r at r * 128, its 16-byte chunk c at 16 * (c ^ (r / 2 % 8)); piece q: rows 8 q .. + 7.
@@ -50,7 +40,7 @@ struct WaveOperand {
   static constexpr int LOADS = 2 * T, BYTES = LOADS * 1024;
   __device__ static __forceinline__ int row(int q, int lane) { return KC ? 8 * q + (lane >> 3) : q * (64 / T) + lane / T; }
   __device__ static __forceinline__ int swz(int row) {
-    return KC ? (row >> 1) & 7 : (T == 4 ? 2 * ((row >> 2) & 1) : (T == 8 ? 2 * ((row >> 1) & 3) : 0));
+    return KC ? (row >> 1) & 7 : (T == 4 ? 2 * ((row >> 2) & 1) : 0);
   }
   // the chunk of its row that a lane's piece q is: direct loads leave lane l's 16 bytes at 16 l
   __device__ static __forceinline__ int chunk(int q, int lane) { return (lane % (KC ? 8 : T)) ^ swz(row(q, lane)); }
@@ -149,7 +139,7 @@ __global__ __launch_bounds__(64 * W) void wave_tile_kernel(std::conditional_t<SO
   // the end, is fetched so far ahead of its place that it ends there, and shifted on its way into LDS.
   auto send = [&](int i) __attribute__((always_inline)) {
     const int step = wave + W * i;
-    const uint8_t *gb = uniform_pointer(B + step * strideB), *ga = CONV ? A : uniform_pointer(A + step * strideA);
+    const uint8_t *gb = wave_uniform(B + step * strideB), *ga = CONV ? A : wave_uniform(A + step * strideA);
     if constexpr (REGS) {
       const int left = (int)(P.k - (int64_t)step * 128 < 128 ? P.k - (int64_t)step * 128 : 128);
       auto fetch = [&](auto operand, bool kc, const uint8_t *g, const uint32_t *off, int ext, int64_t ld, v4i *r) {
